@@ -526,7 +526,7 @@ def main():
         # ms_kernel: the triplet kernel plus the sum of the per-XCD copies
         xi3 = dict(workload=f"{S.n_forests} forests nearest the centre of the eBOSS-like patch "
                             f"({S.n_pix} pixels); r to 40 Mpc/h (10 bins), theta 10 bins, cos alpha 20 bins",
-                   kernel="xi3c_kernel (entries summed in LDS per side-1 cell)" if variant == 0
+                   kernel="xi3_pair_kernel (unordered pairs, half histogram in LDS slices)" if variant != 1
                    else "xi3_kernel (global atomics per entry)",
                    entries=entries, ms_kernel=ms[-1], entries_per_s=entries / t3, dtype="f64",
                    roofline=xi3_roofline(entries, ms[-1], peaks))
@@ -545,7 +545,7 @@ def main():
         xi3["paper_grid"] = dict(
             workload=f"{S.n_forests} forests nearest the centre ({S.n_pix} pixels); r to 80 Mpc/h (20 bins), "
                      f"theta 10 bins, cos alpha 20 bins",
-            kernel={0: "xi3c_kernel", 1: "xi3_kernel", 2: "xi3w_kernel (partner lists in global scratch)"}[
+            kernel={0: "xi3_pair_kernel", 1: "xi3_kernel", 2: "xi3_pair_kernel"}[
                 st3["variant"]],
             entries=e80, ms_kernel=st3["ms_main"], entries_per_s=e80 / (st3["ms_main"] / 1e3),
             roofline=xi3_roofline(e80, st3["ms_main"], peaks))

@@ -78,7 +78,7 @@ struct GridDev {
 // Validation error bits (Globals::flag).
 enum : int32_t {
   kBadOffsets = 1, kBadFinite = 2, kBadWeight = 4, kBadDist = 8, kBadReal = 16, kBadNpix = 32,
-  kBadSub = 64, kBadCap3 = 128, kBadCapC = 256, kBadDet = 512, kBadCapW = 1024
+  kBadSub = 64, kBadCap3 = 128, kBadDet = 512
 };
 
 // ---------------------------------------------------------------- geometry
@@ -157,6 +157,15 @@ __device__ __forceinline__ double wave_max(double v) {
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
   return v;
 }
+
+// Whether the calling lane is set in a wave-uniform 64-bit lane mask: the mask
+// becomes the execution mask of the branch, with no vector instruction.
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// In a short conditional block: keeps it a branch on the execution mask (two
+// scalar instructions and 2-clock moves) where the compiler would turn it into
+// selects (4 clocks each on gfx950).
+__device__ __forceinline__ void keep_branch() { asm volatile(""); }
 
 // ---------------------------------------------------------------- host launchers
 // All launchers enqueue on `stream` and return hipSuccess or the launch error.
@@ -378,6 +387,16 @@ hipError_t launch_xi_means(int precision, const XiArgs& a, int blocks, hipStream
 
 // Three-point function (FP64): pixel positions and products, and the kernel.
 struct Point3 { double x, y, z, wd, w, pad; };
+// One partner of a vertex pixel, 64 bytes (one scalar load): unit vector of the
+// side, w d, w, the partner's forest, and for the side's (r, theta) cell c the
+// half bin of (c1 = c, c2 = 0) and the offset c n_c of c2 = c.
+struct __align__(64) Partner3 { double ux, uy, uz, wd, w; int32_t fid, row, col, pad[3]; };
+// A vertex pixel of the current batch: its list, its output slab, w d and w.
+struct Vertex3 { int64_t off; int32_t slab, pad; double wd, w; };
+// A pass of the pair kernel: side-1 cells [ca, cb) against the side-2 cells
+// [k0, k1) and, with diag, the pairs among [ca, cb) in list order; the half
+// bins [base, base + nslice).
+struct Pass3 { int32_t ca, cb, k0, k1, diag, nslice; int64_t base; };
 struct Xi3Args {
   const ForestInfo* finfo;
   const int32_t* sorted;
@@ -393,7 +412,7 @@ struct Xi3Args {
   const double* cos_theta_edges;  // [n_t + 1] cosines of the theta edges (decreasing)
   const double* cos_edges;        // [n_c + 1]
   double r_e0, r_inv, c_e0, c_inv;
-  double* num;            // n_copies copies of [R][n_bins], copy c at c * copy_stride
+  double* num;            // n_copies copies of the (half) sums, copy c at c * copy_stride
   double* wsum;
   unsigned long long* ntrip;
   int32_t n_copies;
@@ -402,23 +421,37 @@ struct Xi3Args {
   // realisation * n_sub + sub[f] of their main vertex's forest f
   const int32_t* sub;
   int32_t n_sub;
-  // wide kernel: per workgroup two partner lists of w_cap entries (5 doubles,
-  // 2 ints each) at blockIdx.x * 10 w_cap in w_dbl, blockIdx.x * 4 w_cap in w_int
-  double* w_dbl;
-  int32_t* w_int;
-  int32_t w_cap;
+  // pair kernel: neighbours of the forest at sorted position p, partners per
+  // pixel and their scan, and the batch of vertex pixels [v0, v0 + n_v)
+  const int64_t* nb_cnt;
+  const int64_t* nb_off;
+  int64_t* p_cnt;
+  const int64_t* p_off;
+  int32_t* p_most;
+  int64_t n_half;         // half bins per slab
+  Partner3* plist;
+  int32_t* cstart;        // [n_v][n_r n_t + 1] first list position of each cell
+  Vertex3* vinfo;
+  int64_t v0, n_v;
+  int64_t n_units;        // (vertex groups) * n_pass
+  int32_t group;          // vertex pixels per group
+  int32_t n_pass;
+  const Pass3* passes;
 };
 hipError_t launch_xi3_reduce(const double* num_c, const double* wsum_c, const unsigned long long* cnt_c,
                              int n_copies, int64_t stride, int64_t n, double* num, double* wsum, int64_t* ntrip,
                              hipStream_t st);
 hipError_t launch_xi3_points(const lya_forests* F, const ForestInfo* finfo, const double* delta, Point3* pts,
                              hipStream_t st);
-// kernel 0: sums each vertex's entries in LDS before the global atomics (grids
-// with xi3_can_combine; flags kBadCapC when a vertex has more partners than it
-// holds); 1: global atomics per entry; 2: as 0 with the partner list in global
-// scratch (flags kBadCapW beyond w_cap)
-hipError_t launch_xi3(const Xi3Args& a, int kernel, int blocks, hipStream_t st);
-int xi3_blocks_per_cu(int kernel);
+// every entry added to the global sums (any grid)
+hipError_t launch_xi3_direct(const Xi3Args& a, int blocks, hipStream_t st);
+// the pair kernel (grids with xi3_can_combine): partner counts of every pixel;
+// lists and half sums of a batch; full sums from the half sums
+hipError_t launch_xi3_count(const Xi3Args& a, int64_t n_forests, hipStream_t st);
+hipError_t launch_xi3_pairs(const Xi3Args& a, int64_t n_forests, int blocks, hipStream_t st);
+hipError_t launch_xi3_expand(const Xi3Args& a, int64_t n, double* num, double* wsum, int64_t* ntrip, hipStream_t st);
+int xi3_passes(int n_r, int n_t, int n_c, Pass3* out);  // number of passes; fills out unless NULL
+int xi3_blocks_per_cu(bool pairs);
 bool xi3_can_combine(int n_r, int n_t, int n_c);
 int xi3_combine_capacity();
 int xi3_max_cos_bins();

@@ -313,6 +313,8 @@ struct Worklist {
   int32_t* sorted = nullptr;
   int32_t* nbr = nullptr;
   int32_t* pair_p = nullptr;
+  int64_t* cnt = nullptr;     // neighbours of each sorted position, and their scan
+  int64_t* nb_off = nullptr;
   Item* items = nullptr;
   int64_t n_pairs = 0;
   int64_t n_items = 0;
@@ -393,6 +395,8 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
   W.sorted = a.sorted;
   W.nbr = a.nbr;
   W.pair_p = a.pair_p;
+  W.cnt = a.cnt;
+  W.nb_off = a.nb_off;
   W.n_pairs = total;
   if (chunk > 0) {
     HIP_TRY(launch_count_items(a, st));
@@ -804,8 +808,9 @@ lya_status lya_xi_covariance(lya_context* ctx, const double* num, const double* 
   return LYA_OK;
 }
 
-// partner pixels per vertex pixel held by the wide 3PCF kernel's scratch lists
+// partner limit of one vertex pixel, and of the bytes of a batch's lists
 constexpr int kXi3WideCap = 32768;
+constexpr int64_t kXi3ListBytes = (int64_t)4 << 30;
 
 namespace {
 
@@ -912,70 +917,129 @@ lya_status xi3_impl(lya_context* ctx, const lya_forests* F, const lya_grid3* G3,
     a.r_inv = r_inv;
     a.c_e0 = ce[0];
     a.c_inv = 1.0 / cd;
+    a.sub = sub;
+    a.n_sub = sub ? n_sub : 1;
+    // variant 1: the direct kernel; 0 and 2: the pair kernel with partner limits
+    // of 2048 and 32768; by default the pair kernel where the grid fits its
+    // tables (reported as 0 or 2 by the partners met), else the direct one
+    const bool fits = xi3_can_combine(nr, nt, nc);
+    if (o->variant > 2) return fail(ctx, LYA_E_INVALID, "variant %d out of range (xi3 has 3)", o->variant);
+    if ((o->variant == 0 || o->variant == 2) && !fits)
+      return fail(ctx, LYA_E_UNSUPPORTED, "grid too large for the pair kernel (variant %d)", o->variant);
+    const bool direct = o->variant == 1 || !fits;
+    const int64_t ncell = (int64_t)nr * nt;
+    a.n_half = ncell * (ncell + 1) / 2 * nc;
+    const int64_t nsum = direct ? nout : nslab * a.n_half;
     // one copy of the sums per XCD (8 on MI355X) when they fit in 1 GiB of
-    // workspace: the triplet atomics spread over 8 times the addresses
-    const int n_copies = nout * 24 * 8 <= ((int64_t)1 << 30) ? 8 : 1;
+    // workspace: the atomics spread over 8 times the addresses
+    const int n_copies = nsum * 24 * 8 <= ((int64_t)1 << 30) ? 8 : 1;
     double* cn = num;
     double* cw = wsum;
     unsigned long long* cc = (unsigned long long*)ntrip;
-    if (n_copies > 1) {
-      LYA_TRY(wst(ctx, "xi3_num_c", (size_t)(n_copies * nout), &cn));
-      LYA_TRY(wst(ctx, "xi3_wsum_c", (size_t)(n_copies * nout), &cw));
-      LYA_TRY(wst(ctx, "xi3_cnt_c", (size_t)(n_copies * nout), &cc));
-      HIP_TRY(launch_zero(cn, (size_t)(n_copies * nout) * sizeof(double), st));
-      HIP_TRY(launch_zero(cw, (size_t)(n_copies * nout) * sizeof(double), st));
-      HIP_TRY(launch_zero(cc, (size_t)(n_copies * nout) * sizeof(unsigned long long), st));
+    if (n_copies > 1 || !direct) {
+      LYA_TRY(wst(ctx, "xi3_num_c", (size_t)(n_copies * nsum), &cn));
+      LYA_TRY(wst(ctx, "xi3_wsum_c", (size_t)(n_copies * nsum), &cw));
+      LYA_TRY(wst(ctx, "xi3_cnt_c", (size_t)(n_copies * nsum), &cc));
+      HIP_TRY(launch_zero(cn, (size_t)(n_copies * nsum) * sizeof(double), st));
+      HIP_TRY(launch_zero(cw, (size_t)(n_copies * nsum) * sizeof(double), st));
+      HIP_TRY(launch_zero(cc, (size_t)(n_copies * nsum) * sizeof(unsigned long long), st));
     }
     a.num = cn;
     a.wsum = cw;
     a.ntrip = cc;
     a.n_copies = n_copies;
-    a.copy_stride = nout;
-    a.sub = sub;
-    a.n_sub = sub ? n_sub : 1;
-    // variant 0: the combining kernel (LDS sums per vertex and side-1 cell),
-    // 1: the direct kernel, 2: the wide combining kernel (partner lists in
-    // global scratch); by default 0 where the grid fits the LDS slice (else
-    // 1), and 2 instead of 0 when a pixel has more partners than 0 holds
-    const bool fits = xi3_can_combine(nr, nt, nc);
-    if (o->variant > 2) return fail(ctx, LYA_E_INVALID, "variant %d out of range (xi3 has 3)", o->variant);
-    if ((o->variant == 0 || o->variant == 2) && !fits)
-      return fail(ctx, LYA_E_UNSUPPORTED, "grid too large for the combining kernels (variant %d)", o->variant);
-    int kernel = o->variant >= 0 ? o->variant : (fits ? 0 : 1);
+    a.copy_stride = nsum;
+    const int blocks = xi3_blocks_per_cu(!direct) * ctx->n_cu;
+    ctx->stats.grid_blocks = blocks;
     tm.at(3);
-    for (;;) {
-      const int blocks = xi3_blocks_per_cu(kernel) * ctx->n_cu;
-      ctx->stats.grid_blocks = blocks;
-      ctx->stats.variant = kernel;
-      if (kernel == 2) {
-        a.w_cap = kXi3WideCap;
-        LYA_TRY(wst(ctx, "xi3_wide_dbl", (size_t)blocks * 10 * kXi3WideCap, &a.w_dbl));
-        LYA_TRY(wst(ctx, "xi3_wide_int", (size_t)blocks * 4 * kXi3WideCap, &a.w_int));
-      }
+    if (direct) {
+      ctx->stats.variant = 1;
       HIP_TRY(launch_zero(counter, 4, st));
-      HIP_TRY(launch_xi3(a, kernel, blocks, st));
+      HIP_TRY(launch_xi3_direct(a, blocks, st));
       HIP_TRY(hipMemcpyAsync(ctx->pinned, &P.glob->flag, sizeof(int32_t), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
-      const int32_t flag = *(int32_t*)ctx->pinned;
-      if (flag & kBadCap3)
+      if (*(int32_t*)ctx->pinned & kBadCap3)
         return fail(ctx, LYA_E_UNSUPPORTED, "more than %d partner pixels within r_max of one pixel",
                     xi3_partner_capacity());
-      if (flag & kBadCapW)
-        return fail(ctx, LYA_E_UNSUPPORTED, "more than %d partner pixels within r_max of one pixel",
-                    kXi3WideCap);
-      if (!(flag & kBadCapC)) break;
-      if (o->variant == 0)
-        return fail(ctx, LYA_E_UNSUPPORTED, "more than %d partner pixels within r_max of one pixel (variant 0)",
-                    xi3_combine_capacity());
-      // a pixel has more partners than the combining kernel holds: clear the
-      // flag and the sums and run the wide kernel
-      kernel = 2;
-      HIP_TRY(launch_zero(&P.glob->flag, sizeof(int32_t), st));
-      HIP_TRY(launch_zero(cn, (size_t)(n_copies * nout) * sizeof(double), st));
-      HIP_TRY(launch_zero(cw, (size_t)(n_copies * nout) * sizeof(double), st));
-      HIP_TRY(launch_zero(cc, (size_t)(n_copies * nout) * sizeof(unsigned long long), st));
+      if (n_copies > 1) HIP_TRY(launch_xi3_reduce(cn, cw, cc, n_copies, nout, nout, num, wsum, ntrip, st));
+    } else {
+      // partners of every pixel, their scan, the total and the largest count
+      const int64_t npix = F->n_pix;
+      int64_t* p_off;
+      int32_t* most;
+      LYA_TRY(wst(ctx, "xi3_cnt", (size_t)npix, &a.p_cnt));
+      LYA_TRY(wst(ctx, "xi3_off", (size_t)npix, &p_off));
+      LYA_TRY(wst(ctx, "xi3_most", 1, &most));
+      const size_t scan_bytes = worklist_cub_bytes(npix);
+      void* scan_tmp;
+      LYA_TRY(ws(ctx, "xi3_scan", scan_bytes, &scan_tmp));
+      a.nb_cnt = W.cnt;
+      a.nb_off = W.nb_off;
+      a.p_most = most;
+      a.p_off = p_off;
+      HIP_TRY(launch_zero(most, sizeof(int32_t), st));
+      HIP_TRY(launch_zero(a.p_cnt, (size_t)npix * sizeof(int64_t), st));
+      HIP_TRY(launch_xi3_count(a, F->n_forests, st));
+      HIP_TRY(launch_scan(a.p_cnt, p_off, npix, scan_tmp, scan_bytes, st));
+      char* pin = (char*)ctx->pinned;
+      HIP_TRY(hipMemcpyAsync(pin, a.p_cnt + (npix - 1), 8, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipMemcpyAsync(pin + 8, p_off + (npix - 1), 8, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipMemcpyAsync(pin + 16, most, 4, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipStreamSynchronize(st));
+      const int64_t total = *(int64_t*)pin + *(int64_t*)(pin + 8);
+      const int n_most = *(int32_t*)(pin + 16);
+      const int cap = o->variant == 0 ? xi3_combine_capacity() : kXi3WideCap;
+      if (n_most > cap)
+        return fail(ctx, LYA_E_UNSUPPORTED, "more than %d partner pixels within r_max of one pixel%s", cap,
+                    o->variant == 0 ? " (variant 0)" : "");
+      ctx->stats.variant = o->variant >= 0 ? o->variant : (n_most > xi3_combine_capacity() ? 2 : 0);
+      // batches of vertex pixels whose lists fit kXi3ListBytes (at least one pixel)
+      std::vector<int64_t> off;  // list offsets, only read where one batch does not hold them all
+      const int64_t per_vertex = (ncell + 1) * 4 + (int64_t)sizeof(Vertex3);
+      const bool split = total * (int64_t)sizeof(Partner3) + npix * per_vertex > kXi3ListBytes;
+      if (split) {
+        off.resize((size_t)npix + 1);
+        HIP_TRY(hipMemcpyAsync(off.data(), p_off, (size_t)npix * 8, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        off[npix] = total;
+      }
+      std::vector<Pass3> passes((size_t)xi3_passes(nr, nt, nc, nullptr));
+      a.n_pass = xi3_passes(nr, nt, nc, passes.data());
+      Pass3* dp;
+      LYA_TRY(wst(ctx, "xi3_passes", passes.size(), &dp));
+      HIP_TRY(hipMemcpyAsync(dp, passes.data(), passes.size() * sizeof(Pass3), hipMemcpyHostToDevice, st));
+      HIP_TRY(hipStreamSynchronize(st));
+      a.passes = dp;
+      for (int64_t v0 = 0; v0 < npix && total > 0;) {
+        int64_t v1 = npix;
+        if (split) {
+          v1 = v0 + 1;
+          while (v1 < npix && (off[v1 + 1] - off[v0]) * (int64_t)sizeof(Partner3) + (v1 + 1 - v0) * per_vertex <=
+                                  kXi3ListBytes)
+            ++v1;
+        }
+        const int64_t n_list = split ? off[v1] - off[v0] : total;
+        a.v0 = v0;
+        a.n_v = v1 - v0;
+        LYA_TRY(wst(ctx, "xi3_list", (size_t)n_list, &a.plist));
+        LYA_TRY(wst(ctx, "xi3_cstart", (size_t)(a.n_v * (ncell + 1)), &a.cstart));
+        LYA_TRY(wst(ctx, "xi3_vinfo", (size_t)a.n_v, &a.vinfo));
+        // groups of up to 64 vertex pixels (each group and pass adds its slice
+        // to the global sums once), fewer where that would leave less than ~8
+        // work items per workgroup; an item's counts stay below 2^32
+        int64_t group = a.n_v * a.n_pass / (8 * (int64_t)blocks);
+        const int64_t most_pairs = (int64_t)n_most * n_most / 2 + 1;
+        if (group > ((int64_t)1 << 32) / most_pairs - 1) group = ((int64_t)1 << 32) / most_pairs - 1;
+        a.group = (int32_t)(group < 1 ? 1 : (group > 64 ? 64 : group));
+        a.n_units = (a.n_v + a.group - 1) / a.group * a.n_pass;
+        if (a.n_units > UINT32_MAX - 2 * (int64_t)blocks)
+          return fail(ctx, LYA_E_UNSUPPORTED, "too many vertex pixels and passes");
+        HIP_TRY(launch_zero(counter, 4, st));
+        HIP_TRY(launch_xi3_pairs(a, F->n_forests, blocks, st));
+        v0 = v1;
+      }
+      HIP_TRY(launch_xi3_expand(a, nout, num, wsum, ntrip, st));
     }
-    if (n_copies > 1) HIP_TRY(launch_xi3_reduce(cn, cw, cc, n_copies, nout, nout, num, wsum, ntrip, st));
     tm.at(4);
   } else {
     tm.at(1);

@@ -352,3 +352,19 @@ def test_xi3_subsamples_invalid_id(lib):
     with pytest.raises(LyaError) as ei:
         run3_sub(lib, F, grid3(), np.array([0, 1, 2, 3], np.int32), 3)
     assert ei.value.status == LYA_E_INVALID
+
+
+@pytest.mark.parametrize("n_r,n_t,n_c,cos_lo", [
+    (10, 10, 200, -1.0),   # a half-histogram row (up to 20000 bins) longer than the LDS slice: rows in parts
+    (16, 1, 240, -1.0),    # rows of 240 .. 3840 bins: the first fills the slice exactly
+    (3, 40, 5, -0.3),      # several rows per pass; triangles below the cos alpha range leave the grid
+    (1, 1, 1, -1.0),       # one bin: every pair inside one cell
+])
+def test_xi3_pair_kernel_passes_vs_oracle(lib, n_r, n_t, n_c, cos_lo):
+    """The pair kernel's cut of the half histogram into passes: whole rows,
+    parts of a row, a row of exactly the slice's size, and a single cell (both
+    orders of a pair in one bin), on two realisations."""
+    parts = [truncate(make_patch(10, 0.5, 90 + r, z_range=(2.1, 2.3)), 20) for r in range(2)]
+    F = concat_realisations(parts)
+    G3 = O.Grid3(np.linspace(0.0, 35.0, n_r + 1), np.linspace(0.0, np.pi, n_t + 1), np.linspace(cos_lo, 1.0, n_c + 1))
+    check3(run3(lib, F, G3, expect_variant=0), O.xi3_sums(F, G3), f"passes {n_r} {n_t} {n_c}")
