@@ -121,11 +121,12 @@ typedef struct {
   int32_t precision;          /* lya_precision */
   int32_t eta;                /* lya_eta: projection used by lya_dmat and project_deltas */
   int32_t project_deltas;     /* lya_xi: replace delta by eta delta per forest first */
-  int32_t autotune;           /* pick kernel variants by timing them on this input */
+  int32_t autotune;           /* lya_dmat: pick the kernel variant by timing them on
+                                 this input (lya_xi chooses by a rule) */
   int32_t validate;           /* check array contents on the device (one extra sync) */
   int32_t timing;             /* record per-stage device times (see lya_stats) */
   int32_t variant;            /* >= 0 forces that kernel variant; -1 lets the
-                                 autotuner (or the default) choose */
+                                 autotuner (or the rule) choose */
   int32_t counters;           /* lya_dmat: count the work done (in-grid pairs,
                                  outer-product FMAs, out-of-window pairs; see
                                  lya_stats); adds a little work to the kernel */

@@ -196,11 +196,13 @@ __global__ void count_items_kernel(WorklistArgs a) {
   a.item_cnt[p] = (a.cnt[p] + a.chunk - 1) / a.chunk;
 }
 
-__global__ void fill_items_kernel(WorklistArgs a) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// One wave per sorted position, lanes over its items.
+__global__ __launch_bounds__(256) void fill_items_kernel(WorklistArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (p >= a.n_forests) return;
-  const int64_t n = a.cnt[p], base = a.nb_off[p], o = a.item_off[p];
-  for (int64_t k = 0; k * a.chunk < n; ++k) {
+  const int64_t n = a.cnt[p], base = a.nb_off[p], o = a.item_off[p], m = a.item_cnt[p];
+  for (int64_t k = lane; k < m; k += 64) {
     Item it;
     it.nb_begin = base + k * a.chunk;
     it.p = (int32_t)p;
@@ -208,6 +210,15 @@ __global__ void fill_items_kernel(WorklistArgs a) {
     it.nb_count = (int32_t)(left < a.chunk ? left : a.chunk);
     a.items[o + k] = it;
   }
+}
+
+__global__ void item_slabs_kernel(WorklistArgs a, int64_t n_items, const int32_t* sub, int32_t n_sub, uint64_t* keys,
+                                  int32_t* idx) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n_items) return;
+  const int f = a.sorted[a.items[t].p];
+  keys[t] = (uint64_t)a.finfo[f].real * (uint64_t)n_sub + (uint64_t)sub[f];
+  idx[t] = (int32_t)t;
 }
 
 inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -270,9 +281,9 @@ size_t sort_keys_bytes(int64_t n) {
 }
 
 hipError_t launch_sort_keys(uint64_t* keys_in, uint64_t* keys_out, int32_t* v_in, int32_t* v_out,
-                            int64_t n, void* tmp, size_t bytes, hipStream_t st) {
+                            int64_t n, void* tmp, size_t bytes, hipStream_t st, unsigned bits) {
   if (n == 0) return hipSuccess;
-  return rocprim::radix_sort_pairs(tmp, bytes, keys_in, keys_out, v_in, v_out, (size_t)n, 0, 64, st);
+  return rocprim::radix_sort_pairs(tmp, bytes, keys_in, keys_out, v_in, v_out, (size_t)n, 0, bits, st);
 }
 
 hipError_t launch_count_items(const WorklistArgs& a, hipStream_t st) {
@@ -283,7 +294,14 @@ hipError_t launch_count_items(const WorklistArgs& a, hipStream_t st) {
 
 hipError_t launch_fill_items(const WorklistArgs& a, hipStream_t st) {
   if (a.n_forests == 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_items_kernel, dim3(nblk(a.n_forests, 256)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(fill_items_kernel, dim3(nblk(a.n_forests, 4)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_item_slabs(const WorklistArgs& a, int64_t n_items, const int32_t* sub, int32_t n_sub, uint64_t* keys,
+                             int32_t* idx, hipStream_t st) {
+  if (n_items == 0) return hipSuccess;
+  hipLaunchKernelGGL(item_slabs_kernel, dim3(nblk(n_items, 256)), dim3(256), 0, st, a, n_items, sub, n_sub, keys, idx);
   return hipGetLastError();
 }
 

@@ -3,42 +3,66 @@
 // pair count), over every work item of the forest-pair list.
 //
 // Layout of the work.  A work item is one forest f (at sorted position p)
-// against up to kChunkMax neighbour forests g.  The neighbours' pixels form
-// one concatenated stream; each wave takes 64 consecutive stream pixels, one
-// per lane (coalesced loads, every lane busy except at the stream's end), and
-// loops over the pixels of f, which are identical for all lanes and are read
-// through the scalar cache.  Each lane thus evaluates one pixel pair per
-// iteration: r_par = |D_i - D_j| c, r_perp = (D_i + D_j) s with the lane's own
-// (s, c), then the bin and the two products.
+// against a few neighbour forests g; each wave takes items by itself.  The
+// neighbours' pixels form one concatenated stream; the wave takes 64
+// consecutive stream pixels, one per lane, and loops over the pixels of f,
+// which are identical for all lanes and come through scalar loads.  Each lane
+// thus evaluates one pixel pair per iteration: r_par = |D_i - D_j| c, r_perp =
+// (D_i + D_j) s with the lane's own (s, c), then the bin and the two products.
 //
-// Histograms live in LDS, one copy per workgroup (FP64 sums, u32 counts), and
-// are added to the global FP64 outputs when the workgroup finishes, when the
-// realisation changes, or before a count could overflow.
+// Geometry.  Both forms compute the bin coordinates x = (r - e0) / dr in FP64
+// (on gfx950 an FP64 add, multiply or FMA issues in the 4 clocks of an FP32
+// FMA, compare or conversion) as 2^20 + x + g: the upper word then holds the
+// bin and the lower one the fraction, so a bin costs no conversion and the edge
+// guard is one unsigned compare per axis.  A pair whose fraction is within g =
+// 1e-8 of an edge (the coordinates are good to ~3e-10) is binned by comparing
+// its r with the edge array.  The FP32 form's products are FP32.
 //
-// FP32 form.  Distances are re-centred on dc so FP32 keeps ~1e-4 Mpc/h.  A pair
-// whose FP32 bin coordinate lies within the proven error bound (tau) of a bin
-// edge is re-evaluated in FP64 with the same operations as the FP64 form and
-// binned by comparison with the FP64 edges, so the FP32 and FP64 forms bin
-// every pair identically.  Products are FP32 and are accumulated in FP64 in
-// LDS (ds_add_f64 is native on gfx950 and moves the same bytes as a hi/lo
-// pair of FP32 accumulators); with run-length accumulation, consecutive
-// products of the same bin are first summed in FP32 registers (runs end at
-// every 32nd pixel of f, so a run holds at most 32 products).
+// Runs.  Consecutive pixels of f that fall in one bin are summed in registers
+// in the form's arithmetic (a run also ends at every 32nd pixel of f); the run
+// sums are added in FP64.  An LDS atomic costs its CU 8 (f64) or 4 (u32)
+// clocks whatever number of lanes is on, and the lanes' runs end at different
+// iterations, so a finished run waits in its lane (one slot) and the waiting
+// runs go to LDS together when some lane needs its slot again.  On the
+// eBOSS-like workload that is every second iteration instead of four of five
+// (22 lanes each), with 0.5 Mpc/h pixels one in nine instead of one in two.
+// Pairs outside the grid form runs in a bin of their own that is never read.
 //
-// Deterministic form (DET).  The run sums of the run-length form (at most 32
-// products of one lane, summed in a fixed order in the form's arithmetic) are
-// scaled by 2^s (s per realisation, from its largest |w d| and w, so that
-// |run sum| 2^s <= 2^55), rounded to integers and summed exactly as two 64-bit
-// words (low 28 bits and the rest), in LDS and then in global memory; integer
-// addition does not depend on the order, so the sums are bitwise reproducible
-// and identical for a realisation alone or batched (a run depends only on the
-// forest pair and the pixel, not on how the work is split).
+// Histograms live in LDS, one copy per workgroup (FP64 sums, u32 counts, each
+// an array of its own: consecutive bins then fall on consecutive banks), and
+// are added to the global FP64 outputs at the end, when the realisation changes
+// and before a count could overflow.  The waves of a workgroup meet only
+// there: items are ordered by output slab, and a wave whose next item needs
+// another slab (or would overflow the counts) waits at a barrier that the
+// others reach in turn; they then flush and go on with the smallest slab any of
+// them holds.  With several slabs a workgroup takes its tickets in runs, so
+// that it meets a few of the slabs only: with all workgroups going through all
+// slabs together, 26 subsamples of 1961 forests spent 9 of 11 ms in flushes.
 //
-// Bin means.  The MEANS form also sums w_i w_j x_par, w_i w_j x_perp (the bin
-// coordinates x = (r - e0) / dr the binning already computes) and
-// w_i w_j (z_i + z_j), with the pixel redshift z packed in the record's fourth
-// slot; a finalisation turns them into the weighted mean r_par, r_perp and z
-// of each bin, the coordinate columns of the correlation output.
+// Deterministic form (DET).  The run sums (at most 32 products of one lane,
+// summed in a fixed order in the form's arithmetic) are scaled by 2^s (s per
+// realisation, from its largest |w d| and w, so that |run sum| 2^s <= 2^55),
+// rounded to integers and summed exactly in integers, in LDS and then in
+// global memory; integer addition does not depend on the order, so the sums are
+// bitwise reproducible and identical for a realisation alone or batched (a run
+// depends only on the forest pair and the pixel, not on how the work is split).
+//
+// Bin means.  The MEANS form also sums w_i w_j x_par, w_i w_j x_perp (bin
+// coordinates in the form's arithmetic) and w_i w_j (z_i + z_j), with the
+// pixel redshift z packed with the records; a finalisation turns them into the
+// weighted mean r_par, r_perp and z of each bin, the coordinate columns of the
+// correlation output.
+//
+// Measured (MI355X, 8000 forests at 75 / deg^2, 50 x 50 bins to 200 Mpc/h,
+// 4.35e10 candidate and 2.4e10 in-grid pairs, whole call): 19.5 ms, against
+// 26.8 of workgroup-wide items with 16-byte bins, FP32 geometry and an atomic at
+// each iteration with the end of a run; FP64, 5000 forests: 10.0 against 13.9; bin
+// means (5000 forests at 100 / deg^2) 26.0 against 33.6, the deterministic form 16.0
+// against 24.7, 0.5 Mpc/h pixels (4.3e11 candidate pairs) 122 against 214.  Bound by
+// the vector units (about 19 instructions an iteration, three quarters of the time)
+// and by the LDS atomics next.
+#include <type_traits>
+
 #include "lya_bin.h"
 #include "lya_common.h"
 
@@ -47,68 +71,77 @@ namespace lya {
 namespace {
 
 constexpr unsigned kRunMax = 32;
+constexpr int kWaitAll = 0x7fffffff;
 
-struct NbTable {
-  int64_t pix0[kChunkMax];
-  int32_t pref[kChunkMax + 1];
-  double s64[kChunkMax], c64[kChunkMax];
-};
+// 2^20 and its upper word: 2^20 + x has floor(x) in the low bits of its upper
+// word and the fraction in its lower word, in units of 2^-32.
+constexpr double kMagic = 1048576.0;
+constexpr uint32_t kMagicHi = 0x41300000u;
+constexpr double kGuard = 1e-8;        // edge guard, bins
+constexpr uint32_t kGuard2 = 86u;      // 2 kGuard in units of 2^-32
 
 // Loads through the constant address space: with a wave-uniform address the
 // compiler emits scalar (SMEM) loads.  Native vector types are used because
 // class copies cannot bind to address-space-qualified objects.
-typedef float lya_f4 __attribute__((ext_vector_type(4)));
-typedef double lya_d4 __attribute__((ext_vector_type(4)));
+typedef int lya_i16 __attribute__((ext_vector_type(16)));
+typedef int lya_i4 __attribute__((ext_vector_type(4)));
+typedef int lya_i8 __attribute__((ext_vector_type(8)));
+typedef int lya_i2 __attribute__((ext_vector_type(2)));
+#define LYA_CONST(T, p) (*(const __attribute__((address_space(4))) T*)(p))
 
-__device__ __forceinline__ Rec32 load_uniform(const Rec32* p) {
-  const lya_f4 v = *(const __attribute__((address_space(4))) lya_f4*)p;
-  return Rec32{v.x, v.y, v.z, v.w};
-}
-__device__ __forceinline__ Rec64 load_uniform(const Rec64* p) {
-  const lya_d4 v = *(const __attribute__((address_space(4))) lya_d4*)p;
-  return Rec64{v.x, v.y, v.z, v.w};
-}
-__device__ __forceinline__ double load_uniform(const double* p) {
-  return *(const __attribute__((address_space(4))) double*)p;
-}
+// A pixel of f in scalar registers.
+template <typename T> struct UPix { double d; T wd, w; };
 
-// Four FP32 records (64 bytes) or two FP64 records per scalar load.
-typedef float lya_f16 __attribute__((ext_vector_type(16)));
-typedef double lya_d8 __attribute__((ext_vector_type(8)));
-template <typename Rec> struct Batch;
-template <> struct Batch<Rec32> {
+// Four FP32 records or two FP64 records (64 bytes) per scalar load.
+template <typename T> struct Batch;
+template <> struct Batch<float> {
   static constexpr int N = 4;
-  Rec32 r[4];
-  __device__ __forceinline__ void load(const Rec32* p) {
-    const lya_f16 v = *(const __attribute__((address_space(4))) lya_f16*)p;
-    r[0] = Rec32{v[0], v[1], v[2], v[3]};
-    r[1] = Rec32{v[4], v[5], v[6], v[7]};
-    r[2] = Rec32{v[8], v[9], v[10], v[11]};
-    r[3] = Rec32{v[12], v[13], v[14], v[15]};
+  UPix<float> r[4];
+  __device__ __forceinline__ void load(const XRec32* p) {
+    const lya_i16 v = LYA_CONST(lya_i16, p);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      r[u] = UPix<float>{__hiloint2double(v[4 * u + 1], v[4 * u]), __int_as_float(v[4 * u + 2]), __int_as_float(v[4 * u + 3])};
   }
 };
-template <> struct Batch<Rec64> {
+template <> struct Batch<double> {
   static constexpr int N = 2;
-  Rec64 r[2];
+  UPix<double> r[2];
   __device__ __forceinline__ void load(const Rec64* p) {
-    const lya_d8 v = *(const __attribute__((address_space(4))) lya_d8*)p;
-    r[0] = Rec64{v[0], v[1], v[2], v[3]};
-    r[1] = Rec64{v[4], v[5], v[6], v[7]};
+    const lya_i16 v = LYA_CONST(lya_i16, p);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      r[u] = UPix<double>{__hiloint2double(v[8 * u + 1], v[8 * u]), __hiloint2double(v[8 * u + 3], v[8 * u + 2]),
+                          __hiloint2double(v[8 * u + 5], v[8 * u + 4])};
   }
 };
+__device__ __forceinline__ UPix<float> load_pix(const XRec32* p) {
+  const lya_i4 v = LYA_CONST(lya_i4, p);
+  return UPix<float>{__hiloint2double(v[1], v[0]), __int_as_float(v[2]), __int_as_float(v[3])};
+}
+__device__ __forceinline__ UPix<double> load_pix(const Rec64* p) {
+  const lya_i8 v = LYA_CONST(lya_i8, p);
+  return UPix<double>{__hiloint2double(v[1], v[0]), __hiloint2double(v[3], v[2]), __hiloint2double(v[5], v[4])};
+}
 
-// Fixed-point terms of the deterministic form: q = rint(x), |q| <= 2^55, split
-// as q = hi 2^28 + lo with 0 <= lo < 2^28; the two words are summed in separate
-// 64-bit integers (two's complement for hi), exact for fewer than 2^36 terms.
+// Fixed-point terms of the deterministic form: q = rint(x), |q| <= 2^55.  A
+// workgroup sums them in LDS in a 64-bit low and a 32-bit high word; its sum S
+// goes to the global sums split as S = hi 2^28 + lo, 0 <= lo < 2^28, the two
+// words in separate 64-bit integers (two's complement for hi), exact for fewer
+// than 2^36 terms.  The finalisation carries lo into hi, so the result depends
+// only on the total.
 // A term is a run sum of at most kRunMax = 2^5 products below m^2, so the
 // scale is 2^(kDetBits - 2 e) = 2^(50 - 2 e) for m < 2^e.
 constexpr int kDetShift = 28;
 constexpr int kDetBits = 50;
 
-__device__ __forceinline__ void det_add(unsigned long long* h, double x) {
+// Adds q to the 96-bit integer (hi, lo): the upper word changes only on a carry
+// or borrow, once in some hundred additions.
+__device__ __forceinline__ void det_add(unsigned long long* lo, int* hi, double x) {
   const long long q = __double2ll_rn(x);
-  atomicAdd(&h[0], (unsigned long long)(q & ((1ll << kDetShift) - 1)));
-  atomicAdd(&h[1], (unsigned long long)(q >> kDetShift));
+  const unsigned long long old = atomicAdd(lo, (unsigned long long)q);
+  const int c = (int)(old + (unsigned long long)q < old) + (q < 0 ? -1 : 0);
+  if (c != 0) atomicAdd(hi, c);
 }
 
 // s for products below m^2, m given by the bits of a non-negative double:
@@ -124,329 +157,588 @@ __device__ __forceinline__ int det_shift(unsigned long long mbits) {
 }
 
 template <typename T> struct RecOf;
-template <> struct RecOf<float> { using type = Rec32; };
+template <> struct RecOf<float> { using type = XRec32; };
 template <> struct RecOf<double> { using type = Rec64; };
 
-// LDS histograms: hNW[2 L] = sum w_i d_i w_j d_j, hNW[2 L + 1] = sum w_i w_j
-// (interleaved, so one address serves both), hn[L] = pair count; with MEANS,
-// hM[3 L + c] = sum w_i w_j (x_par, x_perp, z_i + z_j)[c].
-template <int BLOCK, bool MEANS>
-__device__ void flush_hist(const XiArgs& a, double* hNW, double* hM, unsigned* hn, int real) {
-  const int NP = a.g.n_par, NT = a.g.n_perp, nb = NP * NT;
-  const int64_t base = (int64_t)real * nb;
-  const int64_t nout = a.n_out;
-  for (int L = threadIdx.x; L < nb; L += BLOCK) {
+// LDS sums: arrays of nd = n_bins + 64 entries, the last 64 for the pairs
+// outside the grid, one per lane (one for all would be a conflict of all).  FP64 sums first: N, W and, with MEANS, w w x_par, w w x_perp, w w
+// (z_i + z_j); DET: the 64-bit low words of N and W, then their 32-bit high
+// words; the u32 counts last.
+template <bool MEANS, bool DET>
+constexpr int n_f64() { return MEANS ? 5 : 2; }
+template <bool MEANS, bool DET>
+constexpr size_t smem_per_bin() {
+  return n_f64<MEANS, DET>() * sizeof(double) + (DET ? 2 * sizeof(int) : 0) + sizeof(unsigned);
+}
+
+// The kernel's arguments, read where they are used: what only the fetch of an
+// item or a flush needs does not stay in scalar registers through the pair loop
+// (8 waves per SIMD leave 80).
+typedef const __attribute__((address_space(4))) XiArgs* KArgs;
+__device__ __forceinline__ KArgs kargs() {
+  KArgs p = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// Adds the LDS sums to the output slab and clears them (the whole workgroup).  Lanes
+// take consecutive output bins, so that a wave's atomics fall into few cache lines,
+// and each workgroup starts at another bin: they end together, and at one address
+// atomics take 12 ns each.
+template <int BLOCK, bool MEANS, bool DET>
+__device__ __forceinline__ void flush_hist(double* h, int slab) {
+  const KArgs a = kargs();
+  const int NP = a->g.n_par, NT = a->g.n_perp, nb = NP * NT, nd = nb + 64;
+  const int64_t base = (int64_t)slab * nb;
+  int* hc = (int*)(h + n_f64<MEANS, DET>() * nd);  // DET high words
+  unsigned* hn = (unsigned*)(hc + (DET ? 2 * nd : 0));
+  const int first = (int)((blockIdx.x * 64u) % (unsigned)nb);
+  for (int n = threadIdx.x; n < nb; n += BLOCK) {
+    const int o = n + first < nb ? n + first : n + first - nb, kp = o / NT, L = (o - kp * NT) * NP + kp;
     const unsigned c = hn[L];
-    if (c) {
-      const int kp = L % NP, kt = L / NP;
-      const int64_t A = base + (int64_t)kp * NT + kt;
-      atomicAdd(&a.num[A], hNW[2 * L]);
-      atomicAdd(&a.wsum[A], hNW[2 * L + 1]);
-      atomicAdd(&a.npairs[A], (unsigned long long)c);
+    if (c == 0u) continue;
+    hn[L] = 0u;
+    const int64_t A = base + o;
+    atomicAdd(&a->npairs[A], (unsigned long long)c);
+    if constexpr (DET) {
+      unsigned long long* hq = (unsigned long long*)h;
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const unsigned long long lo = hq[w * nd + L];
+        const long long hi = hc[w * nd + L];
+        atomicAdd(&a->det_acc[4 * A + 2 * w], lo & ((1ull << kDetShift) - 1));
+        atomicAdd(&a->det_acc[4 * A + 2 * w + 1],
+                  ((unsigned long long)hi << (64 - kDetShift)) | (lo >> kDetShift));
+        hq[w * nd + L] = 0ull;
+        hc[w * nd + L] = 0;
+      }
+    } else {
+      atomicAdd(&a->num[A], h[L]);
+      atomicAdd(&a->wsum[A], h[nd + L]);
+      h[L] = 0.0;
+      h[nd + L] = 0.0;
       if constexpr (MEANS) {
-        atomicAdd(&a.msum[A], hM[3 * L]);
-        atomicAdd(&a.msum[nout + A], hM[3 * L + 1]);
-        atomicAdd(&a.msum[2 * nout + A], hM[3 * L + 2]);
+#pragma unroll
+        for (int w = 0; w < 3; ++w) {
+          atomicAdd(&a->msum[w * a->n_out + A], h[(2 + w) * nd + L]);
+          h[(2 + w) * nd + L] = 0.0;
+        }
       }
     }
-    hNW[2 * L] = 0.0;
-    hNW[2 * L + 1] = 0.0;
-    if constexpr (MEANS) {
-      hM[3 * L] = 0.0;
-      hM[3 * L + 1] = 0.0;
-      hM[3 * L + 2] = 0.0;
-    }
-    hn[L] = 0u;
   }
 }
 
-// Deterministic form's LDS sums: hq[4 L + c] (N low, N high, W low, W high),
-// hn[L] = pair count.
-template <int BLOCK>
-__device__ void flush_det(const XiArgs& a, unsigned long long* hq, unsigned* hn, int real) {
-  const int NP = a.g.n_par, NT = a.g.n_perp, nb = NP * NT;
-  const int64_t base = (int64_t)real * nb;
-  for (int L = threadIdx.x; L < nb; L += BLOCK) {
-    const unsigned c = hn[L];
-    if (c) {
-      const int kp = L % NP, kt = L / NP;
-      const int64_t A = base + (int64_t)kp * NT + kt;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) atomicAdd(&a.det_acc[4 * A + w], hq[4 * L + w]);
-      atomicAdd(&a.npairs[A], (unsigned long long)c);
-    }
-#pragma unroll
-    for (int w = 0; w < 4; ++w) hq[4 * L + w] = 0ull;
-    hn[L] = 0u;
-  }
+// A wave's item: first pixel, stream position, s and c of its neighbours.
+struct WaveTab {
+  int64_t pix[kChunkMax];
+  double s[kChunkMax], c[kChunkMax];
+  int32_t pos[kChunkMax];
+};
+
+__device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ double uniform(double x) {
+  return __hiloint2double(uniform(__double2hiint(x)), uniform(__double2loint(x)));
 }
 
-template <typename T, int BLOCK, bool RLE, bool ZLO, bool MEANS, bool DET = false>
-__global__ __launch_bounds__(BLOCK) void xi_kernel(XiArgs a) {
-  static_assert(RLE || !MEANS, "bin means are accumulated by the run-length form");
+// Lanes whose bin is not that of the run they sum (their low 16 bits differ).
+__device__ __forceinline__ uint64_t other_bin(uint32_t L, uint32_t rkey) {
+  uint64_t m;
+  asm("v_cmp_ne_u16_e64 %0, %1, %2" : "=s"(m) : "v"(L), "v"(rkey));
+  return m;
+}
+
+// In the lanes of mask m: the run (rkey, aN, aW) becomes the waiting run
+// (pkey, pN, pW), ended before pixel i (i16 = i << 16), and a new run starts in
+// bin L.  Written out, under the mask and without a branch, so that the updates
+// happen in place: from a branch the compiler makes a copy of every value on
+// each side of it, as many instructions again.
+__device__ __forceinline__ void change_run(uint64_t m, uint32_t L, uint32_t i16, uint32_t& pkey, uint32_t& rkey,
+                                           float& pN, float& pW, float& aN, float& aW) {
+  uint64_t t;
+  asm volatile("s_and_saveexec_b64 %[t], %[m]\n\t"
+               "v_add_u32_e32 %[pk], %[i], %[rk]\n\t"
+               "v_mov_b32_e32 %[pn], %[an]\n\t"
+               "v_mov_b32_e32 %[pw], %[aw]\n\t"
+               "v_subrev_u32_e32 %[rk], %[i], %[L]\n\t"
+               "v_mov_b32_e32 %[an], 0\n\t"
+               "v_mov_b32_e32 %[aw], 0\n\t"
+               "s_mov_b64 exec, %[t]"
+               : [t] "=&s"(t), [pk] "+v"(pkey), [rk] "+v"(rkey), [pn] "+v"(pN), [pw] "+v"(pW),
+                 [an] "+v"(aN), [aw] "+v"(aW)
+               : [m] "s"(m), [L] "v"(L), [i] "s"(i16)
+               : "scc");
+}
+__device__ __forceinline__ void change_run(uint64_t m, uint32_t L, uint32_t i16, uint32_t& pkey, uint32_t& rkey,
+                                           double& pN, double& pW, double& aN, double& aW) {
+  uint64_t t;
+  asm volatile("s_and_saveexec_b64 %[t], %[m]\n\t"
+               "v_add_u32_e32 %[pk], %[i], %[rk]\n\t"
+               "v_mov_b64_e32 %[pn], %[an]\n\t"
+               "v_mov_b64_e32 %[pw], %[aw]\n\t"
+               "v_subrev_u32_e32 %[rk], %[i], %[L]\n\t"
+               "v_mov_b64_e32 %[an], 0\n\t"
+               "v_mov_b64_e32 %[aw], 0\n\t"
+               "s_mov_b64 exec, %[t]"
+               : [t] "=&s"(t), [pk] "+v"(pkey), [rk] "+v"(rkey), [pn] "+v"(pN), [pw] "+v"(pW),
+                 [an] "+v"(aN), [aw] "+v"(aW)
+               : [m] "s"(m), [L] "v"(L), [i] "s"(i16)
+               : "scc");
+}
+// In the lanes of mask m: p = a, a = 0 (the bin means' further sums).
+__device__ __forceinline__ void change_sum(uint64_t m, float& p, float& a) {
+  uint64_t t;
+  asm volatile("s_and_saveexec_b64 %[t], %[m]\n\tv_mov_b32_e32 %[p], %[a]\n\tv_mov_b32_e32 %[a], 0\n\ts_mov_b64 exec, %[t]"
+               : [t] "=&s"(t), [p] "+v"(p), [a] "+v"(a) : [m] "s"(m) : "scc");
+}
+__device__ __forceinline__ void change_sum(uint64_t m, double& p, double& a) {
+  uint64_t t;
+  asm volatile("s_and_saveexec_b64 %[t], %[m]\n\tv_mov_b64_e32 %[p], %[a]\n\tv_mov_b64_e32 %[a], 0\n\ts_mov_b64 exec, %[t]"
+               : [t] "=&s"(t), [p] "+v"(p), [a] "+v"(a) : [m] "s"(m) : "scc");
+}
+
+// Two workgroups of 16 waves fill a CU's wave slots at 2500 bins (50 KB of LDS
+// for the sums, 14 KB for the waves' items); MEANS needs 110 KB, one workgroup.
+template <typename T, int BLOCK, bool ZLO, bool RUNS, bool MEANS, bool DET>
+__global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
   static_assert(!(DET && MEANS), "the deterministic form has no bin means");
+  static_assert(RUNS || !(DET || MEANS), "these forms sum runs");
+  static_assert((kChunkMax & (kChunkMax - 1)) == 0, "the search for a stream pixel's neighbour halves it");
   using Rec = typename RecOf<T>::type;
   extern __shared__ double smem[];
-  __shared__ NbTable tb;
-  __shared__ int64_t s_item;
+  __shared__ WaveTab tabs[BLOCK / 64];
+  __shared__ int s_next;
+  __shared__ unsigned long long s_pairs;  // candidate pairs added since the last flush
+  __shared__ unsigned s_lo, s_hi;         // several slabs: the workgroup's run of tickets,
+  __shared__ int s_done;                  // and that there is no further one
+  __shared__ int s_gone;                  // one slab: counters found to have no ticket left
 
-  const int NP = a.g.n_par, NT = a.g.n_perp, nb = NP * NT;
-  double* hNW = smem;
-  double* hM = smem + 2 * nb;
-  unsigned* hn = (unsigned*)(smem + (DET ? 4 : (MEANS ? 5 : 2)) * nb);
-  unsigned long long* hq = (unsigned long long*)smem;  // DET
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-
-  for (int L = threadIdx.x; L < nb; L += BLOCK) {
-    if constexpr (DET) {
-      hq[4 * L] = hq[4 * L + 1] = hq[4 * L + 2] = hq[4 * L + 3] = 0ull;
-      hn[L] = 0u;
-      continue;
-    }
-    hNW[2 * L] = 0.0;
-    hNW[2 * L + 1] = 0.0;
-    if constexpr (MEANS) {
-      hM[3 * L] = 0.0;
-      hM[3 * L + 1] = 0.0;
-      hM[3 * L + 2] = 0.0;
-    }
-    hn[L] = 0u;
+  const int lane = threadIdx.x & 63;
+  WaveTab& tab = tabs[uniform((int)threadIdx.x >> 6)];
+  const int NP = kargs()->g.n_par, nb = NP * kargs()->g.n_perp, nd = nb + 64;
+  for (int e = threadIdx.x; e < nd * (int)(smem_per_bin<MEANS, DET>() / 4); e += BLOCK) ((unsigned*)smem)[e] = 0u;
+  if (threadIdx.x == 0) {
+    s_next = kWaitAll;
+    s_pairs = 0ull;
+    s_lo = s_hi = 0u;
+    s_gone = 0;
   }
+  double* const hN = smem;
+  int* const hc = (int*)(smem + n_f64<MEANS, DET>() * nd);
+  unsigned* const hn = (unsigned*)(hc + (DET ? 2 * nd : 0));
 
-  const Rec* __restrict__ recs;
-  if constexpr (sizeof(T) == 4) recs = a.rec32; else recs = a.rec64;
+  const double mp = uniform(kMagic + kGuard - kargs()->g.e0_par * kargs()->g.inv_par);
+  const double uphi = uniform(kMagic + NP + 2.0 * kGuard), uthi = uniform(kMagic + kargs()->g.n_perp + 2.0 * kGuard);
+  // non-uniform edges: every pair in range is binned from the edge arrays
+  const uint32_t thr = kargs()->g.exact_all ? 0xffffffffu : kGuard2;
+  // bins are carried as L = k_perp NP + k_par + G, G what the two upper words add
+  const uint32_t G = (kMagicHi & 0xffffffu) * (uint32_t)NP + kMagicHi, Lout = G + (uint32_t)(nb + lane);
+  int shN = 0, shW = 0;  // DET: s of the current realisation
 
-  BinK<T, ZLO> K;
-  K.init(a.g, a.glob, a.edges_par, a.edges_perp);
-  // x-space constants: x_par = |d_i - d_j| cp + mep, x_perp = d_i st + bt_j
-  const double dcx = sizeof(T) == 4 ? a.glob->dc : 0.0;  // FP32 distances are re-centred
-  const double invp = a.g.inv_par, invt = a.g.inv_perp, e0t = a.g.e0_perp;
-  const T mep = (T)(-a.g.e0_par * a.g.inv_par);
-
-  int cur_key = -1;
-  double pending = 0.0;  // upper bound on pairs added to any bin since the last flush
-  double scN = 1.0, scW = 1.0;  // DET: 2^s of the current realisation
+  int cur = -1;        // output slab of the LDS sums
+  bool have = false;   // an item is held
+  unsigned turns_taken = blockIdx.x;  // thread 0: the next run of tickets
+  unsigned ticket = (unsigned)uniform((int)threadIdx.x >> 6) * gridDim.x + blockIdx.x, ticket_end = 0;
+  int key = 0, nbc = 0, nf = 0, total = 0, log_step = 0, part0 = 0;
+  int64_t fpix0 = 0, fext = 0;
   __syncthreads();
 
   for (;;) {
-    if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(a.counter, 1u);
-    __syncthreads();
-    const int64_t it = s_item;
-    if (it >= a.n_items) break;
-    const Item item = a.items[it];
-    const int f = a.sorted[item.p];
-    const ForestInfo fi = a.finfo[f];
-    const int nbc = item.nb_count;
-
-    // neighbour table: geometry per forest pair, prefix of pixel counts
-    if (threadIdx.x < 64) {
-      int n = 0;
-      if (lane < nbc) {
-        const int g = a.sorted[a.nbr[item.nb_begin + lane]];
-        const ForestInfo gi = a.finfo[g];
-        double s, c;
-        pair_sc(fi, gi, s, c);
-        tb.pix0[lane] = gi.pix0;
-        tb.s64[lane] = s;
-        tb.c64[lane] = c;
-        n = gi.npix;
-      }
-      int incl = n;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += v;
-      }
-      if (lane < nbc) tb.pref[lane + 1] = incl;
-      if (lane == 0) tb.pref[0] = 0;
-    }
-    __syncthreads();
-    const int total = tb.pref[nbc];
-
-    // output slab: the realisation, or realisation * n_sub + subsample of f
-    const int okey = a.sub ? fi.real * a.n_sub + a.sub[f] : fi.real;
-    if (okey != cur_key || pending + (double)total * fi.npix > a.flush_pairs) {
-      if (cur_key >= 0) {
-        if constexpr (DET) flush_det<BLOCK>(a, hq, hn, cur_key); else flush_hist<BLOCK, MEANS>(a, hNW, hM, hn, cur_key);
-        __syncthreads();
-      }
-      cur_key = okey;
-      pending = 0.0;
-      if constexpr (DET) {
-        scN = ldexp(1.0, det_shift(a.det_max[2 * okey]));
-        scW = ldexp(1.0, det_shift(a.det_max[2 * okey + 1]));
-      }
-    }
-    pending += (double)total * fi.npix;
-
-    const Rec* __restrict__ rf = recs + fi.pix0;
-    const int nf = fi.npix;
-
-    for (int base = wave * 64; base < total; base += BLOCK) {
-      const int q = base + lane;
-      int k = 0;
-      {
-        int lo = 0, hi = nbc;
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (tb.pref[mid] <= q) lo = mid; else hi = mid;
+    if (!have) {
+      const KArgs a = kargs();
+      have = true;
+      // Tickets.  One slab: every n-th from the wave's number on (n waves), for its
+      // share, then `grab` at a time from kXiCounters counters, the workgroup's own
+      // first: one counter hands out a ticket in 12 ns at best, and to tell 8192
+      // waves that it has none left took 0.1 ms.  Several slabs: from the
+      // workgroup's run.
+      const unsigned waves = (BLOCK / 64) * gridDim.x;
+      unsigned t = ticket;
+      if (a->chunk > 0) {
+        if (lane == 0) {
+          t = atomicAdd(&s_lo, 1u);
+          t = t < s_hi ? t : ~0u;
         }
-        k = lo;
-      }
-      T dj, wdj, wj, zj = 0, cp, st, bt;
-      double Dj64 = 0.0, s64 = 0.0, c64 = 1.0;
-      if (q < total) {
-        const int64_t j = tb.pix0[k] + (q - tb.pref[k]);
-        const Rec rj = recs[j];
-        dj = rj.d;
-        wdj = rj.wd;
-        wj = rj.w;
-        zj = rj.del;  // the pixel redshift when the records carry z (MEANS)
-        s64 = tb.s64[k];
-        c64 = tb.c64[k];
-        if constexpr (sizeof(T) == 4) Dj64 = a.dist[j]; else Dj64 = rj.d;
-        cp = (T)(c64 * invp);
-        st = (T)(s64 * invt);
-        bt = (T)(((Dj64 + dcx) * s64 - e0t) * invt);
+        t = (unsigned)uniform((int)t);
+      } else if (ticket < (unsigned)a->share * waves) {
+        ticket += waves;
+        if (ticket >= (unsigned)a->share * waves) ticket = ticket_end = (unsigned)a->share * waves;
       } else {
-        // out-of-range lane: a far-away pixel, never in the grid
-        dj = (T)1e30;
-        wdj = 0;
-        wj = 0;
-        cp = 1;
-        st = 0;
-        bt = (T)1e30;
-      }
-
-      // bin of the pair (pixel i of f, this lane's pixel), or -1; xp, xt are
-      // its coordinates in bin units
-      auto bin_of = [&](const Rec& ri, int i, T& xp, T& xt) -> int {
-        const T ad = fabs(ri.d - dj);
-        if constexpr (ZLO) xp = ad * cp; else xp = fma(ad, cp, mep);
-        xt = fma(ri.d, st, bt);
-        return K.bin_x(xp, xt, [&](double& rp64, double& rt64) {
-          double Di64;
-          if constexpr (sizeof(T) == 4) Di64 = load_uniform(a.dist + fi.pix0 + i); else Di64 = ri.d;
-          separations64(Di64, Dj64, c64, s64, rp64, rt64);
-        });
-      };
-      constexpr int NB = Batch<Rec>::N;
-
-      if constexpr (RLE) {
-        // runs of equal bins along f, ended at every kRunMax-th pixel of f (a run
-        // sum holds at most kRunMax FP32 products); out-of-grid pairs form runs
-        // with A = -1 that are never added
-        for (int c0 = 0; c0 < nf; c0 += (int)kRunMax) {
-          const int c1 = min(nf, c0 + (int)kRunMax);
-          int curA = -1, ist = c0;
-          T accN = 0, accW = 0, accP = 0, accT = 0, accZ = 0;
-          auto add_run = [&](int A, int count) {
-            if constexpr (DET) {
-              det_add(&hq[4 * A], __dmul_rn((double)accN, scN));
-              det_add(&hq[4 * A + 2], __dmul_rn((double)accW, scW));
-              atomicAdd(&hn[A], (unsigned)count);
-              return;
-            }
-            atomicAdd(&hNW[2 * A], (double)accN);
-            atomicAdd(&hNW[2 * A + 1], (double)accW);
-            atomicAdd(&hn[A], (unsigned)count);
-            if constexpr (MEANS) {
-              atomicAdd(&hM[3 * A], (double)accP);
-              atomicAdd(&hM[3 * A + 1], (double)accT);
-              atomicAdd(&hM[3 * A + 2], (double)accZ);
-            }
-          };
-          auto pair = [&](const Rec& ri, int i) {
-            T xp, xt;
-            const int A = bin_of(ri, i, xp, xt);
-            if (A != curA) {
-              if (curA >= 0) add_run(curA, i - ist);
-              curA = A;
-              accN = 0;
-              accW = 0;
-              if constexpr (MEANS) {
-                accP = 0;
-                accT = 0;
-                accZ = 0;
+        if (ticket == ticket_end) {
+          t = ~0u;
+          if (lane == 0) {
+            for (int k = s_gone; k < kXiCounters;) {
+              const unsigned w = ((blockIdx.x >> 3) + k) % kXiCounters;
+              const int64_t b = (int64_t)atomicAdd(a->counter + w * kXiCounterStride, 1u) * kXiCounters + w;
+              const int64_t t0 = (int64_t)a->share * waves + b * a->grab;
+              if (t0 < a->n_items * a->n_parts) {
+                t = (unsigned)t0;
+                break;
               }
-              ist = i;
+              k = max(k + 1, atomicMax(&s_gone, k + 1));
             }
-            accN = fma(ri.wd, wdj, accN);
-            if constexpr (MEANS) {
-              const T ww = ri.w * wj;
-              accW += ww;
-              accP = fma(ww, xp, accP);
-              accT = fma(ww, xt, accT);
-              accZ = fma(ww, ri.del + zj, accZ);
-            } else {
-              accW = fma(ri.w, wj, accW);
-            }
-          };
-          int i = c0;
-          for (; i + NB <= c1; i += NB) {
-            Batch<Rec> b;
-            b.load(rf + i);
-#pragma unroll
-            for (int u = 0; u < NB; ++u) pair(b.r[u], i + u);
           }
-          for (; i < c1; ++i) pair(load_uniform(rf + i), i);
-          if (curA >= 0) add_run(curA, c1 - ist);
+          ticket = t = (unsigned)uniform((int)t);
+          ticket_end = ticket + (unsigned)a->grab;
         }
-      } else {
-        auto pair = [&](const Rec& ri, int i) {
-          T xp, xt;
-          const int A = bin_of(ri, i, xp, xt);
-          if (A >= 0) {
-            if constexpr (DET) {
-              det_add(&hq[4 * A], __dmul_rn((double)(ri.wd * wdj), scN));
-              det_add(&hq[4 * A + 2], __dmul_rn((double)(ri.w * wj), scW));
-            } else {
-              atomicAdd(&hNW[2 * A], (double)(ri.wd * wdj));
-              atomicAdd(&hNW[2 * A + 1], (double)(ri.w * wj));
-            }
-            atomicAdd(&hn[A], 1u);
-          }
-        };
-        int i = 0;
-        for (; i + NB <= nf; i += NB) {
-          Batch<Rec> b;
-          b.load(rf + i);
+        if (t != ~0u) ++ticket;
+      }
+      key = kWaitAll;
+      if ((int64_t)t < a->n_items * a->n_parts) {
+        part0 = t % (unsigned)a->n_parts * kRunMax;
+        t /= (unsigned)a->n_parts;
+        const Item item = a->items[a->order ? a->order[t] : (int)t];
+        const int f = a->sorted[item.p];
+        const ForestInfo fi = a->finfo[f];
+        key = uniform(a->sub ? fi.real * a->n_sub + a->sub[f] : fi.real);
+        nbc = uniform(item.nb_count);
+        nf = uniform(fi.npix);
+        fpix0 = ((int64_t)uniform((int)(fi.pix0 >> 32)) << 32) | (uint32_t)uniform((int)fi.pix0);
+        // the neighbours in order of distance: a wave's lanes then leave the grid
+        // together, and the iterations without a pair in it are skipped
+        int n = 0;
+        float dmin = 0.f;
+        double s = 0.0, c = 1.0;
+        int64_t pix = 0;
+        if (lane < nbc) {
+          const ForestInfo gi = a->finfo[a->sorted[a->nbr[item.nb_begin + lane]]];
+          pair_sc(fi, gi, s, c);
+          pix = gi.pix0;
+          n = gi.npix;
+          dmin = (float)gi.dmin;
+        }
+        int rank = 0;
+        for (int t2 = 0; t2 < nbc; ++t2) {
+          const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dmin), t2));
+          rank += (o < dmin || (o == dmin && t2 < lane)) ? 1 : 0;
+        }
+        if (lane < nbc) {
+          tab.s[rank] = s;
+          tab.c[rank] = c;
+          tab.pix[rank] = pix;
+          tab.pos[rank] = n;
+        }
+        __builtin_amdgcn_wave_barrier();
+        n = lane < nbc ? tab.pos[lane] : 0;
+        int incl = n;
 #pragma unroll
-          for (int u = 0; u < NB; ++u) pair(b.r[u], i + u);
+        for (int o = 1; o < kChunkMax; o <<= 1) {
+          const int v = __shfl_up(incl, o, 64);
+          if (lane >= o) incl += v;
         }
-        for (; i < nf; ++i) pair(load_uniform(rf + i), i);
+        if (lane < nbc) tab.pos[lane] = incl - n;
+        total = __builtin_amdgcn_readlane(incl, kChunkMax - 1);
+        fext = (fpix0 >> 5) + uniform(f);
+        // pixels of f per r_par bin, as the power of two below 1.4 times it
+        const float per = 1.4f * (float)(nf - 1) / fmaxf((float)((fi.dmax - fi.dmin) * a->g.inv_par), 1e-6f);
+        log_step = uniform(per < 2.f ? 0 : (per < 4.f ? 1 : (per < 8.f ? 2 : (per < 16.f ? 3 : 4))));
       }
     }
-    __syncthreads();
-  }
-  __syncthreads();
-  if (cur_key >= 0) {
-    if constexpr (DET) flush_det<BLOCK>(a, hq, hn, cur_key); else flush_hist<BLOCK, MEANS>(a, hNW, hM, hn, cur_key);
+    bool go = key == cur;
+    if (go) {
+      // reserve the item's pairs: no bin's count passes 2^32 between flushes
+      const unsigned long long pairs = (unsigned long long)total * (unsigned long long)nf;
+      int over = 0;
+      if (lane == 0) {
+        const unsigned long long old = atomicAdd(&s_pairs, pairs);
+        if (old != 0ull && (double)(old + pairs) > kargs()->flush_pairs) {
+          atomicAdd(&s_pairs, 0ull - pairs);
+          over = 1;
+        }
+      }
+      go = uniform(over) == 0;
+    }
+    if (!go) {
+      // every wave of the workgroup comes here before any goes on; the items
+      // are ordered by slab, so each of them finds an end of the work in `cur`
+      if (lane == 0) atomicMin(&s_next, key);
+      __syncthreads();
+      const int next = uniform(s_next);
+      const bool refill = next == kWaitAll && kargs()->chunk > 0;
+      if (cur >= 0 && !refill) flush_hist<BLOCK, MEANS, DET>(smem, cur);
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        s_next = kWaitAll;
+        if (refill) {
+          const KArgs a = kargs();
+          const unsigned n = (unsigned)(a->n_items * a->n_parts), c = (unsigned)a->chunk;
+          const uint64_t lo = (uint64_t)turns_taken * c;
+          s_lo = lo < n ? (unsigned)lo : n;
+          s_hi = lo + c < n ? (unsigned)(lo + c) : n;
+          s_done = lo >= n;  // not read off s_lo below: a faster wave may have taken every ticket by then
+          turns_taken = gridDim.x + atomicAdd(a->counter, 1u);
+        } else {
+          s_pairs = 0ull;
+        }
+      }
+      __syncthreads();
+      if (refill) {
+        if (uniform(s_done) == 0) {
+          have = false;
+          continue;
+        }
+        if (cur >= 0) flush_hist<BLOCK, MEANS, DET>(smem, cur);
+        break;
+      }
+      cur = next;
+      if (cur == kWaitAll) break;
+      if constexpr (DET) {
+        const KArgs a = kargs();
+        shN = uniform(det_shift(a->det_max[2 * cur]));
+        shW = uniform(det_shift(a->det_max[2 * cur + 1]));
+      }
+      continue;
+    }
+    have = false;
+
+    const Rec* rf;
+    if constexpr (sizeof(T) == 4) rf = kargs()->xrec32 + fpix0; else rf = kargs()->rec64 + fpix0;
+    // Stream pixel of the lane.  Each 16 lanes (an LDS atomic takes 16 at a time)
+    // take every step-th pixel, about one r_par bin apart, so that they rarely
+    // meet on an address or a bank: 16 lanes on 8 addresses cost it 5 clocks
+    // instead of 2.  The wave covers 64 neighbouring pixels (16 step of them in
+    // step / 4 turns where step > 4).
+    const int turns = log_step > 2 ? 1 << (log_step - 2) : 1;
+    int lane_pix;
+    {
+      const int g = lane >> 4, t = lane & 15, ls = min(log_step, 2), step = 1 << log_step;
+      lane_pix = ((g >> ls) << (4 + ls)) + t * step + (g & ((1 << ls) - 1));
+    }
+    for (int block = 0, turn = 0; block < total;) {
+      const int q = block + 4 * turn + lane_pix;
+      if (++turn == turns) {
+        turn = 0;
+        block += 64 * turns;
+      }
+      const bool valid = q < total;
+      // the neighbour of stream pixel q: the last that starts at or before it
+      int k = 0;
+#pragma unroll
+      for (int step = kChunkMax / 2; step > 0; step >>= 1)
+        if (k + step < nbc && tab.pos[k + step] <= q) k += step;
+      double Dj = 0.0, cp = 0.0, st = 0.0, bt = 1.5 * kMagic;  // past the stream's end: outside the grid
+      T wdj = 0, wj = 0, dj = 0, zj = 0, mcp = 0, mst = 0, mbt = 0, mep = 0;
+      {
+        const KArgs a = kargs();
+        const double s64 = tab.s[k], invt = a->g.inv_perp;
+        if (valid) {
+          const int64_t j = tab.pix[k] + (q - tab.pos[k]);
+          const Rec* recs;
+          if constexpr (sizeof(T) == 4) recs = a->xrec32; else recs = a->rec64;
+          const Rec r = recs[j];
+          Dj = r.d;
+          wdj = r.wd;
+          wj = r.w;
+          cp = tab.c[k] * a->g.inv_par;
+          st = s64 * invt;
+          bt = (Dj * s64 - a->g.e0_perp) * invt + (kMagic + kGuard);
+          if constexpr (MEANS) {
+            if constexpr (sizeof(T) == 4) {
+              dj = a->xaux32[j].d;
+              zj = a->xaux32[j].z;
+            } else {
+              dj = Dj;
+              zj = r.del;
+            }
+          }
+        }
+        if constexpr (MEANS) {
+          // coordinates in the form's arithmetic, x_par = |d_i - d_j| mcp + mep,
+          // x_perp = d_i mst + mbt (FP32 distances are re-centred on dc)
+          const double dcx = sizeof(T) == 4 ? a->glob->dc : 0.0;
+          mcp = (T)cp;
+          mst = (T)st;
+          mbt = (T)(((Dj + dcx) * s64 - a->g.e0_perp) * invt);
+          mep = (T)(-a->g.e0_par * a->g.inv_par);
+        }
+      }
+
+      T aN = 0, aW = 0, pN = 0, pW = 0;           // sums of the lane's run, and of its waiting run
+      T aP = 0, aT = 0, aZ = 0, pP = 0, pT = 0, pZ = 0;
+      uint32_t rkey = Lout, pkey = 0;              // bin - (first pixel << 16); bin + (pixels << 16)
+      uint64_t pend = 0ull;                        // lanes with a waiting run
+      uint64_t last = 0ull;                        // lanes that were inside the grid
+      // chunks of kRunMax pixels of f; the item's parts take them in turn, and
+      // runs count pixels in the order taken (lag behind the pixel's own index)
+      int lag = part0, taken = 0;
+
+      auto flush = [&]() __attribute__((always_inline)) {
+        if (lane_in(pend)) {
+          const uint32_t v = pkey - G, L = v & 0x7fffu;
+          if constexpr (DET) {
+            det_add((unsigned long long*)hN + L, hc + L, ldexp((double)pN, shN));
+            det_add((unsigned long long*)hN + nd + L, hc + nd + L, ldexp((double)pW, shW));
+          } else {
+            atomicAdd(&hN[L], (double)pN);
+            atomicAdd(&hN[nd + L], (double)pW);
+            if constexpr (MEANS) {
+              atomicAdd(&hN[2 * nd + L], (double)pP);
+              atomicAdd(&hN[3 * nd + L], (double)pT);
+              atomicAdd(&hN[4 * nd + L], (double)pZ);
+            }
+          }
+          atomicAdd(&hn[L], v >> 16);
+        }
+        pend = 0ull;
+      };
+      // lanes m end their run before pixel i and start one in bin L
+      auto change = [&](uint64_t m, uint32_t L, uint32_t i16) __attribute__((always_inline)) {
+        if (m & pend) flush();
+        pend |= m;
+        change_run(m, L, i16, pkey, rkey, pN, pW, aN, aW);
+        if constexpr (MEANS) {
+          change_sum(m, pP, aP);
+          change_sum(m, pT, aT);
+          change_sum(m, pZ, aZ);
+        }
+      };
+      // N pixels of f, from pixel i on
+      auto pairs = [&](auto n_c, const UPix<T>* r, int i) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_c)::value;
+        uint64_t in[N], some = last;
+        uint32_t L[N], low = 0xffffffffu;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+          const double up = fma(fabs(r[u].d - Dj), cp, mp), ut = fma(r[u].d, st, bt);
+          in[u] = ballot(up < uphi) & ballot(ut < uthi);
+          if constexpr (!ZLO) in[u] &= ballot(up >= kMagic) & ballot(ut >= kMagic);
+          some |= in[u];
+          const uint32_t B = __umul24((uint32_t)__double2hiint(ut), (unsigned)NP) + (uint32_t)__double2hiint(up);
+          L[u] = lane_in(in[u]) ? B : Lout;
+          low = min(low, min((uint32_t)__double2loint(up), (uint32_t)__double2loint(ut)));
+        }
+        if (some == 0ull) return;
+        if constexpr (RUNS) last = in[N - 1];
+        if (ballot(low <= thr)) {
+          // some pair of some lane may be within the guard of an edge: its
+          // coordinates once more (kept, they would take the registers of two waves)
+          const KArgs a = kargs();
+          double Dj2 = Dj;
+          asm volatile("" : "+v"(Dj2));
+          int kt_last = -1;  // non-uniform edges: the bin of the pixel before is the better guess
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            double st2 = st;
+            asm volatile("" : "+v"(st2));
+            const double up = fma(fabs(r[u].d - Dj2), cp, mp), ut = fma(r[u].d, st2, bt);
+            const uint32_t hp = (uint32_t)__double2hiint(up), ht = (uint32_t)__double2hiint(ut);
+            // r_par = 0 (aligned pixel grids) needs no guard at a zero lower edge
+            uint64_t m = ballot((uint32_t)__double2loint(up) <= thr);
+            if (a->g.zero_lo_par && !a->g.exact_all) m &= ballot(hp != kMagicHi);
+            m = in[u] & (m | ballot((uint32_t)__double2loint(ut) <= thr));
+            if (m) {
+              if (lane_in(m)) {
+                double rp64, rt64;
+                separations64(r[u].d, Dj2, tab.c[k], tab.s[k], rp64, rt64);
+                const int kp = bin_exact(rp64, a->edges_par, NP, (int)(hp - kMagicHi));
+                const int kt = bin_exact(rt64, a->edges_perp, a->g.n_perp,
+                                         a->g.exact_all && kt_last >= 0 ? kt_last : (int)(ht - kMagicHi));
+                kt_last = kt;
+                L[u] = (kp >= 0 && kt >= 0) ? G + (uint32_t)(kt * NP + kp) : Lout;
+              }
+            }
+          }
+        }
+        if constexpr (!RUNS) {
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            if (lane_in(in[u])) {
+              const uint32_t B = L[u] & 0x7fffu;
+              atomicAdd(&hN[B], (double)(r[u].wd * wdj));
+              atomicAdd(&hN[nd + B], (double)(r[u].w * wj));
+              atomicAdd(&hn[B], 1u);
+            }
+          }
+          return;
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+          change(other_bin(L[u], rkey), L[u], (uint32_t)(i - lag + u) << 16);
+          aN = fma(r[u].wd, wdj, aN);
+          if constexpr (MEANS) {
+            T di, zi;
+            if constexpr (sizeof(T) == 4) {
+              const lya_i2 x = LYA_CONST(lya_i2, kargs()->xaux32 + fpix0 + i + u);
+              di = __int_as_float(x[0]);
+              zi = __int_as_float(x[1]);
+            } else {
+              di = r[u].d;
+              zi = LYA_CONST(double, &rf[i + u].del);
+            }
+            const T ad = fabs(di - dj);
+            T xp;
+            if constexpr (ZLO) xp = ad * mcp; else xp = fma(ad, mcp, mep);
+            const T xt = fma(di, mst, mbt);
+            const T ww = r[u].w * wj;
+            aW += ww;
+            aP = fma(ww, xp, aP);
+            aT = fma(ww, xt, aT);
+            aZ = fma(ww, zi + zj, aZ);
+          } else {
+            aW = fma(r[u].w, wj, aW);
+          }
+        }
+      };
+      constexpr int NB = Batch<T>::N;
+      for (int c0 = part0; c0 < nf;) {
+        const int c1 = min(nf, c0 + (int)kRunMax);
+        rkey ^= 0x8000u;  // no bin: every lane starts a run
+        last = RUNS ? ~0ull : 0ull;
+        int i = c0;
+        {
+          // no pixel of this chunk within reach of any lane?  (the same rounded
+          // operations from the chunk's extent, so never wrong)
+          const lya_i4 e = LYA_CONST(lya_i4, kargs()->ext + fext + (c0 >> 5));
+          const double lo = __hiloint2double(e[1], e[0]), hi = __hiloint2double(e[3], e[2]);
+          const double gap = fmax(lo - Dj, Dj - hi);
+          const uint64_t near = ballot(fma(gap, cp, mp) < uphi) & ballot(fma(lo, st, bt) < uthi);
+          if (near == 0ull) {
+            if constexpr (RUNS) change(~0ull, Lout, (uint32_t)(c0 - lag) << 16);
+            i = c1;
+          }
+        }
+#pragma unroll 1
+        for (; i + NB <= c1; i += NB) {
+          Batch<T> b;
+          b.load(rf + i);
+          pairs(std::integral_constant<int, NB>{}, b.r, i);
+        }
+#pragma unroll 1
+        for (; i < c1; ++i) {
+          const UPix<T> r = load_pix(rf + i);
+          pairs(std::integral_constant<int, 1>{}, &r, i);
+        }
+        taken = c1 - lag;
+        const int skip = (int)kRunMax * (kargs()->n_parts - 1);
+        lag += skip;
+        c0 += (int)kRunMax + skip;
+      }
+      if constexpr (RUNS) {
+        // the last runs, but not those outside the grid
+        change(ballot((rkey & 0x7fffu) < (uint32_t)nb), Lout, (uint32_t)taken << 16);
+        if (pend) flush();
+      }
+    }
   }
 }
 
+// Two forms, each with two workgroup sizes.  The larger size is the default:
+// most waves per CU, fewest copies of the histograms.  Runs where an r_par bin
+// holds at least 1.2 pixels of a forest; below, where a run would rarely hold two
+// pixels, every pair's products are added by themselves (xi_default_variant).
 struct Variant {
   const char* name;
   int block;
-  bool rle;
+  bool runs;
 };
 constexpr Variant kVariants[] = {
-    {"b256", 256, false},
-    {"b512", 512, false},
-    {"b256-rle", 256, true},
-    {"b512-rle", 512, true},
-};
+    {"b512", 512, false}, {"b1024", 1024, false}, {"b512-runs", 512, true}, {"b1024-runs", 1024, true}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-template <bool MEANS, bool DET = false>
-constexpr size_t smem_per_bin() {
-  return (DET ? 4 : (MEANS ? 5 : 2)) * sizeof(double) + sizeof(unsigned);
-}
-
-template <typename T, int BLOCK, bool RLE, bool ZLO, bool MEANS = false, bool DET = false>
+template <typename T, int BLOCK, bool ZLO, bool RUNS, bool MEANS = false, bool DET = false>
 hipError_t launch_one(const XiArgs& a, int blocks, hipStream_t st) {
-  const size_t smem = (size_t)a.g.n_par * a.g.n_perp * smem_per_bin<MEANS, DET>();
-  auto kern = xi_kernel<T, BLOCK, RLE, ZLO, MEANS, DET>;
+  const size_t smem = ((size_t)a.g.n_par * a.g.n_perp + 64) * smem_per_bin<MEANS, DET>();
+  auto kern = xi_kernel<T, BLOCK, ZLO, RUNS, MEANS, DET>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(BLOCK), smem, st, a);
@@ -456,10 +748,10 @@ hipError_t launch_one(const XiArgs& a, int blocks, hipStream_t st) {
 template <typename T, bool ZLO>
 hipError_t launch_z(int v, const XiArgs& a, int blocks, hipStream_t st) {
   switch (v) {
-    case 0: return launch_one<T, 256, false, ZLO>(a, blocks, st);
-    case 1: return launch_one<T, 512, false, ZLO>(a, blocks, st);
-    case 2: return launch_one<T, 256, true, ZLO>(a, blocks, st);
-    case 3: return launch_one<T, 512, true, ZLO>(a, blocks, st);
+    case 0: return launch_one<T, 512, ZLO, false>(a, blocks, st);
+    case 1: return launch_one<T, 1024, ZLO, false>(a, blocks, st);
+    case 2: return launch_one<T, 512, ZLO, true>(a, blocks, st);
+    case 3: return launch_one<T, 1024, ZLO, true>(a, blocks, st);
   }
   return hipErrorInvalidValue;
 }
@@ -470,10 +762,10 @@ hipError_t launch_t(int v, const XiArgs& a, int blocks, hipStream_t st) {
   return zlo ? launch_z<T, true>(v, a, blocks, st) : launch_z<T, false>(v, a, blocks, st);
 }
 
-template <typename T, int BLOCK, bool RLE, bool MEANS = false, bool DET = false>
+template <typename T, int BLOCK, bool RUNS, bool MEANS = false, bool DET = false>
 int occupancy(int n_bins) {
-  const size_t smem = (size_t)n_bins * smem_per_bin<MEANS, DET>();
-  auto kern = xi_kernel<T, BLOCK, RLE, true, MEANS, DET>;
+  const size_t smem = ((size_t)n_bins + 64) * smem_per_bin<MEANS, DET>();
+  auto kern = xi_kernel<T, BLOCK, true, RUNS, MEANS, DET>;
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return 1;
   int nblk = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nblk, kern, BLOCK, smem) != hipSuccess) return 1;
@@ -483,10 +775,10 @@ int occupancy(int n_bins) {
 template <typename T>
 int occ_t(int v, int n_bins) {
   switch (v) {
-    case 0: return occupancy<T, 256, false>(n_bins);
-    case 1: return occupancy<T, 512, false>(n_bins);
-    case 2: return occupancy<T, 256, true>(n_bins);
-    case 3: return occupancy<T, 512, true>(n_bins);
+    case 0: return occupancy<T, 512, false>(n_bins);
+    case 1: return occupancy<T, 1024, false>(n_bins);
+    case 2: return occupancy<T, 512, true>(n_bins);
+    case 3: return occupancy<T, 1024, true>(n_bins);
   }
   return 1;
 }
@@ -542,8 +834,13 @@ __global__ void finalize_det_kernel(const unsigned long long* acc, const unsigne
   if (i >= n) return;
   const int64_t r = i / n_bins;
   const int sN = det_shift(det_max[2 * r]), sW = det_shift(det_max[2 * r + 1]);
-  const double vn = __dadd_rn(ldexp((double)(long long)acc[4 * i + 1], kDetShift), (double)acc[4 * i]);
-  const double vw = __dadd_rn(ldexp((double)(long long)acc[4 * i + 3], kDetShift), (double)acc[4 * i + 2]);
+  // the low word carried into the high one: both then depend on the total only
+  auto value = [](unsigned long long lo, unsigned long long hi) {
+    hi += lo >> kDetShift;
+    return __dadd_rn(ldexp((double)(long long)hi, kDetShift), (double)(lo & ((1ull << kDetShift) - 1)));
+  };
+  const double vn = value(acc[4 * i], acc[4 * i + 1]);
+  const double vw = value(acc[4 * i + 2], acc[4 * i + 3]);
   num[i] = ldexp(vn, -sN);
   wsum[i] = ldexp(vw, -sW);
   if (npairs[i] >= (1ull << 36)) atomicOr(&glob->flag, kBadDet);
@@ -559,6 +856,8 @@ __global__ void finalize_xi_kernel(const double* num, const double* wsum, double
 }  // namespace
 
 int xi_num_variants() { return kNumVariants; }
+int xi_default_variant(double bin_par, double spacing) { return bin_par < 1.2 * spacing ? 1 : 3; }
+int xi_variant_block(int v) { return kVariants[v].block; }
 const char* xi_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVariants[v].name : "?"; }
 
 hipError_t launch_xi(int variant, int precision, const XiArgs& a, int blocks, hipStream_t st) {
@@ -571,8 +870,7 @@ int xi_blocks_per_cu(int variant, int precision, int n_bins) {
   return precision == LYA_FP64 ? occ_t<double>(variant, n_bins) : occ_t<float>(variant, n_bins);
 }
 
-// The deterministic form: the run-length form with 1024 threads (its 36 B
-// of LDS per bin leave one workgroup per CU at 2500 bins).
+// The deterministic form: 28 B of LDS per bin, two workgroups per CU at 2500 bins.
 constexpr int kDetBlock = 1024;
 
 hipError_t launch_xi_det(int precision, const XiArgs& a, int blocks, hipStream_t st) {
@@ -580,9 +878,9 @@ hipError_t launch_xi_det(int precision, const XiArgs& a, int blocks, hipStream_t
   const bool zlo = a.g.zero_lo_par && a.g.zero_lo_perp;
   if (precision == LYA_FP64)
     return zlo ? launch_one<double, kDetBlock, true, true, false, true>(a, blocks, st)
-               : launch_one<double, kDetBlock, true, false, false, true>(a, blocks, st);
+               : launch_one<double, kDetBlock, false, true, false, true>(a, blocks, st);
   return zlo ? launch_one<float, kDetBlock, true, true, false, true>(a, blocks, st)
-             : launch_one<float, kDetBlock, true, false, false, true>(a, blocks, st);
+             : launch_one<float, kDetBlock, false, true, false, true>(a, blocks, st);
 }
 
 int xi_det_blocks_per_cu(int precision, int n_bins) {
@@ -607,10 +905,8 @@ hipError_t launch_finalize_det(const unsigned long long* det_acc, const unsigned
   return hipGetLastError();
 }
 
-// The bin-means form: one run-length variant, kMeansBlock threads (its
-// histograms need 110 KB of LDS at 2500 bins, so one workgroup per CU; 16
-// waves hide latency better than 8: 246 against 340 ms on the eBOSS-like
-// workload).
+// The bin-means form: 44 B of LDS per bin, one workgroup of 16 waves per CU at
+// 2500 bins.
 constexpr int kMeansBlock = 1024;
 
 hipError_t launch_xi_means(int precision, const XiArgs& a, int blocks, hipStream_t st) {
@@ -618,9 +914,9 @@ hipError_t launch_xi_means(int precision, const XiArgs& a, int blocks, hipStream
   const bool zlo = a.g.zero_lo_par && a.g.zero_lo_perp;
   if (precision == LYA_FP64)
     return zlo ? launch_one<double, kMeansBlock, true, true, true>(a, blocks, st)
-               : launch_one<double, kMeansBlock, true, false, true>(a, blocks, st);
+               : launch_one<double, kMeansBlock, false, true, true>(a, blocks, st);
   return zlo ? launch_one<float, kMeansBlock, true, true, true>(a, blocks, st)
-             : launch_one<float, kMeansBlock, true, false, true>(a, blocks, st);
+             : launch_one<float, kMeansBlock, false, true, true>(a, blocks, st);
 }
 
 int xi_means_blocks_per_cu(int precision, int n_bins) {

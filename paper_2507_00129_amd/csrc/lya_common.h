@@ -12,7 +12,8 @@ namespace lya {
 constexpr int kMaxBins = 4096;     // n_par * n_perp limit (LDS histograms)
 constexpr int kMaxStrips = 4096;   // declination strips of the sky index
 constexpr int kMaxRealisations = 1 << 20;
-constexpr int kChunkMax = 64;      // neighbour forests per xi / backward work item
+constexpr int kXiCounters = 16, kXiCounterStride = 32;  // counters of an xi launch, a cache line each
+constexpr int kChunkMax = 16;      // neighbour forests per xi work item
 
 // Per-forest geometry and layout, FP64 (64 bytes).
 struct ForestInfo {
@@ -42,11 +43,16 @@ struct Globals {
   float tau_perp;
   int32_t flag;     // validation error bits
   int32_t pad;
+  double span;      // sum of the forests' extents along the line of sight
 };
 
 // Pixel records for the xi and backward kernels.
 struct __align__(16) Rec32 { float d, wd, w, del; };   // d = D - dc
 struct __align__(32) Rec64 { double d, wd, w, del; };  // d = D
+// The xi kernel's FP32 form: FP64 distance, FP32 products; and, for the bin
+// means, d = D - dc and the pixel redshift.
+struct __align__(16) XRec32 { double d; float wd, w; };
+struct __align__(8) XAux32 { float d, z; };
 
 // Pixel records for the distortion kernel: D, w and the eta factors
 // p = (1, a), q = (u, b) with a = L - lbar, u = w / W, b = w a / S.
@@ -181,6 +187,9 @@ struct PrecomputeArgs {
   double* delta_proj;   // [n_pix] when project
   Rec32* rec32;
   Rec64* rec64;
+  XRec32* xrec32;       // optional
+  XAux32* xaux32;       // optional
+  double2* ext;         // optional: XiArgs::ext
   DRec32* drec32;
   DRec64* drec64;
   Globals* glob;
@@ -194,7 +203,7 @@ hipError_t launch_validate_sub(const int32_t* sub, int64_t n_forests, int32_t n_
 hipError_t launch_covariance(const double* num, const double* wsum, int64_t n_sub, int64_t nb, double* x,
                              double* tot_w, double* xi, double* cov, hipStream_t st);
 hipError_t launch_forest_stats(const PrecomputeArgs& a, hipStream_t st);
-hipError_t launch_globals(const PrecomputeArgs& a, hipStream_t st);
+hipError_t launch_globals(const PrecomputeArgs& a, hipStream_t st);  // reduces the extents first
 hipError_t launch_pack(const PrecomputeArgs& a, hipStream_t st);
 
 struct WorklistArgs {
@@ -238,6 +247,9 @@ hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t n, void* tmp, si
 hipError_t launch_fill_neighbours(const WorklistArgs& a, hipStream_t st);
 hipError_t launch_count_items(const WorklistArgs& a, hipStream_t st);
 hipError_t launch_fill_items(const WorklistArgs& a, hipStream_t st);
+// sort keys (output slab realisation * n_sub + sub) and indices of the items
+hipError_t launch_item_slabs(const WorklistArgs& a, int64_t n_items, const int32_t* sub, int32_t n_sub, uint64_t* keys,
+                             int32_t* idx, hipStream_t st);
 
 struct XiArgs {
   const ForestInfo* finfo;
@@ -245,10 +257,15 @@ struct XiArgs {
   const int32_t* nbr;
   const Item* items;
   int64_t n_items;
+  int32_t n_parts;         // every item in n_parts tickets: its f pixels in runs of 32 dealt out in turn
+  int32_t share, grab;     // one output slab: tickets a wave starts with, and then takes at a time
+  int32_t chunk;           // several output slabs: tickets a workgroup takes at a time (0 with one)
   unsigned int* counter;
-  const Rec32* rec32;
+  const int32_t* order;    // optional: the order the items are taken in (by output slab)
+  const XRec32* xrec32;
+  const XAux32* xaux32;
   const Rec64* rec64;
-  const double* dist;
+  const double2* ext;      // distance extent of pixels 32 c .. of forest f at (pix0 >> 5) + f + c
   const double* edges_par;
   const double* edges_perp;
   const Globals* glob;
@@ -277,6 +294,9 @@ struct XiArgs {
 constexpr double kXiFlushPairs = 4.0e9;
 int xi_num_variants();
 const char* xi_variant_name(int v);
+int xi_variant_block(int v);  // threads per workgroup
+// variant for r_par bins of width bin_par and pixels `spacing` apart
+int xi_default_variant(double bin_par, double spacing);
 hipError_t launch_xi(int variant, int precision, const XiArgs& a, int blocks, hipStream_t st);
 // deterministic form (fixed-point integer sums, one variant)
 hipError_t launch_xi_det(int precision, const XiArgs& a, int blocks, hipStream_t st);
@@ -336,7 +356,7 @@ __device__ __forceinline__ int dmat_key_kt0(uint64_t k) { return (int)(k & 0xFFF
 // (one thread; writes the count of wider pairs to *out)
 hipError_t launch_dmat_span_split(const uint64_t* keys, int64_t n, int max_span, int64_t* out, hipStream_t st);
 hipError_t launch_sort_keys(uint64_t* keys_in, uint64_t* keys_out, int32_t* v_in, int32_t* v_out,
-                            int64_t n, void* tmp, size_t bytes, hipStream_t st);
+                            int64_t n, void* tmp, size_t bytes, hipStream_t st, unsigned bits = 64);
 size_t sort_keys_bytes(int64_t n);
 // microbenchmarks of the LDS atomic / store and VALU FMA rates (k_peaks.hip)
 hipError_t launch_lds_rate(int kind, int blocks, int iters, unsigned long long* sink, hipStream_t st);

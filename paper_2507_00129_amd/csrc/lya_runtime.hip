@@ -225,6 +225,7 @@ __global__ void init_globals_kernel(Globals* g) {
   g->tau_perp = 0.f;
   g->flag = 0;
   g->pad = 0;
+  g->span = 0.0;
 }
 
 struct Prepared {
@@ -232,6 +233,9 @@ struct Prepared {
   ForestInfo* finfo = nullptr;
   Rec32* rec32 = nullptr;
   Rec64* rec64 = nullptr;
+  XRec32* xrec32 = nullptr;
+  XAux32* xaux32 = nullptr;
+  double2* ext = nullptr;
   DRec32* drec32 = nullptr;
   DRec64* drec64 = nullptr;
   double* edges_par = nullptr;
@@ -244,7 +248,7 @@ struct Prepared {
 // Validation, per-forest sums and record packing.
 lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, const GridDev& gd,
                    const lya_options* o, hipStream_t st, bool xi_rec, bool d_rec, bool project,
-                   Prepared& P, bool pack_z = false) {
+                   Prepared& P, bool pack_z = false, bool bwd_rec = false) {
   const int64_t N = F->n_forests, npix = F->n_pix;
   LYA_TRY(wst(ctx, "globals", 1, &P.glob));
   LYA_TRY(wst(ctx, "finfo", (size_t)N, &P.finfo));
@@ -290,7 +294,10 @@ lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
   a.inv_par = gd.inv_par;
   a.inv_perp = gd.inv_perp;
   if (project) LYA_TRY(wst(ctx, "delta_proj", (size_t)npix, &a.delta_proj));
-  if (a.want_xi32) LYA_TRY(wst(ctx, "rec32", (size_t)npix, &a.rec32));
+  if (a.want_xi32 && bwd_rec) LYA_TRY(wst(ctx, "rec32", (size_t)npix, &a.rec32));
+  if (a.want_xi32 && !bwd_rec) LYA_TRY(wst(ctx, "xrec32", (size_t)npix, &a.xrec32));
+  if (xi_rec && !bwd_rec) LYA_TRY(wst(ctx, "xi_ext", (size_t)(npix / 32 + N + 1), &a.ext));
+  if (a.want_xi32 && pack_z) LYA_TRY(wst(ctx, "xaux32", (size_t)npix, &a.xaux32));
   if (a.want_xi64) LYA_TRY(wst(ctx, "rec64", (size_t)npix, &a.rec64));
   if (a.want_d32) LYA_TRY(wst(ctx, "drec32", (size_t)npix, &a.drec32));
   if (a.want_d64) LYA_TRY(wst(ctx, "drec64", (size_t)npix, &a.drec64));
@@ -304,6 +311,9 @@ lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
   P.delta_proj = a.delta_proj;
   P.rec32 = a.rec32;
   P.rec64 = a.rec64;
+  P.xrec32 = a.xrec32;
+  P.xaux32 = a.xaux32;
+  P.ext = a.ext;
   P.drec32 = a.drec32;
   P.drec64 = a.drec64;
   return LYA_OK;
@@ -316,6 +326,7 @@ struct Worklist {
   int64_t* cnt = nullptr;     // neighbours of each sorted position, and their scan
   int64_t* nb_off = nullptr;
   Item* items = nullptr;
+  int32_t* order = nullptr;   // items by output slab (with a subsample split)
   int64_t n_pairs = 0;
   int64_t n_items = 0;
   int64_t candidates = 0;
@@ -328,11 +339,20 @@ lya_status read_i64(lya_context* ctx, const int64_t* dev, int64_t* host, int cou
   return LYA_OK;
 }
 
+int xi_chunk(const lya_forests* F, int target_stream) {
+  const double mean = F->n_forests ? (double)F->n_pix / (double)F->n_forests : 1.0;
+  int c = (int)llround(target_stream / (mean > 1.0 ? mean : 1.0));
+  if (c < 1) c = 1;
+  if (c > kChunkMax) c = kChunkMax;
+  return c;
+}
+
 // Sky index, neighbour lists and work items (Sec. 2.1 pre-ordering).
 lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev& gd,
                           const Prepared& P, hipStream_t st, bool symmetric, bool use_keep,
                           uint64_t keep_thr, uint64_t seed, bool want_pairs, int chunk,
-                          const char* tag, Worklist& W, bool own_by_index = false) {
+                          const char* tag, Worklist& W, bool own_by_index = false, int64_t min_items = 0,
+                          const int32_t* sub = nullptr, int32_t n_sub = 1) {
   const int64_t N = F->n_forests;
   const int R = F->n_realisations;
   const double dmin = __builtin_bit_cast(double, P.host.dmin_bits);
@@ -399,6 +419,16 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
   W.nb_off = a.nb_off;
   W.n_pairs = total;
   if (chunk > 0) {
+    if (min_items > 0) {
+      // shorter items where there would be fewer than min_items, down to ~512
+      // partner pixels (eight waves' worth: a wave's last 64 are rarely full),
+      // and below that only where not every wave would get one
+      const int64_t waves = 32 * (int64_t)ctx->n_cu, floor = xi_chunk(F, 512), each = total / waves;
+      int64_t c = total / min_items;
+      if (c < (each < floor ? each : floor)) c = each < floor ? each : floor;
+      if (c < 1) c = 1;
+      if (c < a.chunk) a.chunk = (int)c;
+    }
     HIP_TRY(launch_count_items(a, st));
     HIP_TRY(launch_scan(a.item_cnt, a.item_off, N, a.cub_tmp, a.cub_bytes, st));
     HIP_TRY(hipMemcpyAsync((char*)ctx->pinned, a.item_cnt + (N - 1), 8, hipMemcpyDeviceToHost, st));
@@ -409,16 +439,51 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
     LYA_TRY(wst(ctx, (t + "_items").c_str(), (size_t)W.n_items, &a.items));
     HIP_TRY(launch_fill_items(a, st));
     W.items = a.items;
+    if (sub && W.n_items > 0) {
+      // items in order of their output slab
+      if (W.n_items > INT32_MAX) return fail(ctx, LYA_E_UNSUPPORTED, "too many work items");
+      uint64_t *k_in, *k_out;
+      int32_t* idx;
+      LYA_TRY(wst(ctx, "wl_slab_keys_in", (size_t)W.n_items, &k_in));
+      LYA_TRY(wst(ctx, "wl_slab_keys", (size_t)W.n_items, &k_out));
+      LYA_TRY(wst(ctx, "wl_slab_idx", (size_t)W.n_items, &idx));
+      LYA_TRY(wst(ctx, "wl_order", (size_t)W.n_items, &W.order));
+      const size_t bytes = sort_keys_bytes(W.n_items);
+      void* tmp;
+      LYA_TRY(ws(ctx, "wl_slab_tmp", bytes, &tmp));
+      HIP_TRY(launch_item_slabs(a, W.n_items, sub, n_sub, k_in, idx, st));
+      unsigned bits = 1;
+      while (bits < 63 && ((int64_t)R * n_sub) >> bits) ++bits;
+      HIP_TRY(launch_sort_keys(k_in, k_out, idx, W.order, W.n_items, tmp, bytes, st, bits));
+    }
   }
   return LYA_OK;
 }
 
-int xi_chunk(const lya_forests* F, int target_stream) {
-  const double mean = F->n_forests ? (double)F->n_pix / (double)F->n_forests : 1.0;
-  int c = (int)llround(target_stream / (mean > 1.0 ? mean : 1.0));
-  if (c < 1) c = 1;
-  if (c > kChunkMax) c = kChunkMax;
-  return c;
+
+// Workgroups of an xi launch: all that fit, but at least four tickets each (a
+// workgroup clears and flushes its histograms whatever it did).  With several
+// output slabs, runs of at least 16 tickets (one per wave), four per workgroup where there are
+// enough.
+int xi_grid(int most, int block, int64_t n_slabs, XiArgs& a) {
+  const int64_t n = a.n_items * a.n_parts;
+  int64_t want = (n + 3) / 4;
+  a.chunk = 0;
+  {
+    // a quarter of the tickets (at least one each) dealt out to the waves
+    // beforehand, the rest a 32nd of a wave's part at a time; with three quarters
+    // dealt out the waves ended too far apart (8000 forests: 23.4 ms, not 19.6)
+    const int64_t waves = (want < most ? want : most) * (block / 64), per = waves > 0 ? n / waves : 0;
+    const int64_t share = per / 4, grab = per / 32;
+    a.share = (int32_t)(share < 1 ? 1 : (share > (1 << 20) ? 1 << 20 : share));
+    a.grab = (int32_t)(grab < 1 ? 1 : (grab > (1 << 20) ? 1 << 20 : grab));
+  }
+  if (n_slabs > 1) {
+    const int64_t per = n / (4 * (int64_t)most);
+    a.chunk = (int32_t)(per < 16 ? 16 : (per > (1 << 20) ? 1 << 20 : per));
+    want = (n + a.chunk - 1) / a.chunk;
+  }
+  return (int)(want < 1 ? 1 : (want < most ? want : most));
 }
 
 // Optional per-stage device timing: events 0..5 bracket the stages.
@@ -568,30 +633,47 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
     }
     tm.at(1);
     Worklist W;
-    const int chunk = xi_chunk(F, 4096);
+    // items of ~2048 partner pixels, shorter ones where a wave would get less
+    // than 4 of them (16 with several output slabs, where a workgroup's waves
+    // wait for each other between slabs)
+    const int chunk = xi_chunk(F, 2048);
+    const int64_t n_slabs = (int64_t)F->n_realisations * (sub ? n_sub : 1);
+    const int64_t min_items = 32 * (int64_t)ctx->n_cu * (n_slabs > 1 ? 16 : 4);
     // subsample sums and the deterministic form list each unordered pair under
     // the forest with the smaller input index: the owner (and with it which
     // forest's pixels form the run sums) then does not depend on the sky
     // index, whose strip height follows the smallest distance of the whole
     // batch
     LYA_TRY(build_worklist(ctx, F, gd, P, st, false, false, 0, 0, false, chunk, "xi", W,
-                           sub != nullptr || o->deterministic != 0));
+                           sub != nullptr || o->deterministic != 0, min_items, sub, n_sub));
     tm.at(2);
     ctx->stats.forest_pairs = W.n_pairs;
     ctx->stats.work_items = W.n_items;
     ctx->stats.candidate_pairs = W.candidates;
     unsigned int* counter;
-    LYA_TRY(wst(ctx, "xi_counter", 1, &counter));
+    LYA_TRY(wst(ctx, "xi_counter", kXiCounters * kXiCounterStride, &counter));
     XiArgs a{};
     a.finfo = P.finfo;
     a.sorted = W.sorted;
     a.nbr = W.nbr;
     a.items = W.items;
     a.n_items = W.n_items;
+    // few items: their runs of 32 pixels of f as tickets of their own, one per
+    // wave (8 with several slabs, where tickets are taken from LDS)
+    a.n_parts = 1;
+    {
+      const int64_t tickets = (n_slabs > 1 ? 8 : 1) * 32 * (int64_t)ctx->n_cu, runs = F->n_pix / F->n_forests / 32 + 1;
+      if (W.n_items > 0 && W.n_items < tickets) {
+        const int64_t parts = tickets / W.n_items;
+        a.n_parts = (int32_t)(parts < runs ? parts : runs);
+      }
+    }
+    a.order = W.order;
     a.counter = counter;
-    a.rec32 = P.rec32;
+    a.xrec32 = P.xrec32;
+    a.xaux32 = P.xaux32;
+    a.ext = P.ext;
     a.rec64 = P.rec64;
-    a.dist = F->dist;
     a.edges_par = P.edges_par;
     a.edges_perp = P.edges_perp;
     a.glob = P.glob;
@@ -615,10 +697,10 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
       HIP_TRY(launch_det_max(F, P.finfo, o->project_deltas ? P.delta_proj : F->delta, det_max, st));
       a.det_max = det_max;
       a.det_acc = det_acc;
-      const int blocks = xi_det_blocks_per_cu(o->precision, nb) * ctx->n_cu;
+      const int blocks = xi_grid(xi_det_blocks_per_cu(o->precision, nb) * ctx->n_cu, 1024, n_slabs, a);
       ctx->stats.variant = -1;
       ctx->stats.grid_blocks = blocks;
-      HIP_TRY(launch_zero(counter, 4, st));
+      HIP_TRY(launch_zero(counter, 4 * kXiCounters * kXiCounterStride, st));
       tm.at(3);
       HIP_TRY(launch_xi_det(o->precision, a, blocks, st));
       HIP_TRY(launch_finalize_det(det_acc, det_max, a.npairs, nout, nb, num, wsum, P.glob, st));
@@ -634,10 +716,10 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
 
     if (means) {
       // one run-length form with the coordinate sums; no variant choice
-      const int blocks = xi_means_blocks_per_cu(o->precision, nb) * ctx->n_cu;
+      const int blocks = xi_grid(xi_means_blocks_per_cu(o->precision, nb) * ctx->n_cu, 1024, n_slabs, a);
       ctx->stats.variant = -1;
       ctx->stats.grid_blocks = blocks;
-      HIP_TRY(launch_zero(counter, 4, st));
+      HIP_TRY(launch_zero(counter, 4 * kXiCounters * kXiCounterStride, st));
       tm.at(3);
       HIP_TRY(launch_xi_means(o->precision, a, blocks, st));
       tm.at(4);
@@ -647,55 +729,15 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
       return tm.finish(ctx);
     }
 
-    // autotune: time each variant on a prefix of the work list, into scratch outputs
-    char key[128];
-    snprintf(key, sizeof key, "xi/%d/%d/%d", o->precision, nb,
-             (int)(F->n_pix / (F->n_forests ? F->n_forests : 1) / 64));
-    int variant = 0;
-    auto found = ctx->tuned.find(key);
-    if (o->variant >= 0) {
-      if (o->variant >= xi_num_variants())
-        return fail(ctx, LYA_E_INVALID, "variant %d out of range (xi has %d)", o->variant, xi_num_variants());
-      variant = o->variant;
-    } else if (found != ctx->tuned.end()) {
-      variant = found->second;
-    } else if (o->autotune && W.n_items > 0 && !ctx->noalloc) {
-      double* sn;
-      double* sw;
-      unsigned long long* sc;
-      LYA_TRY(wst(ctx, "tune_num", (size_t)nout, &sn));
-      LYA_TRY(wst(ctx, "tune_wsum", (size_t)nout, &sw));
-      LYA_TRY(wst(ctx, "tune_cnt", (size_t)nout, &sc));
-      XiArgs t = a;
-      t.num = sn;
-      t.wsum = sw;
-      t.npairs = sc;
-      int64_t sample = W.n_items / 8;
-      if (sample < 4 * ctx->n_cu) sample = W.n_items < 4 * ctx->n_cu ? W.n_items : 4 * ctx->n_cu;
-      t.n_items = sample;
-      float best = 1e30f;
-      for (int v = 0; v < xi_num_variants(); ++v) {
-        const int blocks = xi_blocks_per_cu(v, o->precision, nb) * ctx->n_cu;
-        float ms_v = 0.f;
-        for (int rep = 0; rep < 2; ++rep) {
-          HIP_TRY(launch_zero(counter, 4, st));
-          HIP_TRY(hipEventRecord(ctx->ev[6], st));
-          HIP_TRY(launch_xi(v, o->precision, t, blocks, st));
-          HIP_TRY(hipEventRecord(ctx->ev[7], st));
-          HIP_TRY(hipEventSynchronize(ctx->ev[7]));
-          HIP_TRY(hipEventElapsedTime(&ms_v, ctx->ev[6], ctx->ev[7]));
-        }
-        if (ms_v < best) {
-          best = ms_v;
-          variant = v;
-        }
-      }
-      ctx->tuned[key] = variant;
-    }
-    const int blocks = xi_blocks_per_cu(variant, o->precision, nb) * ctx->n_cu;
+    if (o->variant >= xi_num_variants())
+      return fail(ctx, LYA_E_INVALID, "variant %d out of range (xi has %d)", o->variant, xi_num_variants());
+    const double gaps = (double)(F->n_pix - F->n_forests);
+    const int variant =
+        o->variant >= 0 ? o->variant : xi_default_variant(1.0 / gd.inv_par, gaps > 0.0 ? P.host.span / gaps : 0.0);
+    const int blocks = xi_grid(xi_blocks_per_cu(variant, o->precision, nb) * ctx->n_cu, xi_variant_block(variant), n_slabs, a);
     ctx->stats.variant = variant;
     ctx->stats.grid_blocks = blocks;
-    HIP_TRY(launch_zero(counter, 4, st));
+    HIP_TRY(launch_zero(counter, 4 * kXiCounters * kXiCounterStride, st));
     tm.at(3);
     HIP_TRY(launch_xi(variant, o->precision, a, blocks, st));
     tm.at(4);
@@ -1301,7 +1343,7 @@ lya_status lya_xi_backward(lya_context* ctx, const lya_forests* F, const lya_gri
   if (F->n_forests > 0 && F->n_pix > 0) {
     Prepared P;
     const bool project = o->project_deltas != 0;
-    LYA_TRY(prepare(ctx, F, G, gd, o, st, true, false, project, P));
+    LYA_TRY(prepare(ctx, F, G, gd, o, st, true, false, project, P, false, true));
     tm.at(1);
     Worklist W;
     LYA_TRY(build_worklist(ctx, F, gd, P, st, true, false, 0, 0, false, INT32_MAX, "bw", W));

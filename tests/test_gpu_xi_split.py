@@ -1,0 +1,69 @@
+"""How the xi kernel deals out its work and which form it takes, against the FP64
+oracle: forests at the edges of the 32-pixel runs and 64-lane blocks, more
+neighbours than one item holds, forests whose far end is out of reach (runs of 32
+pixels passed over whole), aligned pixel grids (r_par = 0), tickets that are parts
+of an item (few forests) and several output slabs with fewer tickets than waves.
+The narrow grid's r_par bins are narrower than the pixels, where the rule takes the
+form that adds every pair by itself.
+
+Tolerances as for the other xi tests, from the working precision: a bin's sum
+within 1e-12 (FP64) or 1e-5 (FP32 products and 32-term sums: 32 x 6e-8 = 2e-6) of
+its absolute sum; counts equal."""
+import numpy as np
+import pytest
+
+import oracle as O
+from synth import Grid, concat_realisations, make_patch, sky_cells, uniform_grid
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-12, "fp32": 1e-5}
+GRIDS = {"wide": uniform_grid(15, 60.0), "offset": Grid(np.linspace(4.0, 90.0, 12), np.linspace(2.0, 70.0, 18)),
+         "narrow": uniform_grid(20, 30.0)}
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2507_00129_amd import Library
+    L = Library(0)
+    yield L
+    L.close()
+
+
+def compare(out, ref, prec, shape):
+    assert ref.n_near_edge == 0, "input has pairs within 1e-12 of an edge; choose another seed"
+    np.testing.assert_array_equal(out["npairs"].reshape(shape), ref.npairs.reshape(shape))
+    e_n = float(np.max(np.abs(out["num"].reshape(shape) - ref.num.reshape(shape)) /
+                       np.where(ref.absnum > 0, ref.absnum, 1.0).reshape(shape)))
+    e_w = O.err_rel(out["wsum"].reshape(shape), ref.wsum.reshape(shape))
+    print(f"[{prec}] pairs={int(ref.npairs.sum())} e_N={e_n:.2e} e_W={e_w:.2e}", flush=True)
+    assert e_n <= TOL[prec] and e_w <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("grid", list(GRIDS))
+@pytest.mark.parametrize("n,npix,width", [(3, (64, 65), 0.1), (40, (1, 33), 0.3), (60, (31, 129), 0.5),
+                                          (24, (300, 700), 0.6)])
+def test_items_runs_and_parts(lib, prec, grid, n, npix, width):
+    from paper_2507_00129_amd import DeviceForests
+    G = GRIDS[grid]
+    # quasars below z = 2.46 start at one wavelength: their pixels are aligned
+    log = npix[0] < 200  # 2 Mpc/h pixels; else 0.5
+    F = concat_realisations([make_patch(n, width, 40 + n, model="log" if log else "lin", npix_range=npix, z_range=(2.1, 2.6)),
+                             make_patch(5, width, 41 + n, npix_range=(1, 40), z_range=(2.1, 2.4))])
+    ref = O.xi_sums(F, G)
+    out = lib.xi(DeviceForests.from_host(F), G, precision=prec)
+    assert lib.last_stats()["variant"] == (1 if grid == "narrow" and log else 3)
+    compare({k: out[k].cpu().numpy() for k in ("npairs", "num", "wsum")}, ref, prec, (2, G.n_bins))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,cells", [(9, 3), (60, 5), (150, 2)])
+def test_slabs_with_few_tickets(lib, prec, n, cells):
+    from paper_2507_00129_amd import DeviceForests
+    F = make_patch(n, 0.2 * n ** 0.5, 70 + n, npix_range=(20, 140), z_range=(2.1, 2.6))
+    sub, G, n_sub = sky_cells(F, cells, cells), GRIDS["wide"], cells * cells
+    ref = O.xi_sums(F, G, sub=sub, n_sub=n_sub)
+    out = lib.xi_subsamples(DeviceForests.from_host(F), G, torch.from_numpy(sub).cuda(), n_sub, precision=prec)
+    compare({k: out[k].cpu().numpy() for k in ("npairs", "num", "wsum")}, ref, prec, (n_sub, G.n_bins))
