@@ -6,195 +6,365 @@
 //                                        S2_i = sum_j gamma xi w_j
 // over every pixel j of every other forest of the same realisation.
 //
-// Work item = one forest f with all of its neighbours (a symmetric neighbour
-// list), so every contribution to f's pixels is summed inside one workgroup
-// and written with plain stores.  Lanes own pixels i of f; the neighbour's
-// pixels j are wave-uniform (scalar loads, several records at a time); the
-// bin of each pair comes from the shared binner, and over a run of
-// consecutive pixels j in one bin the lane sums w_j delta_j and w_j before it
-// gathers gamma, gamma*xi from an LDS table once for the run.  Waves
-// split the neighbours; each lane sums a neighbour's contributions in the
-// working precision, adds them to FP64 registers, and the waves combine their
-// FP64 sums through LDS.
+// Work item = one forest f with some of its neighbours (a symmetric neighbour
+// list); each wave takes items by itself.  Lanes own 64 pixels i of f at a time;
+// the neighbour's pixels j are wave-uniform (scalar loads, several records at a
+// time).  Bins come from FP64 coordinates 2^20 + x (upper word: the bin, lower:
+// the fraction), as in the forward kernel.  Over a run of consecutive pixels j
+// in one bin the lane sums w_j delta_j and w_j in the form's arithmetic; gamma
+// and gamma xi come from an LDS table once per run.  A finished run waits in its
+// lane (one slot), so that the lanes' runs, which end at different pixels, meet
+// the table together.  A neighbour's sums are added to FP64 registers in the
+// form's precision, an item's to S1 and S2 in global memory; a last kernel makes
+// the gradients of them.
+//
+// The table holds one realisation; items are ordered by realisation, and a wave
+// whose item belongs to the next one waits until the others get there too.
+//
+// Measured (MI355X, FP32, 3.3e10 candidate pairs counted once, 50 x 50 bins to 200
+// Mpc/h): 15.6 ms, against 44 of one workgroup of 8 waves per forest with FP32
+// geometry, which kept 4 waves on a SIMD, gathered from the table at each
+// iteration with the end of a run (36 vector instructions an iteration) and had 6
+// forests per workgroup to balance.  Bound by the vector units; a quarter of the
+// lanes have no pixel (forests of 100).
 #include "lya_bin.h"
 #include "lya_common.h"
+#include "lya_pairs.h"
 
 namespace lya {
 
 namespace {
 
-constexpr int kGroup = 2048;  // pixels of f handled per pass (LDS accumulators)
+typedef const __attribute__((address_space(4))) BwdArgs* BArgs;
+// The kernel's arguments, read again where they are used: what only an item or
+// the exact path needs does not stay in scalar registers through the pair loop.
+__device__ __forceinline__ BArgs bargs() {
+  BArgs p = (BArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
 
-template <typename R>
-__device__ __forceinline__ R load_u(const R* p);
-typedef float bw_f4 __attribute__((ext_vector_type(4)));
-typedef double bw_d4 __attribute__((ext_vector_type(4)));
-template <>
-__device__ __forceinline__ Rec32 load_u(const Rec32* p) {
-  const bw_f4 v = *(const __attribute__((address_space(4))) bw_f4*)p;
-  return Rec32{v.x, v.y, v.z, v.w};
-}
-template <>
-__device__ __forceinline__ Rec64 load_u(const Rec64* p) {
-  const bw_d4 v = *(const __attribute__((address_space(4))) bw_d4*)p;
-  return Rec64{v.x, v.y, v.z, v.w};
-}
-// Four (FP32) or two (FP64) consecutive records with one scalar load.
-template <typename R> struct BwBatch;
-typedef float bw_f16 __attribute__((ext_vector_type(16)));
-typedef double bw_d8 __attribute__((ext_vector_type(8)));
-template <> struct BwBatch<Rec32> {
-  static constexpr int N = 4;
-  Rec32 r[4];
-  __device__ __forceinline__ void load(const Rec32* p) {
-    const bw_f16 v = *(const __attribute__((address_space(4))) bw_f16*)p;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) r[u] = Rec32{v[4 * u], v[4 * u + 1], v[4 * u + 2], v[4 * u + 3]};
-  }
-};
-template <> struct BwBatch<Rec64> {
-  static constexpr int N = 2;
-  Rec64 r[2];
-  __device__ __forceinline__ void load(const Rec64* p) {
-    const bw_d8 v = *(const __attribute__((address_space(4))) bw_d8*)p;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) r[u] = Rec64{v[4 * u], v[4 * u + 1], v[4 * u + 2], v[4 * u + 3]};
-  }
+// A wave's item: its neighbours.
+struct BwdTab {
+  int64_t pix[kChunkMax];
+  double s[kChunkMax], c[kChunkMax];
+  int32_t n[kChunkMax], f[kChunkMax];
 };
 
-__device__ __forceinline__ double load_ud(const double* p) {
-  return *(const __attribute__((address_space(4))) double*)p;
+template <typename T> struct Pair2;
+template <> struct Pair2<float> { using type = float2; };
+template <> struct Pair2<double> { using type = double2; };
+
+// In the lanes of mask m: the run (rkey, aN, aW) becomes the waiting run and a
+// run in bin L starts (under the mask and in place, see k_xi.hip's change_run).
+__device__ __forceinline__ void next_run(uint64_t m, uint32_t L, uint32_t& pkey, uint32_t& rkey, float& pN, float& pW,
+                                         float& aN, float& aW) {
+  uint64_t t;
+  asm volatile("s_and_saveexec_b64 %[t], %[m]\n\t"
+               "v_mov_b32_e32 %[pk], %[rk]\n\t"
+               "v_mov_b32_e32 %[pn], %[an]\n\t"
+               "v_mov_b32_e32 %[pw], %[aw]\n\t"
+               "v_mov_b32_e32 %[rk], %[L]\n\t"
+               "v_mov_b32_e32 %[an], 0\n\t"
+               "v_mov_b32_e32 %[aw], 0\n\t"
+               "s_mov_b64 exec, %[t]"
+               : [t] "=&s"(t), [pk] "+v"(pkey), [rk] "+v"(rkey), [pn] "+v"(pN), [pw] "+v"(pW),
+                 [an] "+v"(aN), [aw] "+v"(aW)
+               : [m] "s"(m), [L] "v"(L)
+               : "scc");
+}
+__device__ __forceinline__ void next_run(uint64_t m, uint32_t L, uint32_t& pkey, uint32_t& rkey, double& pN, double& pW,
+                                         double& aN, double& aW) {
+  uint64_t t;
+  asm volatile("s_and_saveexec_b64 %[t], %[m]\n\t"
+               "v_mov_b32_e32 %[pk], %[rk]\n\t"
+               "v_mov_b64_e32 %[pn], %[an]\n\t"
+               "v_mov_b64_e32 %[pw], %[aw]\n\t"
+               "v_mov_b32_e32 %[rk], %[L]\n\t"
+               "v_mov_b64_e32 %[an], 0\n\t"
+               "v_mov_b64_e32 %[aw], 0\n\t"
+               "s_mov_b64 exec, %[t]"
+               : [t] "=&s"(t), [pk] "+v"(pkey), [rk] "+v"(rkey), [pn] "+v"(pN), [pw] "+v"(pW),
+                 [an] "+v"(aN), [aw] "+v"(aW)
+               : [m] "s"(m), [L] "v"(L)
+               : "scc");
 }
 
-template <typename T> struct RecOfB;
-template <> struct RecOfB<float> { using type = Rec32; };
-template <> struct RecOfB<double> { using type = Rec64; };
-
+// Two workgroups of 16 waves fill a CU's wave slots (2500 bins: 20 KB of table in
+// FP32, 40 KB in FP64, and 10 KB for the waves' items).
 template <typename T, int BLOCK, bool ZLO>
-__global__ __launch_bounds__(BLOCK) void xi_bwd_kernel(BwdArgs a) {
-  using Rec = typename RecOfB<T>::type;
-  constexpr int NW = BLOCK / 64;
+__global__ __launch_bounds__(BLOCK, 8) void xi_bwd_kernel(BwdArgs) {
+  using Rec = typename RecOf<T>::type;
+  using T2 = typename Pair2<T>::type;
   extern __shared__ double smem[];
-  const int NP = a.g.n_par, NT = a.g.n_perp, nb = NP * NT;
-  double* acc1 = smem;                 // [kGroup]
-  double* acc2 = smem + kGroup;        // [kGroup]
-  T* tab = (T*)(smem + 2 * kGroup);    // [nb][2]: gamma, gamma * xi  (local layout)
-  __shared__ int64_t s_item;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  T2* const gam = (T2*)smem;  // [nb]: gamma, gamma xi  (local layout)
+  __shared__ BwdTab tabs[BLOCK / 64];
+  __shared__ int s_next, s_done, s_gone;
+  __shared__ unsigned s_lo, s_hi;  // several realisations: the workgroup's run of tickets
 
-  BinK<T, ZLO> K;
-  K.init(a.g, a.glob, a.edges_par, a.edges_perp);
-  const double dc2 = 2.0 * a.glob->dc;
-  const Rec* __restrict__ recs;
-  if constexpr (sizeof(T) == 4) recs = a.rec32; else recs = a.rec64;
+  const int lane = threadIdx.x & 63;
+  BwdTab& tab = tabs[uniform((int)threadIdx.x >> 6)];
+  const int NP = bargs()->g.n_par;
+  const double mp = uniform(kMagic + kGuard - bargs()->g.e0_par * bargs()->g.inv_par);
+  const double uphi = uniform(kMagic + NP + 2.0 * kGuard), uthi = uniform(kMagic + bargs()->g.n_perp + 2.0 * kGuard);
+  const uint32_t thr = bargs()->g.exact_all ? 0xffffffffu : kGuard2;
+  // bins are carried as L = k_perp NP + k_par + G, G what the two upper words add
+  const uint32_t G = (kMagicHi & 0xffffffu) * (uint32_t)NP + kMagicHi;
+  const uint32_t Lout = G + (uint32_t)(NP * bargs()->g.n_perp);
+  if (threadIdx.x == 0) {
+    s_next = kWaitAll;
+    s_lo = s_hi = 0u;
+    s_gone = 0;
+  }
 
-  int cur_real = -1;
+  int cur = -1;        // realisation of the table
+  bool have = false;   // an item is held
+  unsigned turns_taken = blockIdx.x;  // thread 0: the next run of tickets
+  unsigned ticket = (unsigned)uniform((int)threadIdx.x >> 6) * gridDim.x + blockIdx.x, ticket_end = 0;
+  int key = 0, nbc = 0, nf = 0, part = 0;
+  int64_t fpix0 = 0;
+  __syncthreads();
+
   for (;;) {
-    if (tid == 0) s_item = (int64_t)atomicAdd(a.counter, 1u);
-    __syncthreads();
-    const int64_t it = s_item;
-    if (it >= a.n_items) break;
-    const Item item = a.items[it];
-    const ForestInfo fi = a.finfo[a.sorted[item.p]];
-    if (fi.real != cur_real) {
-      const double2* src = a.gtab + (int64_t)fi.real * nb;
-      for (int L = tid; L < nb; L += BLOCK) {
-        const double2 v = src[L];
-        tab[2 * L] = (T)v.x;
-        tab[2 * L + 1] = (T)v.y;
+    if (!have) {
+      // tickets as in the forward kernel
+      const BArgs a = bargs();
+      have = true;
+      const unsigned waves = (BLOCK / 64) * gridDim.x;
+      unsigned t = ticket;
+      if (a->chunk > 0) {
+        if (lane == 0) {
+          t = atomicAdd(&s_lo, 1u);
+          t = t < s_hi ? t : ~0u;
+        }
+        t = (unsigned)uniform((int)t);
+      } else if (ticket < (unsigned)a->share * waves) {
+        ticket += waves;
+        if (ticket >= (unsigned)a->share * waves) ticket = ticket_end = (unsigned)a->share * waves;
+      } else {
+        if (ticket == ticket_end) {
+          ticket = t = grab_ticket(a->counter, (unsigned)a->share * waves, (unsigned)a->grab,
+                                            (unsigned)(a->n_items * a->n_parts), &s_gone);
+          ticket_end = ticket + (unsigned)a->grab;
+        }
+        if (t != ~0u) ++ticket;
       }
-      cur_real = fi.real;
+      key = kWaitAll;
+      if ((int64_t)t < a->n_items * a->n_parts) {
+        part = t % (unsigned)a->n_parts;
+        t /= (unsigned)a->n_parts;
+        const Item item = a->items[t];
+        const ForestInfo fi = a->finfo[a->sorted[item.p]];
+        key = uniform(fi.real);
+        nbc = uniform(item.nb_count);
+        nf = uniform(fi.npix);
+        fpix0 = ((int64_t)uniform((int)(fi.pix0 >> 32)) << 32) | (uint32_t)uniform((int)fi.pix0);
+        if (lane < nbc) {
+          const int g = a->sorted[a->nbr[item.nb_begin + lane]];
+          const ForestInfo gi = a->finfo[g];
+          double s, c;
+          pair_sc(fi, gi, s, c);
+          tab.pix[lane] = gi.pix0;
+          tab.s[lane] = s;
+          tab.c[lane] = c;
+          tab.n[lane] = gi.npix;
+          tab.f[lane] = g;
+        }
+      }
     }
-    const Rec* __restrict__ rf = recs + fi.pix0;
-    const int nf = fi.npix;
+    if (key != cur) {
+      // every wave of the workgroup comes here before any goes on
+      if (lane == 0) atomicMin(&s_next, key);
+      __syncthreads();
+      const BArgs a = bargs();
+      const int next = uniform(s_next);
+      const bool refill = next == kWaitAll && a->chunk > 0;
+      if (next != kWaitAll) {
+        const int nb = NP * a->g.n_perp;
+        const double2* src = a->gtab + (int64_t)next * nb;
+        for (int L = threadIdx.x; L < nb; L += BLOCK) {
+          const double2 v = src[L];
+          T2 g;
+          g.x = (T)v.x;
+          g.y = (T)v.y;
+          gam[L] = g;
+        }
+      }
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        s_next = kWaitAll;
+        if (refill) {
+          const unsigned n = (unsigned)(a->n_items * a->n_parts), c = (unsigned)a->chunk;
+          const uint64_t lo = (uint64_t)turns_taken * c;
+          s_lo = lo < n ? (unsigned)lo : n;
+          s_hi = lo + c < n ? (unsigned)(lo + c) : n;
+          s_done = lo >= n;
+          turns_taken = gridDim.x + atomicAdd(a->counter, 1u);
+        }
+      }
+      __syncthreads();
+      if (refill) {
+        if (uniform(s_done) != 0) break;
+        have = false;
+        continue;
+      }
+      cur = next;
+      if (cur == kWaitAll) break;
+      continue;
+    }
+    have = false;
 
-    for (int g0 = 0; g0 < nf; g0 += kGroup) {
-      const int ng0 = min(kGroup, nf - g0);
-      for (int x = tid; x < ng0; x += BLOCK) {
-        acc1[x] = 0.0;
-        acc2[x] = 0.0;
+    for (int i0 = 64 * part; i0 < nf; i0 += 64 * bargs()->n_parts) {
+      const int i = i0 + lane;
+      const bool valid = i < nf;
+      double Di = 0.0, s1 = 0.0, s2 = 0.0;
+      {
+        const BArgs a = bargs();
+        const Rec* recs;
+        if constexpr (sizeof(T) == 4) recs = a->xrec32; else recs = a->rec64;
+        if (valid) Di = recs[fpix0 + i].d;
       }
-      __syncthreads();
-      for (int ib = 0; ib < ng0; ib += 64) {
-        const int i = g0 + ib + lane;
-        const bool valid = ib + lane < ng0;
-        Rec ri;
-        double Di64 = 0.0;
-        if (valid) {
-          ri = rf[i];
-          if constexpr (sizeof(T) == 4) Di64 = a.dist[fi.pix0 + i];
-        } else {
-          ri.d = (T)1e30;  // far away: never in the grid
-          ri.wd = 0;
-          ri.w = 0;
-          ri.del = 0;
+#pragma unroll 1
+      for (int k = 0; k < nbc; ++k) {
+        // lanes past the forest's end: outside the grid and off the edge guard
+        double cp, st = 0.0, bt;
+        past_end(cp, bt);
+        const int ng = uniform(tab.n[k]);
+        const int64_t gp = tab.pix[k];
+        const int64_t gpix0 = ((int64_t)uniform((int)(gp >> 32)) << 32) | (uint32_t)uniform((int)gp);
+        const Rec* rg;
+        const double2* ext;
+        {
+          const BArgs a = bargs();
+          if (valid) {
+            const double s64 = tab.s[k], invt = a->g.inv_perp;
+            cp = tab.c[k] * a->g.inv_par;
+            st = s64 * invt;
+            bt = (Di * s64 - a->g.e0_perp) * invt + (kMagic + kGuard);
+          }
+          if constexpr (sizeof(T) == 4) rg = a->xrec32 + gpix0; else rg = a->rec64 + gpix0;
+          ext = a->ext + (gpix0 >> 5) + uniform(tab.f[k]);
         }
-        double s1 = 0.0, s2 = 0.0;
-        for (int k = wave; k < item.nb_count; k += NW) {
-          const ForestInfo gi = a.finfo[a.sorted[a.nbr[item.nb_begin + k]]];
-          double s64, c64;
-          pair_sc(fi, gi, s64, c64);
-          const T s = (T)s64, c = (T)c64;
-          const T bsep = sizeof(T) == 4 ? (T)(dc2 * s64) : (T)0;
-          const Rec* __restrict__ rg = recs + gi.pix0;
-          // runs of consecutive pixels j in one bin: their w delta and w are
-          // summed first and gamma, gamma xi gathered once per run
-          T p1 = 0, p2 = 0, awd = 0, aw = 0;
-          int cur = -1;
-          auto pair = [&](const Rec& rj, int j) __attribute__((always_inline)) {
-            T rp, rt;
-            separations(ri.d, rj.d, c, s, bsep, rp, rt);
-            const int L = K.bin(rp, rt, [&](double& rp64, double& rt64) {
-              if constexpr (sizeof(T) == 4) {
-                separations64(Di64, load_ud(a.dist + gi.pix0 + j), c64, s64, rp64, rt64);
-              } else {
-                rp64 = rp;
-                rt64 = rt;
-              }
-            });
-            if (L != cur) {
-              if (cur >= 0) {
-                p1 += tab[2 * cur] * awd;
-                p2 += tab[2 * cur + 1] * aw;
-              }
-              cur = L;
-              awd = 0;
-              aw = 0;
-            }
-            awd += rj.wd;
-            aw += rj.w;
-          };
-          constexpr int NBAT = BwBatch<Rec>::N;
-          int j = 0;
-          for (; j + NBAT <= gi.npix; j += NBAT) {
-            BwBatch<Rec> b;
-            b.load(rg + j);
+        T p1 = 0, p2 = 0, aN = 0, aW = 0, pN = 0, pW = 0;
+        uint32_t rkey = Lout, pkey = Lout;
+        uint64_t pend = 0ull, last = 0ull;  // lanes with a waiting run; that were inside the grid
+        auto flush = [&]() __attribute__((always_inline)) {
+          if (lane_in(pend) && pkey != Lout) {
+            const T2 g = gam[pkey - G];
+            p1 += g.x * pN;
+            p2 += g.y * pW;
+          }
+          pend = 0ull;
+        };
+        auto change = [&](uint64_t m, uint32_t L) __attribute__((always_inline)) {
+          if (m == 0ull) return;
+          if (m & pend) flush();
+          pend |= m;
+          next_run(m, L, pkey, rkey, pN, pW, aN, aW);
+        };
+        auto pairs = [&](auto n_c, const UPix<T>* r) __attribute__((always_inline)) {
+          constexpr int N = decltype(n_c)::value;
+          uint64_t in[N], some = last;
+          uint32_t L[N], low = 0xffffffffu;
 #pragma unroll
-            for (int u = 0; u < NBAT; ++u) pair(b.r[u], j + u);
+          for (int u = 0; u < N; ++u) {
+            const double up = fma(fabs(r[u].d - Di), cp, mp), ut = fma(r[u].d, st, bt);
+            in[u] = ballot(up < uphi) & ballot(ut < uthi);
+            if constexpr (!ZLO) in[u] &= ballot(up >= kMagic) & ballot(ut >= kMagic);
+            some |= in[u];
+            const uint32_t B = __umul24((uint32_t)__double2hiint(ut), (unsigned)NP) + (uint32_t)__double2hiint(up);
+            L[u] = lane_in(in[u]) ? B : Lout;
+            low = min(low, min((uint32_t)__double2loint(up), (uint32_t)__double2loint(ut)));
           }
-          for (; j < gi.npix; ++j) pair(load_u(rg + j), j);
-          if (cur >= 0) {
-            p1 += tab[2 * cur] * awd;
-            p2 += tab[2 * cur + 1] * aw;
+          if (some == 0ull) return;
+          last = in[N - 1];
+          if (ballot(low <= thr)) {
+            // some pair may be within the guard of an edge: by the edges then
+            const BArgs a = bargs();
+            double Di2 = Di;
+            asm volatile("" : "+v"(Di2));
+            int kt_last = -1;  // non-uniform edges: the bin of the pixel before is the better guess
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+              double st2 = st;
+              asm volatile("" : "+v"(st2));
+              const double up = fma(fabs(r[u].d - Di2), cp, mp), ut = fma(r[u].d, st2, bt);
+              const uint32_t hp = (uint32_t)__double2hiint(up), ht = (uint32_t)__double2hiint(ut);
+              // r_par = 0 (aligned pixel grids) needs no guard at a zero lower edge
+              uint64_t m = ballot((uint32_t)__double2loint(up) <= thr);
+              if (a->g.zero_lo_par && !a->g.exact_all) m &= ballot(hp != kMagicHi);
+              m = in[u] & (m | ballot((uint32_t)__double2loint(ut) <= thr));
+              if (m) {
+                if (lane_in(m)) {
+                  double rp64, rt64;
+                  separations64(Di2, r[u].d, tab.c[k], tab.s[k], rp64, rt64);
+                  const int kp = bin_exact(rp64, a->edges_par, NP, (int)(hp - kMagicHi));
+                  const int kt = bin_exact(rt64, a->edges_perp, a->g.n_perp,
+                                           a->g.exact_all && kt_last >= 0 ? kt_last : (int)(ht - kMagicHi));
+                  kt_last = kt;
+                  L[u] = (kp >= 0 && kt >= 0) ? G + (uint32_t)(kt * NP + kp) : Lout;
+                }
+              }
+            }
           }
-          s1 += (double)p1;
-          s2 += (double)p2;
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            change(ballot(L[u] != rkey), L[u]);
+            aN += r[u].wd;
+            aW += r[u].w;
+          }
+        };
+        constexpr int NB = Batch<T>::N;
+        for (int c0 = 0; c0 < ng; c0 += (int)kRunMax) {
+          const int c1 = min(ng, c0 + (int)kRunMax);
+          int j = c0;
+          {
+            // no pixel of this chunk within reach of any lane?  (the same rounded
+            // operations from the chunk's extent, so never wrong)
+            const lya_i4 e = LYA_CONST(lya_i4, ext + (c0 >> 5));
+            const double lo = __hiloint2double(e[1], e[0]), hi = __hiloint2double(e[3], e[2]);
+            const double gap = fmax(lo - Di, Di - hi);
+            if ((ballot(fma(gap, cp, mp) < uphi) & ballot(fma(lo, st, bt) < uthi)) == 0ull) {
+              change(ballot(rkey != Lout), Lout);
+              last = 0ull;
+              j = c1;
+            }
+          }
+#pragma unroll 1
+          for (; j + NB <= c1; j += NB) {
+            Batch<T> b;
+            b.load(rg + j);
+            pairs(std::integral_constant<int, NB>{}, b.r);
+          }
+#pragma unroll 1
+          for (; j < c1; ++j) {
+            const UPix<T> r = load_pix(rg + j);
+            pairs(std::integral_constant<int, 1>{}, &r);
+          }
         }
-        if (valid) {
-          atomicAdd(&acc1[ib + lane], s1);
-          atomicAdd(&acc2[ib + lane], s2);
-        }
+        change(ballot(rkey != Lout), Lout);
+        if (pend) flush();
+        s1 += (double)p1;
+        s2 += (double)p2;
       }
-      __syncthreads();
-      for (int x = tid; x < ng0; x += BLOCK) {
-        const int64_t i = fi.pix0 + g0 + x;
-        const double w = a.weight[i], de = a.delta[i];
-        a.grad_delta[i] = w * acc1[x];
-        a.grad_weight[i] = de * acc1[x] - acc2[x];
+      if (valid) {
+        const BArgs a = bargs();
+        atomicAdd(&a->grad_delta[fpix0 + i], s1);
+        atomicAdd(&a->grad_weight[fpix0 + i], s2);
       }
-      __syncthreads();
     }
   }
+}
+
+// The gradients from the sums S1 (in grad_delta) and S2 (in grad_weight).
+__global__ __launch_bounds__(256) void bwd_finish_kernel(const double* weight, const double* delta, int64_t n,
+                                                         double* grad_delta, double* grad_weight) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const double s1 = grad_delta[i], s2 = grad_weight[i];
+  if (s1 == 0.0 && s2 == 0.0) return;
+  grad_delta[i] = weight[i] * s1;
+  grad_weight[i] = delta[i] * s1 - s2;
 }
 
 // gamma_A = dL/dxi_A / W_A (0 where W_A = 0) and gamma_A xi_A, in the local
@@ -248,23 +418,25 @@ __global__ __launch_bounds__(256) void project_adjoint_kernel(lya_forests F, con
   }
 }
 
-template <typename T, int BLOCK>
+constexpr int kBlock = 1024;
+
+template <typename T>
 hipError_t launch_one(const BwdArgs& a, int blocks, hipStream_t st) {
-  const size_t smem = 2 * kGroup * sizeof(double) + (size_t)a.g.n_par * a.g.n_perp * 2 * sizeof(T);
-  auto kern = (a.g.zero_lo_par && a.g.zero_lo_perp) ? xi_bwd_kernel<T, BLOCK, true> : xi_bwd_kernel<T, BLOCK, false>;
+  const size_t smem = (size_t)a.g.n_par * a.g.n_perp * 2 * sizeof(T);
+  auto kern = (a.g.zero_lo_par && a.g.zero_lo_perp) ? xi_bwd_kernel<T, kBlock, true> : xi_bwd_kernel<T, kBlock, false>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(BLOCK), smem, st, a);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), smem, st, a);
   return hipGetLastError();
 }
 
-template <typename T, int BLOCK>
+template <typename T>
 int occupancy(int n_bins) {
-  const size_t smem = 2 * kGroup * sizeof(double) + (size_t)n_bins * 2 * sizeof(T);
-  auto kern = xi_bwd_kernel<T, BLOCK, true>;
+  const size_t smem = (size_t)n_bins * 2 * sizeof(T);
+  auto kern = xi_bwd_kernel<T, kBlock, true>;
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return 1;
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, BLOCK, smem) != hipSuccess) return 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, kBlock, smem) != hipSuccess) return 1;
   return n > 0 ? n : 1;
 }
 
@@ -289,11 +461,16 @@ hipError_t launch_project_adjoint(const lya_forests* F, const EtaInfo* einfo, co
 
 hipError_t launch_xi_bwd(int precision, const BwdArgs& a, int blocks, hipStream_t st) {
   if (a.n_items == 0) return hipSuccess;
-  return precision == LYA_FP64 ? launch_one<double, 512>(a, blocks, st) : launch_one<float, 512>(a, blocks, st);
+  const hipError_t e = precision == LYA_FP64 ? launch_one<double>(a, blocks, st) : launch_one<float>(a, blocks, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(bwd_finish_kernel, dim3((unsigned)((a.n_pix + 255) / 256)), dim3(256), 0, st, a.weight, a.delta,
+                     a.n_pix, a.grad_delta, a.grad_weight);
+  return hipGetLastError();
 }
 
+int xi_bwd_block() { return kBlock; }
 int xi_bwd_blocks_per_cu(int precision, int n_bins) {
-  return precision == LYA_FP64 ? occupancy<double, 512>(n_bins) : occupancy<float, 512>(n_bins);
+  return precision == LYA_FP64 ? occupancy<double>(n_bins) : occupancy<float>(n_bins);
 }
 
 }  // namespace lya

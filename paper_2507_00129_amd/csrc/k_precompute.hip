@@ -227,7 +227,6 @@ __global__ __launch_bounds__(256) void pack_kernel(PrecomputeArgs a, lya_forests
     // fourth slot: delta, or the pixel redshift lambda / lambda_Lya - 1 with
     // lambda = exp(loglam) Angstrom (bin means)
     const double x4 = a.pack_z ? exp(F.loglam[i]) / kLyaAlphaAngstrom - 1.0 : de;
-    if (a.rec32) a.rec32[i] = Rec32{(float)(D - dc), (float)wd, (float)w, (float)x4};
     if (a.xrec32) a.xrec32[i] = XRec32{D, (float)wd, (float)w};
     if (a.xaux32) a.xaux32[i] = XAux32{(float)(D - dc), (float)x4};
     if (a.want_xi64) a.rec64[i] = Rec64{D, wd, w, x4};

@@ -65,64 +65,11 @@
 
 #include "lya_bin.h"
 #include "lya_common.h"
+#include "lya_pairs.h"
 
 namespace lya {
 
 namespace {
-
-constexpr unsigned kRunMax = 32;
-constexpr int kWaitAll = 0x7fffffff;
-
-// 2^20 and its upper word: 2^20 + x has floor(x) in the low bits of its upper
-// word and the fraction in its lower word, in units of 2^-32.
-constexpr double kMagic = 1048576.0;
-constexpr uint32_t kMagicHi = 0x41300000u;
-constexpr double kGuard = 1e-8;        // edge guard, bins
-constexpr uint32_t kGuard2 = 86u;      // 2 kGuard in units of 2^-32
-
-// Loads through the constant address space: with a wave-uniform address the
-// compiler emits scalar (SMEM) loads.  Native vector types are used because
-// class copies cannot bind to address-space-qualified objects.
-typedef int lya_i16 __attribute__((ext_vector_type(16)));
-typedef int lya_i4 __attribute__((ext_vector_type(4)));
-typedef int lya_i8 __attribute__((ext_vector_type(8)));
-typedef int lya_i2 __attribute__((ext_vector_type(2)));
-#define LYA_CONST(T, p) (*(const __attribute__((address_space(4))) T*)(p))
-
-// A pixel of f in scalar registers.
-template <typename T> struct UPix { double d; T wd, w; };
-
-// Four FP32 records or two FP64 records (64 bytes) per scalar load.
-template <typename T> struct Batch;
-template <> struct Batch<float> {
-  static constexpr int N = 4;
-  UPix<float> r[4];
-  __device__ __forceinline__ void load(const XRec32* p) {
-    const lya_i16 v = LYA_CONST(lya_i16, p);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      r[u] = UPix<float>{__hiloint2double(v[4 * u + 1], v[4 * u]), __int_as_float(v[4 * u + 2]), __int_as_float(v[4 * u + 3])};
-  }
-};
-template <> struct Batch<double> {
-  static constexpr int N = 2;
-  UPix<double> r[2];
-  __device__ __forceinline__ void load(const Rec64* p) {
-    const lya_i16 v = LYA_CONST(lya_i16, p);
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-      r[u] = UPix<double>{__hiloint2double(v[8 * u + 1], v[8 * u]), __hiloint2double(v[8 * u + 3], v[8 * u + 2]),
-                          __hiloint2double(v[8 * u + 5], v[8 * u + 4])};
-  }
-};
-__device__ __forceinline__ UPix<float> load_pix(const XRec32* p) {
-  const lya_i4 v = LYA_CONST(lya_i4, p);
-  return UPix<float>{__hiloint2double(v[1], v[0]), __int_as_float(v[2]), __int_as_float(v[3])};
-}
-__device__ __forceinline__ UPix<double> load_pix(const Rec64* p) {
-  const lya_i8 v = LYA_CONST(lya_i8, p);
-  return UPix<double>{__hiloint2double(v[1], v[0]), __hiloint2double(v[3], v[2]), __hiloint2double(v[5], v[4])};
-}
 
 // Fixed-point terms of the deterministic form: q = rint(x), |q| <= 2^55.  A
 // workgroup sums them in LDS in a 64-bit low and a 32-bit high word; its sum S
@@ -155,10 +102,6 @@ __device__ __forceinline__ int det_shift(unsigned long long mbits) {
   const int sh = kDetBits - 2 * e;
   return sh > 1000 ? 1000 : (sh < -1000 ? -1000 : sh);
 }
-
-template <typename T> struct RecOf;
-template <> struct RecOf<float> { using type = XRec32; };
-template <> struct RecOf<double> { using type = Rec64; };
 
 // LDS sums: arrays of nd = n_bins + 64 entries, the last 64 for the pairs
 // outside the grid, one per lane (one for all would be a conflict of all).  FP64 sums first: N, W and, with MEANS, w w x_par, w w x_perp, w w
@@ -234,12 +177,6 @@ struct WaveTab {
   double s[kChunkMax], c[kChunkMax];
   int32_t pos[kChunkMax];
 };
-
-__device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ double uniform(double x) {
-  return __hiloint2double(uniform(__double2hiint(x)), uniform(__double2loint(x)));
-}
 
 // Lanes whose bin is not that of the run they sum (their low 16 bits differ).
 __device__ __forceinline__ uint64_t other_bin(uint32_t L, uint32_t rkey) {
@@ -365,20 +302,8 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
         if (ticket >= (unsigned)a->share * waves) ticket = ticket_end = (unsigned)a->share * waves;
       } else {
         if (ticket == ticket_end) {
-          t = ~0u;
-          if (lane == 0) {
-            for (int k = s_gone; k < kXiCounters;) {
-              const unsigned w = ((blockIdx.x >> 3) + k) % kXiCounters;
-              const int64_t b = (int64_t)atomicAdd(a->counter + w * kXiCounterStride, 1u) * kXiCounters + w;
-              const int64_t t0 = (int64_t)a->share * waves + b * a->grab;
-              if (t0 < a->n_items * a->n_parts) {
-                t = (unsigned)t0;
-                break;
-              }
-              k = max(k + 1, atomicMax(&s_gone, k + 1));
-            }
-          }
-          ticket = t = (unsigned)uniform((int)t);
+          ticket = t = grab_ticket(a->counter, (unsigned)a->share * waves, (unsigned)a->grab,
+                                            (unsigned)(a->n_items * a->n_parts), &s_gone);
           ticket_end = ticket + (unsigned)a->grab;
         }
         if (t != ~0u) ++ticket;
@@ -516,7 +441,9 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
 #pragma unroll
       for (int step = kChunkMax / 2; step > 0; step >>= 1)
         if (k + step < nbc && tab.pos[k + step] <= q) k += step;
-      double Dj = 0.0, cp = 0.0, st = 0.0, bt = 1.5 * kMagic;  // past the stream's end: outside the grid
+      // (past the stream's end: no pixel)
+      double Dj = 0.0, cp, st = 0.0, bt;
+      past_end(cp, bt);
       T wdj = 0, wj = 0, dj = 0, zj = 0, mcp = 0, mst = 0, mbt = 0, mep = 0;
       {
         const KArgs a = kargs();

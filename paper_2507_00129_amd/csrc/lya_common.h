@@ -47,7 +47,6 @@ struct Globals {
 };
 
 // Pixel records for the xi and backward kernels.
-struct __align__(16) Rec32 { float d, wd, w, del; };   // d = D - dc
 struct __align__(32) Rec64 { double d, wd, w, del; };  // d = D
 // The xi kernel's FP32 form: FP64 distance, FP32 products; and, for the bin
 // means, d = D - dc and the pixel redshift.
@@ -185,7 +184,6 @@ struct PrecomputeArgs {
   ForestInfo* finfo;
   EtaInfo* einfo;
   double* delta_proj;   // [n_pix] when project
-  Rec32* rec32;
   Rec64* rec64;
   XRec32* xrec32;       // optional
   XAux32* xaux32;       // optional
@@ -384,12 +382,13 @@ struct BwdArgs {
   const ForestInfo* finfo;
   const int32_t* sorted;
   const int32_t* nbr;
-  const Item* items;       // one item per forest, all its neighbours (symmetric list)
+  const Item* items;       // a forest and some of its neighbours (symmetric list)
   int64_t n_items;
+  int32_t n_parts, share, grab, chunk;  // as in XiArgs; a part of an item: every n-th 64 pixels of its forest
   unsigned int* counter;
-  const Rec32* rec32;
+  const XRec32* xrec32;
+  const double2* ext;
   const Rec64* rec64;
-  const double* dist;
   const double* weight;
   const double* delta;
   const double* edges_par;
@@ -397,7 +396,8 @@ struct BwdArgs {
   const Globals* glob;
   GridDev g;
   const double2* gtab;     // [R][nb] (gamma, gamma * xi) in local bin order
-  double* grad_delta;
+  int64_t n_pix;
+  double* grad_delta;      // S1 and S2 on the way
   double* grad_weight;
 };
 hipError_t launch_gamma(const double* grad_xi, const double* xi, const double* wsum, double2* out,
@@ -481,6 +481,7 @@ hipError_t launch_finalize_means(const double* wsum, const double* msum, int64_t
                                  double* rpar, double* rperp, double* z, hipStream_t st);
 hipError_t launch_project_adjoint(const lya_forests* F, const EtaInfo* einfo, const double* delta_proj,
                                   double* grad_delta, double* grad_weight, hipStream_t st);
+int xi_bwd_block();
 int xi_bwd_blocks_per_cu(int precision, int n_bins);
 
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);

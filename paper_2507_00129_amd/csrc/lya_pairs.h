@@ -1,0 +1,104 @@
+// What the pair kernels (xi and its backward pass) share: bin coordinates as
+// 2^20 + x, wave-uniform pixel loads and the hand-out of work.
+#pragma once
+#include <type_traits>
+
+#include "lya_common.h"
+
+namespace lya {
+
+constexpr unsigned kRunMax = 32;
+constexpr int kWaitAll = 0x7fffffff;
+
+// 2^20 and its upper word: 2^20 + x has floor(x) in the low bits of its upper
+// word and the fraction in its lower word, in units of 2^-32.
+constexpr double kMagic = 1048576.0;
+constexpr uint32_t kMagicHi = 0x41300000u;
+constexpr double kGuard = 1e-8;        // edge guard, bins
+constexpr uint32_t kGuard2 = 86u;      // 2 kGuard in units of 2^-32
+
+// Loads through the constant address space: with a wave-uniform address the
+// compiler emits scalar (SMEM) loads.  Native vector types are used because
+// class copies cannot bind to address-space-qualified objects.
+typedef int lya_i16 __attribute__((ext_vector_type(16)));
+typedef int lya_i4 __attribute__((ext_vector_type(4)));
+typedef int lya_i8 __attribute__((ext_vector_type(8)));
+typedef int lya_i2 __attribute__((ext_vector_type(2)));
+#define LYA_CONST(T, p) (*(const __attribute__((address_space(4))) T*)(p))
+
+// A pixel of f in scalar registers.
+template <typename T> struct UPix { double d; T wd, w; };
+
+// Four FP32 records or two FP64 records (64 bytes) per scalar load.
+template <typename T> struct Batch;
+template <> struct Batch<float> {
+  static constexpr int N = 4;
+  UPix<float> r[4];
+  __device__ __forceinline__ void load(const XRec32* p) {
+    const lya_i16 v = LYA_CONST(lya_i16, p);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      r[u] = UPix<float>{__hiloint2double(v[4 * u + 1], v[4 * u]), __int_as_float(v[4 * u + 2]), __int_as_float(v[4 * u + 3])};
+  }
+};
+template <> struct Batch<double> {
+  static constexpr int N = 2;
+  UPix<double> r[2];
+  __device__ __forceinline__ void load(const Rec64* p) {
+    const lya_i16 v = LYA_CONST(lya_i16, p);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      r[u] = UPix<double>{__hiloint2double(v[8 * u + 1], v[8 * u]), __hiloint2double(v[8 * u + 3], v[8 * u + 2]),
+                          __hiloint2double(v[8 * u + 5], v[8 * u + 4])};
+  }
+};
+__device__ __forceinline__ UPix<float> load_pix(const XRec32* p) {
+  const lya_i4 v = LYA_CONST(lya_i4, p);
+  return UPix<float>{__hiloint2double(v[1], v[0]), __int_as_float(v[2]), __int_as_float(v[3])};
+}
+__device__ __forceinline__ UPix<double> load_pix(const Rec64* p) {
+  const lya_i8 v = LYA_CONST(lya_i8, p);
+  return UPix<double>{__hiloint2double(v[1], v[0]), __hiloint2double(v[3], v[2]), __hiloint2double(v[5], v[4])};
+}
+
+template <typename T> struct RecOf;
+template <> struct RecOf<float> { using type = XRec32; };
+template <> struct RecOf<double> { using type = Rec64; };
+
+__device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ double uniform(double x) {
+  return __hiloint2double(uniform(__double2hiint(x)), uniform(__double2loint(x)));
+}
+
+// Coefficients of a lane without a pixel: up = 2^20 + e0 + 2^-17 |D_i - D_j|, ut =
+// 1.5 * 2^20 + 0.5: outside the grid and, for any usual unit of D, off the edge guard,
+// which would send every batch of the wave to the exact path (as zeros would: 0.16 ms
+// instead of 0.09 for 234 forests of 47 pixels).  Written out: the compiler would keep
+// the constants in registers through the pair loop.
+__device__ __forceinline__ void past_end(double& cp, double& bt) {
+  int c, h, l;
+  asm volatile("v_mov_b32_e32 %0, 0x3ee00000\n\tv_mov_b32_e32 %1, 0x41380000\n\tv_mov_b32_e32 %2, 0x80000000"
+               : "=v"(c), "=v"(h), "=v"(l));
+  cp = __hiloint2double(c, 0);
+  bt = __hiloint2double(h, l);
+}
+
+// A wave's next `grab` tickets of n, the first of which is returned (~0u: none left),
+// from kXiCounters counters beyond the first `base` tickets, the workgroup's own
+// counter first.  gone (LDS): counters the workgroup has found empty.
+__device__ __forceinline__ unsigned grab_ticket(unsigned* counter, unsigned base, unsigned grab, unsigned n, int* gone) {
+  unsigned t = ~0u;
+  if ((threadIdx.x & 63) == 0) {
+    for (int k = *(volatile int*)gone; k < kXiCounters;) {
+      const unsigned w = ((blockIdx.x >> 3) + k) % kXiCounters;
+      t = base + (atomicAdd(counter + w * kXiCounterStride, 1u) * kXiCounters + w) * grab;
+      if (t < n) break;
+      t = ~0u;
+      k = max(k + 1, atomicMax(gone, k + 1));
+    }
+  }
+  return (unsigned)uniform((int)t);
+}
+
+}  // namespace lya

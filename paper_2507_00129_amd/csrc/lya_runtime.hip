@@ -231,7 +231,6 @@ __global__ void init_globals_kernel(Globals* g) {
 struct Prepared {
   Globals* glob = nullptr;
   ForestInfo* finfo = nullptr;
-  Rec32* rec32 = nullptr;
   Rec64* rec64 = nullptr;
   XRec32* xrec32 = nullptr;
   XAux32* xaux32 = nullptr;
@@ -248,7 +247,7 @@ struct Prepared {
 // Validation, per-forest sums and record packing.
 lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, const GridDev& gd,
                    const lya_options* o, hipStream_t st, bool xi_rec, bool d_rec, bool project,
-                   Prepared& P, bool pack_z = false, bool bwd_rec = false) {
+                   Prepared& P, bool pack_z = false) {
   const int64_t N = F->n_forests, npix = F->n_pix;
   LYA_TRY(wst(ctx, "globals", 1, &P.glob));
   LYA_TRY(wst(ctx, "finfo", (size_t)N, &P.finfo));
@@ -294,9 +293,8 @@ lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
   a.inv_par = gd.inv_par;
   a.inv_perp = gd.inv_perp;
   if (project) LYA_TRY(wst(ctx, "delta_proj", (size_t)npix, &a.delta_proj));
-  if (a.want_xi32 && bwd_rec) LYA_TRY(wst(ctx, "rec32", (size_t)npix, &a.rec32));
-  if (a.want_xi32 && !bwd_rec) LYA_TRY(wst(ctx, "xrec32", (size_t)npix, &a.xrec32));
-  if (xi_rec && !bwd_rec) LYA_TRY(wst(ctx, "xi_ext", (size_t)(npix / 32 + N + 1), &a.ext));
+  if (a.want_xi32) LYA_TRY(wst(ctx, "xrec32", (size_t)npix, &a.xrec32));
+  if (xi_rec) LYA_TRY(wst(ctx, "xi_ext", (size_t)(npix / 32 + N + 1), &a.ext));
   if (a.want_xi32 && pack_z) LYA_TRY(wst(ctx, "xaux32", (size_t)npix, &a.xaux32));
   if (a.want_xi64) LYA_TRY(wst(ctx, "rec64", (size_t)npix, &a.rec64));
   if (a.want_d32) LYA_TRY(wst(ctx, "drec32", (size_t)npix, &a.drec32));
@@ -309,7 +307,6 @@ lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
   memcpy(&P.host, ctx->pinned, sizeof(Globals));
   P.einfo = einfo;
   P.delta_proj = a.delta_proj;
-  P.rec32 = a.rec32;
   P.rec64 = a.rec64;
   P.xrec32 = a.xrec32;
   P.xaux32 = a.xaux32;
@@ -461,11 +458,21 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
 }
 
 
-// Workgroups of an xi launch: all that fit, but at least four tickets each (a
+// Few items: tickets are parts of an item (every n-th run of `pixels` pixels of its
+// forest), one per wave, or 8 with several slabs, where tickets are taken from LDS.
+int32_t item_parts(const lya_context* ctx, const lya_forests* F, int64_t n_items, int64_t n_slabs, int pixels) {
+  const int64_t tickets = (n_slabs > 1 ? 8 : 1) * 32 * (int64_t)ctx->n_cu;
+  if (n_items <= 0 || n_items >= tickets) return 1;
+  const int64_t parts = tickets / n_items, runs = F->n_pix / F->n_forests / pixels + 1;
+  return (int32_t)(parts < runs ? parts : runs);
+}
+
+// Workgroups of a launch of the xi kernel or its backward pass: all that fit, but at least four tickets each (a
 // workgroup clears and flushes its histograms whatever it did).  With several
 // output slabs, runs of at least 16 tickets (one per wave), four per workgroup where there are
 // enough.
-int xi_grid(int most, int block, int64_t n_slabs, XiArgs& a) {
+template <typename Args>
+int xi_grid(int most, int block, int64_t n_slabs, Args& a) {
   const int64_t n = a.n_items * a.n_parts;
   int64_t want = (n + 3) / 4;
   a.chunk = 0;
@@ -658,16 +665,7 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
     a.nbr = W.nbr;
     a.items = W.items;
     a.n_items = W.n_items;
-    // few items: their runs of 32 pixels of f as tickets of their own, one per
-    // wave (8 with several slabs, where tickets are taken from LDS)
-    a.n_parts = 1;
-    {
-      const int64_t tickets = (n_slabs > 1 ? 8 : 1) * 32 * (int64_t)ctx->n_cu, runs = F->n_pix / F->n_forests / 32 + 1;
-      if (W.n_items > 0 && W.n_items < tickets) {
-        const int64_t parts = tickets / W.n_items;
-        a.n_parts = (int32_t)(parts < runs ? parts : runs);
-      }
-    }
+    a.n_parts = item_parts(ctx, F, W.n_items, n_slabs, 32);
     a.order = W.order;
     a.counter = counter;
     a.xrec32 = P.xrec32;
@@ -1343,10 +1341,11 @@ lya_status lya_xi_backward(lya_context* ctx, const lya_forests* F, const lya_gri
   if (F->n_forests > 0 && F->n_pix > 0) {
     Prepared P;
     const bool project = o->project_deltas != 0;
-    LYA_TRY(prepare(ctx, F, G, gd, o, st, true, false, project, P, false, true));
+    LYA_TRY(prepare(ctx, F, G, gd, o, st, true, false, project, P));
     tm.at(1);
     Worklist W;
-    LYA_TRY(build_worklist(ctx, F, gd, P, st, true, false, 0, 0, false, INT32_MAX, "bw", W));
+    LYA_TRY(build_worklist(ctx, F, gd, P, st, true, false, 0, 0, false, xi_chunk(F, 2048), "bw", W, false,
+                           32 * (int64_t)ctx->n_cu * (R > 1 ? 16 : 4)));
     tm.at(2);
     ctx->stats.forest_pairs = W.n_pairs;
     ctx->stats.work_items = W.n_items;
@@ -1355,7 +1354,7 @@ lya_status lya_xi_backward(lya_context* ctx, const lya_forests* F, const lya_gri
     LYA_TRY(wst(ctx, "bw_gamma", (size_t)R * nb, &gtab));
     HIP_TRY(launch_gamma(grad_xi, xi, wsum, gtab, R * nb, gd.n_par, gd.n_perp, st));
     unsigned int* counter;
-    LYA_TRY(wst(ctx, "bw_counter", 1, &counter));
+    LYA_TRY(wst(ctx, "bw_counter", kXiCounters * kXiCounterStride, &counter));
     BwdArgs a{};
     a.finfo = P.finfo;
     a.sorted = W.sorted;
@@ -1363,9 +1362,10 @@ lya_status lya_xi_backward(lya_context* ctx, const lya_forests* F, const lya_gri
     a.items = W.items;
     a.n_items = W.n_items;
     a.counter = counter;
-    a.rec32 = P.rec32;
+    a.xrec32 = P.xrec32;
     a.rec64 = P.rec64;
-    a.dist = F->dist;
+    a.ext = P.ext;
+    a.n_pix = F->n_pix;
     a.weight = F->weight;
     a.delta = project ? P.delta_proj : F->delta;
     a.edges_par = P.edges_par;
@@ -1375,9 +1375,10 @@ lya_status lya_xi_backward(lya_context* ctx, const lya_forests* F, const lya_gri
     a.gtab = gtab;
     a.grad_delta = grad_delta;
     a.grad_weight = grad_weight;
-    const int blocks = xi_bwd_blocks_per_cu(o->precision, nb) * ctx->n_cu;
+    a.n_parts = item_parts(ctx, F, W.n_items, R, 64);
+    const int blocks = xi_grid(xi_bwd_blocks_per_cu(o->precision, nb) * ctx->n_cu, xi_bwd_block(), R, a);
     ctx->stats.grid_blocks = blocks;
-    HIP_TRY(launch_zero(counter, 4, st));
+    HIP_TRY(launch_zero(counter, 4 * kXiCounters * kXiCounterStride, st));
     tm.at(3);
     HIP_TRY(launch_xi_bwd(o->precision, a, blocks, st));
     if (project) HIP_TRY(launch_project_adjoint(F, P.einfo, P.delta_proj, grad_delta, grad_weight, st));

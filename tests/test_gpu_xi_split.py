@@ -67,3 +67,28 @@ def test_slabs_with_few_tickets(lib, prec, n, cells):
     ref = O.xi_sums(F, G, sub=sub, n_sub=n_sub)
     out = lib.xi_subsamples(DeviceForests.from_host(F), G, torch.from_numpy(sub).cuda(), n_sub, precision=prec)
     compare({k: out[k].cpu().numpy() for k in ("npairs", "num", "wsum")}, ref, prec, (n_sub, G.n_bins))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("grid", ["wide", "offset", "graded"])
+@pytest.mark.parametrize("n,npix,width", [(3, (64, 65), 0.1), (40, (1, 33), 0.3), (60, (127, 130), 0.5)])
+def test_gradient_items_and_realisations(lib, prec, grid, n, npix, width):
+    """The backward pass over the same edges (lanes own 64 pixels of a forest), one
+    realisation and three of unequal size; the gradients within the forward's
+    tolerances of their largest value."""
+    from paper_2507_00129_amd import DeviceForests
+    G = GRIDS[grid] if grid != "graded" else Grid(np.linspace(0.0, 60.0, 11), 60.0 * (np.arange(13) / 12) ** 1.3)
+    one = make_patch(n, width, 40 + n, npix_range=npix, z_range=(2.1, 2.6))
+    for F in (one, concat_realisations([one, make_patch(7, width, 41 + n, npix_range=(1, 40), z_range=(2.1, 2.4)),
+                                        make_patch(33, width, 42 + n, npix_range=(60, 70), z_range=(2.1, 2.4))])):
+        X = O.xi_sums(F, G)
+        assert X.n_near_edge == 0, "input has pairs within 1e-12 of an edge; choose another seed"
+        gxi = np.random.default_rng(n).normal(size=X.xi.shape)
+        want = O.xi_grad(F, G, gxi, X.xi, X.wsum)
+        dF = DeviceForests.from_host(F)
+        put = lambda x: torch.as_tensor(x, device="cuda:0")
+        got = lib.xi_backward(dF, G, put(gxi), put(X.xi), put(X.wsum), precision=prec)
+        for g, w in zip(got, want):
+            e = O.err_norm(g.cpu().numpy(), w)
+            print(f"[{prec} {grid}] e_g={e:.2e}", flush=True)
+            assert e <= TOL[prec]
