@@ -25,17 +25,28 @@
 // pixels (up to PMAX each) and bin both rows against them, adding w and w a
 // to the rows' histograms in LDS; the wave then reads the histograms back in
 // MFMA operand layout, scaled by sqrt(w_row c_l), and issues one step for
-// every tile block (bx <= by) that the union of the two rows' block masks
-// covers.  Two LDS buffers alternate (three rotate with two waves), so the
-// binning of the next two rows is issued while the matrix core works on the
-// current ones.  The pair
+// every tile block (bx <= by) that the union of the rows' block masks
+// covers.  Two LDS buffers alternate, so the binning of the next rows is
+// issued while the matrix core works on the current ones.  The pair
 // histograms H are summed in registers from the operands of the f rows; after
 // them, one more step per block adds the H term (K = 4 is kl) and the
 // Kronecker term w_A goes to an FP64 LDS accumulator.
 //
 // Two waves per workgroup (NW = 2) split the tile and the binning: wave w
-// keeps the blocks (bx, by) with bx & 1 = w and bins row r + w of each step;
-// the two rows' block masks meet in LDS after the step's barrier.
+// keeps the blocks (bx, by) with bx & 1 = w and bins every second row; they take
+// four rows, two MFMA steps, per turn (half the barriers, masks and block tests
+// per row); the rows' block masks meet in LDS after the turn's barrier.
+//
+// Bins come from FP64 coordinates 2^20 + x (upper word: the bin, lower: the
+// fraction), as in the xi kernel; pairs within 1e-8 of an edge are binned by the
+// edges.  Bound by the latency of one wave's instructions, two waves to a SIMD (the
+// tile fills the registers): a turn of the row loop is geometry, LDS adds, a barrier,
+// operand reads and a scalar test and branch for every tile block.  Measured (MI355X,
+// FP32, 5000 forests at 100 / deg^2, 2.57e6 forest pairs, 50 x 50 bins): 177 ms, of
+// which 13 are the pairs' setup and flushes, against 259 with FP32 coordinates (some
+// 40 instructions an evaluation instead of 20), tests folded into vector selects,
+// 300 scalar registers spilled and two rows per turn; large tile alone 200 against
+// 325.  The sums' order, and so every bit of them, is the same.
 //
 // Tiles: NB x NB blocks of 16 window bins (the upper triangle, NB (NB+1)/2
 // accumulators).  Windows wider than NB blocks take several passes over the
@@ -49,6 +60,7 @@
 
 #include "lya_bin.h"
 #include "lya_common.h"
+#include "lya_pairs.h"
 
 namespace lya {
 
@@ -201,6 +213,36 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// A pixel of the other forest of a sweep: distance, w, w a.
+template <typename T> struct OPix { double D; T w, wa; };
+template <> struct __align__(16) OPix<float> { double D; float w, wa; };
+
+typedef const __attribute__((address_space(4))) DmatArgs* DArgs;
+// The kernel's arguments, read again where they are used: kept, they and what is
+// derived from them spilled 300 scalar registers into vector lanes.
+__device__ __forceinline__ DArgs dargs() {
+  DArgs p = (DArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// Barrier of the workgroup's waves, its LDS operations complete: the wait is written
+// out because the compiler left it out before the barrier of the row loop, and rows
+// were then lost now and then.  One wave needs neither (its LDS operations are in
+// order).
+template <int NW>
+__device__ __forceinline__ void sync() {
+  if constexpr (NW > 1) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
+// Bit n of a uniform mask, as one scalar test and branch where it is used (the
+// compiler would fold neighbouring tests into masks and vector selects).
+__device__ __forceinline__ bool bit_of(uint32_t& m, int n) {
+  asm volatile("" : "+s"(m));
+  return (m >> n) & 1u;
+}
+
 // Uniform pair data.
 struct WPair {
   int64_t pf, pg;
@@ -209,8 +251,10 @@ struct WPair {
   double fdmin, fdmax, gdmin, gdmax;
 };
 
-template <typename T, int NB, int PMAX, int WPE, bool ZLO, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void dmat_wave_kernel(DmatArgs a) {
+// COUNT: with the statistics of options.counters (a launch of its own: the counting
+// took scalar registers from every other launch).
+template <typename T, int NB, int PMAX, int WPE, bool ZLO, int NW, bool COUNT>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void dmat_wave_kernel(DmatArgs) {
   static_assert(NW == 1 || NW == 2, "one or two waves per workgroup");
   using Form = WForm<T>;
   using Acc = typename Form::Acc;
@@ -218,42 +262,52 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
   constexpr bool kF32 = sizeof(T) == 4;
   constexpr int MB = NB * (NB + 1) / 2;  // accumulator blocks
   constexpr int MBW = NW == 1 ? MB : wrow_base(NB);  // accumulator slots of one wave
-  constexpr int NBUF = NW == 1 ? 2 : 3;    // row-histogram buffers
-  constexpr int NH = 2 / NW;               // rows of a step binned by one wave
+  constexpr int SUB = NW;                  // MFMA steps (of two rows) per turn of the row loop
+  constexpr int ROWS = 2 * SUB;            // rows of a turn
+  constexpr int NH = ROWS / NW;            // rows of a turn binned by one wave: wv, wv + NW, ...
   constexpr bool kTrim = NW == 2 || !kF32;  // per-pass pixel ranges (below)
   constexpr bool kReuse = kTrim && NB >= 7;  // pair histograms kept across passes (below)
   constexpr int NX = NB / 2, NY = NB - NX;  // rectangle passes: NX x NY blocks
   constexpr int SB = NB;                 // storage blocks per row and component
   constexpr int SW = 16 * SB + 16;       // storage stride (padded against bank conflicts)
   static_assert(NX + NY == SB, "a rectangle pass stores its x and y ranges side by side");
-  constexpr int CH = 64 * PMAX;          // other-forest pixels held in registers at a time
-  constexpr int GB = 4;                  // tile blocks staged per flush group
+  constexpr int CH = 64 * PMAX;          // other-forest pixels staged at a time
+  constexpr int GB = NW == 1 ? 4 : 2;    // tile blocks staged per flush group
   // row histograms in FP64 in both forms: on gfx950 an LDS FP64 atomic add
   // runs ~24x faster than an FP32 one (measured by lya_measure_peaks)
-  __shared__ double buf[NBUF][4][SW];    // [buffer][2 row + l][storage bin]
+  __shared__ __align__(16) double buf[2][2 * ROWS][SW];  // [buffer][2 row + l][storage bin]
+  __shared__ OPix<T> opix[NW == 1 ? 1 : CH];  // two waves: the other forest's pixels
   __shared__ T stg[NW][GB * 256];        // flush stage of each wave: GB blocks of 16 x 16
-  __shared__ uint32_t smask[3][NW];      // two waves: block mask of each wave's row, per buffer
+  __shared__ uint32_t smask[2][NW];      // two waves: block mask of each wave's rows, per buffer
   __shared__ int64_t s_item;             // two waves: the work item
   __shared__ uint8_t slot_by[MBW];       // block column of each accumulator slot
   __shared__ uint8_t slot_t[MBW];        // two waves: the slot's row position t (block row 2 t + wave)
   __shared__ double wdacc[16 * NB];      // w_A of the run (diagonal passes)
   __shared__ int32_t otab[16 * SB];      // output bin of each storage bin of the pass (-1 past the window)
   constexpr int RCH = 128;               // rows of a sweep staged at a time
-  __shared__ T srow[3][RCH];             // d, w, w a of the staged rows
-  __shared__ double srowD[RCH];          // FP64 distance of the staged rows (edge guard)
+  __shared__ T srow[2][RCH];             // w, w a of the staged rows
+  __shared__ double srowD[RCH];          // their distances
 
   const int lane = NW == 1 ? (int)threadIdx.x : (int)(threadIdx.x & 63);
   const int wv = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lk = lane >> 4, lm = lane & 15;
   const int rpar = lk >> 1, comp = lk & 1;  // operand slot of this lane: row of the step, l
 
-  BinK<T, ZLO> K;
-  K.init(a.g, a.glob, a.edges_par, a.edges_perp);
-  const int NP = K.NP, NT = K.NT, nb = NP * NT;
-  const Rec* __restrict__ recs;
-  if constexpr (kF32) recs = a.drec32; else recs = a.drec64;
+  // bin coordinates 2^20 + x + guard (upper word: the bin, lower: the fraction)
+  const int NP = dargs()->g.n_par;
+  const double mp = uniform(kMagic + kGuard - dargs()->g.e0_par * dargs()->g.inv_par);
+  const double mt = uniform(kMagic + kGuard - dargs()->g.e0_perp * dargs()->g.inv_perp);
+  const double uphi = uniform(kMagic + NP + 2.0 * kGuard), uthi = uniform(kMagic + dargs()->g.n_perp + 2.0 * kGuard);
+  const uint32_t thr = dargs()->g.exact_all ? 0xffffffffu : kGuard2;
+  const uint32_t G = (kMagicHi & 0xffffffu) * (uint32_t)NP + kMagicHi;  // what the upper words add to k_perp NP + k_par
+  auto records = []() __attribute__((always_inline)) {
+    if constexpr (kF32) return dargs()->drec32; else return dargs()->drec64;
+  };
+  auto distance = [](const Rec& r) __attribute__((always_inline)) -> double {
+    if constexpr (kF32) return r.D; else return r.d;
+  };
 
-  for (int e = threadIdx.x; e < NBUF * 4 * SW; e += 64 * NW) (&buf[0][0][0])[e] = 0.0;
+  for (int e = threadIdx.x; e < 2 * 2 * ROWS * SW; e += 64 * NW) (&buf[0][0][0])[e] = 0.0;
   for (int e = threadIdx.x; e < 16 * NB; e += 64 * NW) wdacc[e] = 0.0;
   for (int j = threadIdx.x; j < MBW; j += 64 * NW) {
     if constexpr (NW == 1) {
@@ -281,58 +335,65 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
   // pair costs one scalar bit test: a rectangle pass keeps the pairs with
   // bx < NX <= by, a diagonal pass every bx <= by
   // With two waves, each issues the steps of its own blocks, (2 t + wv, by).
-  auto tile_steps = [&](uint32_t u, bool diag, int ymin, const T* A, const T* B) __attribute__((always_inline)) {
+  auto tile_steps = [&](uint32_t u, bool diag, int ymin, const T (&op)[SUB][SB]) __attribute__((always_inline)) {
     constexpr uint32_t kXMask = (1u << NX) - 1u;
-    const uint32_t ux = diag ? u : (u & kXMask), uy = diag ? (u & ~((1u << ymin) - 1u)) : (u & ~kXMask);
+    uint32_t ux = diag ? u : (u & kXMask), uy = diag ? (u & ~((1u << ymin) - 1u)) : (u & ~kXMask);
     if constexpr (NW == 1) {
       static_for<0, NB>([&](auto BY) __attribute__((always_inline)) {
         constexpr int by = decltype(BY)::value;
-        if (!((uy >> by) & 1u)) return;
+        if (!bit_of(uy, by)) return;
         static_for<0, by + 1>([&](auto BX) __attribute__((always_inline)) {
           constexpr int bx = decltype(BX)::value;
           constexpr int j = by * (by + 1) / 2 + bx;
-          if ((ux >> bx) & 1u) acc[j] = Form::step(A[bx], B[by], acc[j]);
+          if (bit_of(ux, bx)) {
+#pragma unroll
+            for (int u2 = 0; u2 < SUB; ++u2) acc[j] = Form::step(op[u2][bx], op[u2][by], acc[j]);
+          }
         });
       });
     } else {
-      const uint32_t uxw = ux >> wv;  // bit 2 t: block 2 t + wv
-      T Aw[(NB + 1) / 2];
-#pragma unroll
-      for (int t = 0; t < (NB + 1) / 2; ++t) Aw[t] = (2 * t + 1 < NB && wv) ? A[2 * t + 1] : A[2 * t];
+      uint32_t uxw = ux >> wv;  // bit 2 t: block 2 t + wv
+      // wave 1 has no block (by, by) of an even row
+      uint32_t uxd = wv == 0 ? uxw : 0u;
       static_for<0, NB>([&](auto BY) __attribute__((always_inline)) {
         constexpr int by = decltype(BY)::value;
-        if (!((uy >> by) & 1u)) return;
+        if (!bit_of(uy, by)) return;
         static_for<0, by / 2 + 1>([&](auto TT) __attribute__((always_inline)) {
           constexpr int t = decltype(TT)::value;
           constexpr int sl = wrow_base(by) + t;
-          const bool on = (2 * t == by) ? (wv == 0 && (uxw >> (2 * t)) & 1u) : ((uxw >> (2 * t)) & 1u);
-          if (on) acc[sl] = Form::step(Aw[t], B[by], acc[sl]);
+          if (bit_of(2 * t == by ? uxd : uxw, 2 * t)) {
+#pragma unroll
+            for (int u2 = 0; u2 < SUB; ++u2)
+              acc[sl] = Form::step((2 * t + 1 < NB && wv) ? op[u2][2 * t + 1] : op[u2][2 * t], op[u2][by], acc[sl]);
+          }
         });
       });
     }
   };
 
   for (;;) {
-    __syncthreads();
+    sync<NW>();
     int64_t it;
+    const DArgs a = dargs();
     if constexpr (NW == 1) {
       unsigned itv = 0;
-      if (lane == 0) itv = atomicAdd(a.counter, 1u);
+      if (lane == 0) itv = atomicAdd(a->counter, 1u);
       it = (int64_t)(unsigned)__builtin_amdgcn_readlane((int)itv, 0);
     } else {
-      if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(a.counter, 1u);
-      __syncthreads();
+      if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(a->counter, 1u);
+      sync<NW>();
       it = s_item;
     }
-    if (it >= a.n_items) break;
-    const int64_t k0 = it * a.item_stride * a.chunk;
-    const int64_t k1 = min(a.n_pairs, k0 + (int64_t)a.chunk);
+    if (it >= a->n_items) break;
+    const int64_t k0 = it * a->item_stride * a->chunk;
+    const int64_t k1 = min(a->n_pairs, k0 + (int64_t)a->chunk);
     for (int64_t r0 = k0; r0 < k1;) {
-      const uint64_t key = a.wkeys[r0];
+      const DArgs a = dargs();
+      const uint64_t key = a->wkeys[r0];
       int64_t lo = r0 + 1, hi = k1;  // end of the run of equal keys
       while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
-        if (a.wkeys[mid] == key) lo = mid + 1; else hi = mid;
+        if (a->wkeys[mid] == key) lo = mid + 1; else hi = mid;
       }
       int64_t r1 = lo;
       if (key == ~0ull) {
@@ -345,7 +406,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
       const int nwin = span * NP;
       const int base_L = kt0 * NP;
       const int nblk = (nwin + 15) >> 4;
-      const int64_t obase = (int64_t)real * nb;
       const int npass = count_passes<NB, NX, NY>(nblk);
       // Windows of two segments (three or more passes) keep each pair's
       // histograms H between passes: the first diagonal pass stores H over the
@@ -353,31 +413,39 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
       // passes read them, so that they need only the f rows whose own outer
       // products reach their blocks.  The store holds hsave_run pairs per wave,
       // so a run is cut into pieces of at most that many (each its own tile).
-      const bool reuse = kReuse && a.hsave != nullptr && nblk > NB && nblk <= 2 * NB;
-      if (reuse) r1 = min(r1, r0 + (int64_t)a.hsave_run);
+      const bool reuse = kReuse && a->hsave != nullptr && nblk > NB && nblk <= 2 * NB;
+      if (reuse) r1 = min(r1, r0 + (int64_t)a->hsave_run);
       T* const hsbase =
-          reuse ? (T*)a.hsave + ((int64_t)blockIdx.x * NW + wv) * a.hsave_run * (int64_t)(2 * NB * 64) + lane
+          reuse ? (T*)a->hsave + ((int64_t)blockIdx.x * NW + wv) * a->hsave_run * (int64_t)(2 * NB * 64) + lane
                 : nullptr;
 
       for (int ps = 0; ps < npass; ++ps) {
         const WPass P = pass_of<NB, NX, NY>(ps, nblk);
-        __syncthreads();  // the previous pass's flush has read the table
+        sync<NW>();  // the previous pass's flush has read the table
         for (int e = threadIdx.x; e < 16 * SB; e += 64 * NW) {
           const int sb = e >> 4;
           const bool ypart = !P.diag && sb >= NX;
           const int wb = ypart ? P.y0 + (sb - NX) : P.x0 + sb;
           const int w = 16 * wb + (e & 15);
           const bool used = ypart ? sb - NX < P.ny : sb < P.nx;
-          otab[e] = (used && w < nwin) ? out_index(w + base_L, NP, NT) : -1;
+          otab[e] = (used && w < nwin) ? out_index(w + base_L, NP, dargs()->g.n_perp) : -1;
         }
+        // storage bin of L = k_perp NP + k_par + G: L - cx below nx_bins (x range),
+        // else 16 NX + L - cy below ny_bins (y range of a rectangle pass)
+        const uint32_t cx = G + (uint32_t)(base_L + 16 * P.x0), cy = G + (uint32_t)(base_L + 16 * P.y0);
+        const uint32_t nx_bins = (uint32_t)max(0, min(16 * P.nx, nwin - 16 * P.x0));
+        const uint32_t ny_bins = P.diag ? 0u : (uint32_t)max(0, min(16 * P.ny, nwin - 16 * P.y0));
 
         for (int64_t kk = r0; kk < r1; ++kk) {
-          const int q = a.worder[kk];
+          const DArgs a = dargs();
+          const int q = a->worder[kk];
           WPair pr;
           {
-            const ForestInfo fi = a.finfo[a.sorted[a.pair_p[q]]];
-            const ForestInfo gi = a.finfo[a.sorted[a.nbr[q]]];
+            const ForestInfo fi = a->finfo[a->sorted[a->pair_p[q]]];
+            const ForestInfo gi = a->finfo[a->sorted[a->nbr[q]]];
             pair_sc(fi, gi, pr.s, pr.c);
+            pr.s = uniform(pr.s);
+            pr.c = uniform(pr.c);
             pr.pf = fi.pix0;
             pr.pg = gi.pix0;
             pr.nf = fi.npix;
@@ -389,7 +457,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
           }
           // pixels within r_par reach of the other forest's extent: the first and
           // last such pixel of each forest bound the rows and the lanes' pixels
-          const double reach = a.g.emax_par / pr.c * (1.0 + 1e-12) + 1e-9;
+          const double reach = a->g.emax_par / pr.c * (1.0 + 1e-12) + 1e-9;
           // A window of several passes (two-wave FP32 kernel, FP64 kernels; in the
           // one-wave FP32 kernels the extra registers spilled): pixels are kept
           // only where they can reach the pass's blocks.  A pixel at distance D
@@ -409,9 +477,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
           const bool frows = reuse && ps > 0;
           double ulo[2] = {-INFINITY, -INFINITY}, uhi[2] = {INFINITY, INFINITY};
           double rlo[2] = {-INFINITY, -INFINITY}, rhi[2] = {INFINITY, INFINITY};
-          if (kTrim && npass > 1 && !(a.counters && ps == 0) && pr.s > 0.0) {
-            auto edge_lo = [&](int B) { return K.et[kt0 + min(span - 1, (16 * B) / NP)]; };
-            auto edge_hi = [&](int B) { return K.et[kt0 + min(span - 1, (16 * B + 15) / NP) + 1]; };
+          if (kTrim && npass > 1 && !(COUNT && ps == 0) && pr.s > 0.0) {
+            auto edge_lo = [&](int B) { return a->edges_perp[kt0 + min(span - 1, (16 * B) / NP)]; };
+            auto edge_hi = [&](int B) { return a->edges_perp[kt0 + min(span - 1, (16 * B + 15) / NP) + 1]; };
             const int u1 = P.diag ? P.x0 + P.nx - 1 : P.y0 + P.ny - 1;
             const double el = edge_lo(P.x0) * (1.0 - 1e-9) / pr.s, eh = edge_hi(u1) * (1.0 + 1e-9) / pr.s;
             ulo[0] = el - pr.gdmax - 1e-6;  // f against g
@@ -439,8 +507,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
               const int e = e0 + lane;
               bool in = false, inr = false;
               if (e < n) {
-                double D;
-                if constexpr (kF32) D = recs[p0 + e].D; else D = recs[p0 + e].d;
+                const double D = distance(records()[p0 + e]);
                 in = D > lo_u && D < hi_u;
                 inr = D > lo_r && D < hi_r;
               }
@@ -472,16 +539,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
           if (none && !(reuse && ps < 2)) continue;
           T cf0, cf1, cg0, cg1;  // c of f and g: (1 / W, 1 / S), 0 where the term is off
           {
-            const EtaInfo ef = a.einfo[a.sorted[a.pair_p[q]]];
-            const EtaInfo eg = a.einfo[a.sorted[a.nbr[q]]];
+            const EtaInfo ef = a->einfo[a->sorted[a->pair_p[q]]];
+            const EtaInfo eg = a->einfo[a->sorted[a->nbr[q]]];
             cf0 = (T)(ef.active ? 1.0 / ef.W : 0.0);
             cf1 = (T)(ef.slope ? 1.0 / ef.S : 0.0);
             cg0 = (T)(eg.active ? 1.0 / eg.W : 0.0);
             cg1 = (T)(eg.slope ? 1.0 / eg.S : 0.0);
           }
-          const T s = (T)pr.s, c = (T)pr.c;
-          const T bsep = kF32 ? (T)(2.0 * a.glob->dc * pr.s) : (T)0;
-          const bool count_in = a.counters && ps == 0;
+          const double cp = pr.c * a->g.inv_par, st_ = pr.s * a->g.inv_perp;
+          const bool count_in = COUNT && ps == 0;
 
           // the two sweeps: rows of f against g's pixels (rs = 0, which also sums
           // the pair histograms H), then rows of g against f's pixels
@@ -495,272 +561,273 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
             const int64_t poth0 = rs ? pr.pf + f_lo : pr.pg + g_lo;
             const T co_l = comp ? (rs ? cf1 : cg1) : (rs ? cf0 : cg0);  // c of the other forest, this lane's l
             const int nch = (no + CH - 1) / CH;
-            // the other forest's pixels, CH at a time, in registers: lane l holds
-            // pixels c0 + l ppl + k, k < ppl <= PMAX (blocked, so that the 64 pixels
-            // of one k are spread over the forest and mostly fall in different bins)
-            T od[PMAX], ow[PMAX], owa[PMAX];
-            int ppl = 0, cn = 0, cload = -1;
+            // the other forest's pixels, CH at a time, in registers (one wave) or LDS (two):
+            // lane l takes pixels c0 + l ppl + k, k < ppl <= PMAX (blocked, so that the 64
+            // pixels of one k are spread over the forest and mostly fall in different bins)
+            OPix<T> mine[NW == 1 ? PMAX : 1];
+            int ppl = 0, cload = -1;
             auto load_other = [&](int c0) {
               if (c0 == cload) return;
               cload = c0;
-              cn = min(CH, no - c0);
+              const int cn = min(CH, no - c0);
               ppl = (cn + 63) >> 6;
-#pragma unroll
-              for (int k = 0; k < PMAX; ++k) {
-                const int j = lane * ppl + k;
-                od[k] = (T)1e30;  // far away: never in the grid
-                ow[k] = owa[k] = (T)0;
-                if (k < ppl && j < cn) {
-                  const Rec rec = recs[poth0 + c0 + j];
-                  od[k] = rec.d;
-                  ow[k] = rec.w;
-                  owa[k] = rec.w * rec.a;
+              auto pixel = [&](int j) __attribute__((always_inline)) -> OPix<T> {
+                OPix<T> o{1e30, (T)0, (T)0};  // past the last: far away, never in the grid
+                if (j < cn) {
+                  const Rec rec = records()[poth0 + c0 + j];
+                  o = OPix<T>{distance(rec), rec.w, rec.w * rec.a};
                 }
+                return o;
+              };
+              if constexpr (NW == 1) {
+#pragma unroll
+                for (int k = 0; k < PMAX; ++k) mine[k] = pixel(k < ppl ? lane * ppl + k : cn);
+                return;
               }
+              sync<NW>();  // the pixels before have been read
+              for (int j = threadIdx.x; j < 64 * ppl; j += 64 * NW) {
+                opix[j] = pixel(j);
+              }
+              sync<NW>();
             };
             // the rows, RCH at a time, staged in LDS from rbase on (rows past nr as zeros)
             int rbase = -RCH;
-            auto rows_at = [&](int r) {
+            auto rows_at = [&](int r) -> bool {  // true: staged now
               const int cb = r & ~(RCH - 1);
-              if (cb == rbase) return;
+              if (cb == rbase) return false;
               rbase = cb;
-              __syncthreads();
+              sync<NW>();
               for (int i = threadIdx.x; i < RCH; i += 64 * NW) {
                 const int rr = cb + i;
-                T d = 0, w = 0, wa = 0;
+                T w = 0, wa = 0;
                 double D = 0.0;
                 if (rr < nr) {
-                  const Rec rec = recs[prow0 + rr];
-                  d = rec.d;
+                  const Rec rec = records()[prow0 + rr];
                   w = rec.w;
                   wa = rec.w * rec.a;
-                  if constexpr (kF32) D = rec.D; else D = rec.d;
+                  D = distance(rec);
                 }
-                srow[0][i] = d;
-                srow[1][i] = w;
-                srow[2][i] = wa;
+                srow[0][i] = w;
+                srow[1][i] = wa;
                 srowD[i] = D;
               }
-              __syncthreads();
+              sync<NW>();
+              return true;
             };
-            // bins rows r and r + 1 into buffer bsel (w and w a added at each pair's
-            // storage bin); returns the union of their block masks (uniform).  The
-            // 2 x NK evaluations of a chunk run in three phases -- the FP32 bins,
-            // then the FP64 edge path where some lane needs it (a uniform branch),
-            // then the storage bins and the LDS adds -- so that the independent
-            // evaluations interleave instead of waiting on one another.
-            auto bin_chunk = [&](auto NKC, int c0, int r, int bsel, const T* rdv, bool row1ok)
-                __attribute__((always_inline)) -> uint32_t {
+            // bins this wave's rows of the turn from row r into buffer bsel (w and w a
+            // added at each pair's storage bin) against pixels k0 ... of each lane;
+            // returns the blocks the lane reached.  The NH x NKE evaluations run in
+            // three phases -- the bins, then the edge path where some lane needs it (a
+            // uniform branch), then the storage bins and the LDS adds -- so that the
+            // independent evaluations interleave instead of waiting on one another.
+            auto bin_chunk = [&](auto NKC, int k0, int r, int bsel, const double* rdv) __attribute__((always_inline))
+                -> uint32_t {
               constexpr int NKE = decltype(NKC)::value;
-              int L[NH][NKE];
-              bool inr[NH][NKE], need[NH][NKE];
-              bool anyneed = false;
+              uint32_t L[NH][NKE], low = 0xffffffffu;
+              uint64_t in[NH][NKE];
+              double od[NKE];
+              T ow[NKE], owa[NKE];
+#pragma unroll
+              for (int k = 0; k < NKE; ++k) {
+                const OPix<T> o = NW == 1 ? mine[NW == 1 ? k : 0] : opix[lane * ppl + k0 + k];
+                od[k] = o.D;
+                ow[k] = o.w;
+                owa[k] = o.wa;
+              }
 #pragma unroll
               for (int hi = 0; hi < NH; ++hi) {
-                const int h = NW == 1 ? hi : wv;  // row r + h
+                const uint64_t row = r + wv + NW * hi < nr ? ~0ull : 0ull;
 #pragma unroll
                 for (int k = 0; k < NKE; ++k) {
-                  T rp, rt;
-                  separations(rdv[hi], od[k], c, s, bsep, rp, rt);
-                  T xp, xt;
-                  if constexpr (ZLO) {
-                    xp = rp * K.invp;
-                    xt = rt * K.invt;
-                  } else {
-                    xp = (rp - K.e0p) * K.invp;
-                    xt = (rt - K.e0t) * K.invt;
-                  }
-                  const bool in = (h == 0 || row1ok) & (xp < K.np_hi) & (xt < K.nt_hi) &
-                                  (ZLO || ((xp > K.lo_p) & (xt > K.lo_t)));
-                  const T rxp = rint(xp), rxt = rint(xt);
-                  bool gp = fabs(xp - rxp) < K.taup, gt = fabs(xt - rxt) < K.taut;
-                  if constexpr (ZLO) {
-                    gp &= rxp != (T)0;
-                  } else {
-                    gp &= !(K.zlp & (rxp == (T)0));
-                    gt &= !(K.zlt & (rxt == (T)0));
-                  }
-                  // (clamped before the conversion: out-of-range lanes are discarded below)
-                  L[hi][k] = (int)__umul24((unsigned)(int)fmin(xt, (T)65536), (unsigned)NP) + (int)fmin(xp, (T)65536);
-                  inr[hi][k] = in;
-                  need[hi][k] = in & (gp | gt);
-                  anyneed |= need[hi][k];
+                  const double up = fma(fabs(rdv[hi] - od[k]), cp, mp), ut = fma(rdv[hi] + od[k], st_, mt);
+                  in[hi][k] = row & ballot(up < uphi) & ballot(ut < uthi);
+                  if constexpr (!ZLO) in[hi][k] &= ballot(up >= kMagic) & ballot(ut >= kMagic);
+                  const uint32_t hp = (uint32_t)__double2hiint(up);
+                  L[hi][k] = __umul24((uint32_t)__double2hiint(ut), (unsigned)NP) + hp;
+                  uint32_t lop = (uint32_t)__double2loint(up);
+                  // r_par = 0 (aligned pixel grids, every row) needs no guard at a zero lower edge
+                  if constexpr (ZLO) lop = max(lop, (hp - (kMagicHi + 1u)) >> 16);
+                  low = min(low, min(lop, (uint32_t)__double2loint(ut)));
                 }
               }
-              if (__ballot(anyneed)) {
-                // within rounding of an edge: the FP64 separations against the edges
+              if (ballot(low <= thr)) {
+                // some pair may be within the guard of an edge: its separations
+                // against the edges
+                const DArgs a = dargs();
 #pragma unroll
                 for (int hi = 0; hi < NH; ++hi) {
-                  const int h = NW == 1 ? hi : wv;  // row r + h
+                  double D2 = rdv[hi];
+                  asm volatile("" : "+v"(D2));  // computed again, not kept
 #pragma unroll
                   for (int k = 0; k < NKE; ++k) {
-                    if (need[hi][k]) {
-                      double rp64, rt64;
-                      if constexpr (kF32) {
-                        separations64(srowD[r + h - rbase], recs[poth0 + c0 + lane * ppl + k].D, pr.c, pr.s,
-                                      rp64, rt64);
-                      } else {
-                        separations(rdv[hi], od[k], c, s, bsep, rp64, rt64);
+                    const double up = fma(fabs(D2 - od[k]), cp, mp), ut = fma(D2 + od[k], st_, mt);
+                    const uint32_t hp = (uint32_t)__double2hiint(up), ht = (uint32_t)__double2hiint(ut);
+                    uint64_t m = ballot((uint32_t)__double2loint(up) <= thr);
+                    if (a->g.zero_lo_par && !a->g.exact_all) m &= ballot(hp != kMagicHi);
+                    m = in[hi][k] & (m | ballot((uint32_t)__double2loint(ut) <= thr));
+                    if (m) {
+                      bool out = false;
+                      if (lane_in(m)) {
+                        double rp64, rt64;
+                        separations64(D2, od[k], pr.c, pr.s, rp64, rt64);
+                        const int kp = bin_exact(rp64, a->edges_par, NP, (int)(hp - kMagicHi));
+                        const int kt = bin_exact(rt64, a->edges_perp, a->g.n_perp, (int)(ht - kMagicHi));
+                        L[hi][k] = G + (uint32_t)(kt * NP + kp);
+                        out = kp < 0 || kt < 0;
                       }
-                      const int kp = bin_exact(rp64, K.ep, NP, (int)floor((rp64 - a.g.e0_par) * a.g.inv_par));
-                      const int kt = bin_exact(rt64, K.et, NT, (int)floor((rt64 - a.g.e0_perp) * a.g.inv_perp));
-                      L[hi][k] = (kp >= 0 && kt >= 0) ? (int)__umul24((unsigned)kt, (unsigned)NP) + kp : -1;
+                      in[hi][k] &= ~ballot(out);
                     }
                   }
                 }
               }
-              uint32_t bits = 0;
-              int sidx[NH][NKE];
-              bool ok[NH][NKE];
+              if constexpr (COUNT) {
 #pragma unroll
-              for (int hi = 0; hi < NH; ++hi) {
+                for (int hi = 0; hi < NH; ++hi)
 #pragma unroll
-                for (int k = 0; k < NKE; ++k) {
-                  const int w = L[hi][k] - base_L;
-                  const bool ing = inr[hi][k] & (L[hi][k] >= 0);
-                  const bool inw = ing & ((unsigned)w < (unsigned)nwin);
-                  if (a.counters) {  // statistics only (uniform)
+                  for (int k = 0; k < NKE; ++k) {
+                    const bool ing = lane_in(in[hi][k]), inw = ing & (L[hi][k] - G - (uint32_t)base_L < (uint32_t)nwin);
                     n_lost += (ing & !inw) ? 1ull : 0ull;
                     if (count_in && rs == 0) n_in += inw ? 1ull : 0ull;
                   }
-                  // storage bin of the pass
-                  const int wx = w - 16 * P.x0, wy = w - 16 * P.y0;
-                  const bool okx = (unsigned)wx < (unsigned)(16 * P.nx);
-                  const bool oky = !P.diag & ((unsigned)wy < (unsigned)(16 * P.ny));
-                  sidx[hi][k] = okx ? wx : 16 * NX + wy;
-                  ok[hi][k] = inw & (okx | oky);
-                  bits |= ok[hi][k] ? (1u << ((sidx[hi][k] >> 4) & 31)) : 0u;
-                }
               }
+              uint32_t bits = 0;
 #pragma unroll
               for (int hi = 0; hi < NH; ++hi) {
-                const int h = NW == 1 ? hi : wv;  // row r + h
-                double* hw = &buf[bsel][2 * h][0];
+                double* hw = &buf[bsel][2 * (wv + NW * hi)][0];
 #pragma unroll
                 for (int k = 0; k < NKE; ++k) {
-                  if (ok[hi][k]) {
-                    atomicAdd(&hw[sidx[hi][k]], (double)ow[k]);
-                    atomicAdd(&hw[SW + sidx[hi][k]], (double)owa[k]);
+                  const uint32_t wx = L[hi][k] - cx, wy = L[hi][k] - cy;
+                  const bool okx = wx < nx_bins;
+                  const uint32_t sidx = okx ? wx : wy + 16u * NX;
+                  if (lane_in(in[hi][k] & (ballot(okx) | ballot(wy < ny_bins)))) {
+                    bits |= 1u << (sidx >> 4);
+                    atomicAdd(&hw[sidx], (double)ow[k]);
+                    atomicAdd(&hw[SW + sidx], (double)owa[k]);
                   }
                 }
               }
               return bits;
             };
-            // with two waves, wave h bins row r + h; the block masks of the two
-            // rows are combined through LDS after the next barrier
-            auto bin_rows = [&](int r, int bsel) -> uint32_t {
+            // bins this wave's rows, from row r on, into buffer bsel.  Two waves clear
+            // their rows there first (one wave cleared them when it read them), and their
+            // block masks are combined through LDS after the next barrier
+            auto bin_rows = [&](int r, int bsel, double* rdv) -> uint32_t {
               uint32_t bits = 0;
-              rows_at(r);
-              T rdv[NH];
-              if constexpr (NW == 1) {
-                rdv[0] = srow[0][r - rbase];
-                rdv[1] = srow[0][r + 1 - rbase];
-              } else {
-                rdv[0] = srow[0][r + wv - rbase];
+              if (rows_at(r)) {
+#pragma unroll
+                for (int h = 0; h < NH; ++h) rdv[h] = srowD[r + wv + NW * h - rbase];
               }
-              const bool row1ok = r + 1 < nr;
+#pragma unroll
+              for (int h = 0; NW > 1 && h < NH; ++h) {
+                double2* const clr = (double2*)&buf[bsel][2 * (wv + NW * h)][0];
+#pragma unroll
+                for (int e = 0; e < SW; e += 64)
+                  if (e + 64 <= SW || lane < SW - e) clr[e + lane] = double2{0.0, 0.0};
+              }
 #pragma unroll 1
               for (int c0 = 0; c0 < no; c0 += CH) {
                 load_other(c0);
-                // slots k >= ppl hold far-away pixels (never in the grid)
-                if (ppl <= 2) bits |= bin_chunk(std::integral_constant<int, 2 < PMAX ? 2 : PMAX>{}, c0, r, bsel, rdv, row1ok);
-                else bits |= bin_chunk(std::integral_constant<int, PMAX>{}, c0, r, bsel, rdv, row1ok);
+                if constexpr (NW == 1) {
+                  if (ppl <= 2) bits |= bin_chunk(std::integral_constant<int, 2 < PMAX ? 2 : PMAX>{}, 0, r, bsel, rdv);
+                  else bits |= bin_chunk(std::integral_constant<int, PMAX>{}, 0, r, bsel, rdv);
+                  continue;
+                }
+                int k = 0;
+#pragma unroll 1
+                for (; k + 2 <= ppl; k += 2) bits |= bin_chunk(std::integral_constant<int, 2>{}, k, r, bsel, rdv);
+                if (k < ppl) bits |= bin_chunk(std::integral_constant<int, 1>{}, k, r, bsel, rdv);
               }
               return wave_or(bits);
             };
 
-            // steps of two rows; the binning of step st + 1 is issued before the
-            // matrix steps of step st, into the next buffer.  One wave reads and
-            // clears its buffer in one step (two buffers); with two waves, a buffer
-            // read in step st is cleared in step st + 1, after the barrier that
-            // follows both waves' reads, so three buffers rotate.
-            const int nsteps = (nr + 1) >> 1;
+            // turns of SUB steps of two rows; the binning of the next turn's rows is
+            // issued before the matrix steps of this one, into the other buffer: a wave
+            // clears and bins rows that every wave read in the turn before, on the far
+            // side of the barrier.  (Two steps per turn with two waves: half the
+            // barriers, masks and block tests.)
+            const int nturns = (nr + ROWS - 1) / ROWS;
             uint32_t ucur = 0;
 #pragma unroll 1
-            for (int st = -1; st < nsteps; ++st) {
-              T op[SB];
-              T wr = 0, wra = 0;
+            for (int st = -1; st < nturns; ++st) {
+              const int bcur = st & 1, bnext = bcur ^ 1;
+              double rdv[NH];
+#pragma unroll
+              for (int h = 0; h < NH; ++h) rdv[h] = 0.0;
+              T op[SUB][SB];
+              T wr[SUB], wra[SUB];
               if (st >= 0) {
-                __syncthreads();  // the rows' LDS adds (and the last clears) are complete
-                const int bsel = NW == 1 ? (st & 1) : st % 3;
-                if constexpr (NW == 2) ucur = (uint32_t)__builtin_amdgcn_readfirstlane((int)(smask[bsel][0] | smask[bsel][1]));
-                // this lane's row (rows past nr were staged as zeros)
-                wr = srow[1][2 * st + rpar - rbase];
-                wra = srow[2][2 * st + rpar - rbase];
-                // operands: R^l of the lane's row over every block slot (slots the
-                // step does not reach hold zeros), read without branches so the
-                // reads overlap; the slots are cleared for the next use of this buffer
-                double ov[SB];
+                sync<NW>();  // the rows' LDS adds are complete
+                if constexpr (NW == 2) ucur = (uint32_t)__builtin_amdgcn_readfirstlane((int)(smask[bcur][0] | smask[bcur][1]));
+                // operands: R^l of the lane's rows over every block slot (slots the
+                // turn does not reach hold zeros), read without branches so the reads
+                // overlap; rows past nr were staged with zero weights
 #pragma unroll
-                for (int b = 0; b < SB; ++b) ov[b] = buf[bsel][lk][16 * b + lm];
-                if constexpr (NW == 1) {
+                for (int u2 = 0; u2 < SUB; ++u2) {
+                  wr[u2] = srow[0][ROWS * st + 2 * u2 + rpar - rbase];
+                  wra[u2] = srow[1][ROWS * st + 2 * u2 + rpar - rbase];
+                  double ov[SB];
 #pragma unroll
-                  for (int b = 0; b < SB; ++b) {
-                    op[b] = (T)ov[b];
-                    buf[bsel][lk][16 * b + lm] = 0.0;
+                  for (int b = 0; b < SB; ++b) ov[b] = buf[bcur][4 * u2 + lk][16 * b + lm];
+                  if (u2 == 0) {
+                    // the distances of the next rows, with the same wait
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) rdv[h] = srowD[(ROWS * (st + 1) + wv + NW * h) & (RCH - 1)];
                   }
-                } else {
-                  const int bclr = (st + 2) % 3;  // read by both waves in step st - 1
 #pragma unroll
                   for (int b = 0; b < SB; ++b) {
-                    op[b] = (T)ov[b];
-                    if ((b & 1) == wv) buf[bclr][lk][16 * b + lm] = 0.0;
+                    op[u2][b] = (T)ov[b];
+                    if constexpr (NW == 1) buf[bcur][lk][16 * b + lm] = 0.0;
                   }
                 }
               }
-              const uint32_t unext =
-                  st + 1 < nsteps ? bin_rows(2 * st + 2, NW == 1 ? ((st + 1) & 1) : (st + 1) % 3) : 0u;
+              const uint32_t unext = st + 1 < nturns ? bin_rows(ROWS * (st + 1), bnext, rdv) : 0u;
               if constexpr (NW == 2) {
-                if (lane == 0) smask[(st + 1) % 3][wv] = unext;
+                if (lane == 0) smask[bnext][wv] = unext;
               }
               if (st >= 0) {
-                if (a.counters && wv == 0) {
+                if (COUNT && wv == 0) {
                   // outer-product FMAs of the sparse rows: 2 per (x, y) of nonzero R bins,
                   // counted per row over the x and y ranges
                   // (a diagonal pass with ymin > 0 counts the pairs reaching block ymin:
                   // all of its pairs less those below it)
-                  int cx[2] = {0, 0}, cy[2] = {0, 0}, cl[2] = {0, 0};
 #pragma unroll
-                  for (int b = 0; b < SB; ++b) {
-                    if (!((ucur >> b) & 1u)) continue;
-                    const uint64_t m = __ballot(op[b] != (T)0);
+                  for (int u2 = 0; u2 < SUB; ++u2) {
+                    int cx[2] = {0, 0}, cy[2] = {0, 0}, cl[2] = {0, 0};
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                      const int nz = __popc((uint32_t)((m >> (32 * h)) | (m >> (32 * h + 16))) & 0xFFFFu);
-                      if (P.diag || b < NX) cx[h] += nz; else cy[h] += nz;
-                      if (P.diag && b < P.ymin) cl[h] += nz;
+                    for (int b = 0; b < SB; ++b) {
+                      const uint64_t m = __ballot(op[u2][b] != (T)0);
+#pragma unroll
+                      for (int h = 0; h < 2; ++h) {
+                        const int nz = __popc((uint32_t)((m >> (32 * h)) | (m >> (32 * h + 16))) & 0xFFFFu);
+                        if (P.diag || b < NX) cx[h] += nz; else cy[h] += nz;
+                        if (P.diag && b < P.ymin) cl[h] += nz;
+                      }
                     }
-                  }
 #pragma unroll
-                  for (int h = 0; h < 2; ++h)
-                    nalg += P.diag ? 2ull * (unsigned long long)(cx[h] * cx[h] - cl[h] * cl[h])
-                                   : 2ull * (unsigned long long)cx[h] * (unsigned long long)cy[h];
+                    for (int h = 0; h < 2; ++h)
+                      nalg += P.diag ? 2ull * (unsigned long long)(cx[h] * cx[h] - cl[h] * cl[h])
+                                     : 2ull * (unsigned long long)cx[h] * (unsigned long long)cy[h];
+                  }
                 }
                 if (rs == 0) {
                   u_h |= ucur;
 #pragma unroll
-                  for (int b = 0; b < SB; ++b)
-                    if ((ucur >> b) & 1u) {
-                      h0[b] = fma(wr, op[b], h0[b]);
-                      h1[b] = fma(wra, op[b], h1[b]);
+                  for (int u2 = 0; u2 < SUB; ++u2)
+#pragma unroll
+                    for (int b = 0; b < SB; ++b) {  // (zeros where the turn reaches no pixel)
+                      h0[b] = fma(wr[u2], op[u2][b], h0[b]);
+                      h1[b] = fma(wra[u2], op[u2][b], h1[b]);
                     }
                 }
-                const T sq = Form::root(wr * co_l);
 #pragma unroll
-                for (int b = 0; b < SB; ++b) op[b] *= sq;
-                tile_steps(ucur, P.diag, P.ymin, op, op);
+                for (int u2 = 0; u2 < SUB; ++u2) {
+                  const T sq = Form::root(wr[u2] * co_l);
+#pragma unroll
+                  for (int b = 0; b < SB; ++b) op[u2][b] *= sq;
+                }
+                tile_steps(ucur, P.diag, P.ymin, op);
               }
               if constexpr (NW == 1) ucur = unext;
-            }
-            if constexpr (NW == 2) {
-              // the last step's buffer, once both waves have read it
-              if (nsteps > 0) {
-                __syncthreads();
-                const int bl = (nsteps - 1) % 3;
-#pragma unroll
-                for (int b = 0; b < SB; ++b)
-                  if ((b & 1) == wv) buf[bl][lk][16 * b + lm] = 0.0;
-              }
             }
 
           }
@@ -830,7 +897,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
               });
             });
           }
-          if (a.counters && wv == 0) {
+          if (COUNT && wv == 0) {
             int hx = 0, qy = 0, hl = 0, ql = 0;
 #pragma unroll
             for (int b = 0; b < SB; ++b) {
@@ -860,9 +927,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
         // loop; off-diagonal blocks (bx < by, every block of a rectangle pass)
         // also go to (y, x).
         // (with two waves, each flushes its own slots)
-        static_for<0, (MBW + GB - 1) / GB>([&](auto G) __attribute__((always_inline)) {
-          constexpr int g = decltype(G)::value;
-          __syncthreads();  // the previous group's stage has been read
+        const DArgs a = dargs();
+        const int nb = NP * a->g.n_perp;
+        const int64_t obase = (int64_t)real * nb;
+        static_for<0, (MBW + GB - 1) / GB>([&](auto GC) __attribute__((always_inline)) {
+          constexpr int g = decltype(GC)::value;
+          sync<NW>();  // the previous group's stage has been read
           static_for<0, GB>([&](auto I) __attribute__((always_inline)) {
             constexpr int jj = g * GB + decltype(I)::value;
             if constexpr (jj < MBW) {
@@ -871,7 +941,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
               acc[jj] = Acc{0, 0, 0, 0};
             }
           });
-          __syncthreads();
+          sync<NW>();
           for (int e = lane; e < GB * 256; e += 64) {
             const int jj = g * GB + (e >> 8);
             if (jj >= MBW) break;
@@ -887,8 +957,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
             }
             const int ox = otab[16 * bx + ((e >> 4) & 15)], oy = otab[16 * by + (e & 15)];
             if (v != 0.0 && ox >= 0 && oy >= 0) {
-              atomicAdd(&a.dnum[(obase + ox) * nb + oy], v);
-              if (bx != by) atomicAdd(&a.dnum[(obase + oy) * nb + ox], v);
+              atomicAdd(&a->dnum[(obase + ox) * nb + oy], v);
+              if (bx != by) atomicAdd(&a->dnum[(obase + oy) * nb + ox], v);
             }
           }
         });
@@ -897,8 +967,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
             const double v = wdacc[x];
             const int ox = otab[x];
             if (v != 0.0 && ox >= 0) {
-              atomicAdd(&a.wd[obase + ox], v);
-              atomicAdd(&a.dnum[(obase + ox) * nb + ox], v);
+              atomicAdd(&a->wd[obase + ox], v);
+              atomicAdd(&a->dnum[(obase + ox) * nb + ox], v);
             }
             wdacc[x] = 0.0;
           }
@@ -907,7 +977,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
       r0 = r1;
     }
   }
-  if (a.counters) {
+  if constexpr (COUNT) {
+    unsigned long long* const counters = dargs()->counters;
     unsigned long long ni = n_in, nl = n_lost;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -915,26 +986,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
       nl += __shfl_xor(nl, o, 64);
     }
     if (lane == 0) {
-      atomicAdd(&a.counters[0], ni);
-      atomicAdd(&a.counters[1], nalg);
-      atomicAdd(&a.counters[2], nl);
+      atomicAdd(&counters[0], ni);
+      atomicAdd(&counters[1], nalg);
+      atomicAdd(&counters[2], nl);
     }
   }
 }
 
 template <typename T, int NB, int PMAX, int WPE, int NW>
 hipError_t launch_wave(const DmatArgs& a, int blocks, hipStream_t st) {
-  if (a.g.zero_lo_par && a.g.zero_lo_perp)
-    hipLaunchKernelGGL((dmat_wave_kernel<T, NB, PMAX, WPE, true, NW>), dim3(blocks), dim3(64 * NW), 0, st, a);
-  else
-    hipLaunchKernelGGL((dmat_wave_kernel<T, NB, PMAX, WPE, false, NW>), dim3(blocks), dim3(64 * NW), 0, st, a);
+  const bool zlo = a.g.zero_lo_par && a.g.zero_lo_perp;
+  auto kern = a.counters ? (zlo ? dmat_wave_kernel<T, NB, PMAX, WPE, true, NW, true> : dmat_wave_kernel<T, NB, PMAX, WPE, false, NW, true>)
+                         : (zlo ? dmat_wave_kernel<T, NB, PMAX, WPE, true, NW, false> : dmat_wave_kernel<T, NB, PMAX, WPE, false, NW, false>);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * NW), 0, st, a);
   return hipGetLastError();
 }
 
 template <typename T, int NB, int PMAX, int WPE, int NW>
 int wave_occupancy() {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, dmat_wave_kernel<T, NB, PMAX, WPE, true, NW>, 64 * NW, 0) !=
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, dmat_wave_kernel<T, NB, PMAX, WPE, true, NW, false>, 64 * NW, 0) !=
       hipSuccess)
     return 4;
   return n > 0 ? n : 1;

@@ -1174,6 +1174,13 @@ lya_status lya_dmat(lya_context* ctx, const lya_forests* F, const lya_grid* G, c
       }
       const int64_t per = W.n_pairs / (64 * (int64_t)max_wg * ctx->n_cu);
       a.chunk = (int32_t)(per < 16 ? 16 : (per > kDmatChunk ? kDmatChunk : per));
+      if (o->precision == LYA_FP64 && per < 16) {
+        // few pairs: about 8 items per workgroup of the large-tile kernel (four on a
+        // CU).  38600 pairs in items of 16 took 22.4 ms, of 3 8.5, of 5 8.3.  Not in
+        // FP32, whose tiles' sums depend on where the items end.
+        const int64_t few = W.n_pairs / (8 * 4 * (int64_t)ctx->n_cu);
+        a.chunk = (int32_t)(few < 1 ? 1 : (few > 16 ? 16 : few));
+      }
       a.n_items = (W.n_pairs + a.chunk - 1) / a.chunk;
     }
     a.drec32 = P.drec32;
