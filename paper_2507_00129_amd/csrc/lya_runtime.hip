@@ -1257,7 +1257,21 @@ lya_status lya_dmat(lya_context* ctx, const lya_forests* F, const lya_grid* G, c
       char key[96];
       snprintf(key, sizeof key, "dmat/%d/%d", o->precision, nb);
       auto found = ctx->tuned.find(key);
-      if (found != ctx->tuned.end()) {
+      // FP32 calls with fewer than 32 pairs per CU, where nothing was tuned before the
+      // first of them, take the 8-wave kernel untimed: it shares a pair among 8 waves,
+      // where the wave kernels end in a tail (1057 pairs: 2.3 ms, not 4.3; 735: 1.8, not
+      // 2.9), and is within a fifth of them elsewhere (8118 pairs: 6.4 ms, not 5.7).
+      // What such calls took first they keep, so that their rounding does not change
+      // when a larger call is tuned.  FP64 wave kernels take smaller items and are timed.
+      char few_key[104];
+      snprintf(few_key, sizeof few_key, "%s/few", key);
+      bool few = o->precision != LYA_FP64 && W.n_pairs < 32 * (int64_t)ctx->n_cu;
+      if (few && ctx->tuned.count(few_key) == 0) {
+        if (found == ctx->tuned.end()) ctx->tuned[few_key] = 0; else few = false;
+      }
+      if (few) {
+        variant = 0;
+      } else if (found != ctx->tuned.end()) {
         variant = found->second;
       } else if (o->autotune && W.n_pairs > 0 && dmat_num_variants() > 1) {
         // time each variant on a prefix of the pair list into scratch outputs
