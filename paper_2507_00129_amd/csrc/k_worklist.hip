@@ -35,9 +35,9 @@ __global__ void keys_kernel(WorklistArgs a) {
   a.ids[f] = (int32_t)f;
 }
 
-__global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
+__global__ void fill_i32_kernel(int32_t* a, int32_t* b, int64_t n, int32_t v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+  if (i < n) a[i] = b[i] = v;
 }
 
 __device__ __forceinline__ int cell_of(uint64_t key, int n_strips) {
@@ -246,9 +246,7 @@ hipError_t launch_sort_forests(WorklistArgs& a, hipStream_t st) {
   const size_t ncell = (size_t)a.n_real * a.n_strips;
   // empty cells read -1 (a fill kernel rather than a memset node)
   hipLaunchKernelGGL(fill_i32_kernel, dim3(nblk((int64_t)ncell, 256)), dim3(256), 0, st, a.cell_begin,
-                     (int64_t)ncell, -1);
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(nblk((int64_t)ncell, 256)), dim3(256), 0, st, a.cell_end,
-                     (int64_t)ncell, -1);
+                     a.cell_end, (int64_t)ncell, -1);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(cells_kernel, dim3(nblk(a.n_forests, 256)), dim3(256), 0, st, a);

@@ -715,6 +715,11 @@ __global__ void zero_kernel(uint32_t* p, size_t n) {
     p[i] = 0u;
 }
 
+__global__ void zero3_kernel(uint32_t* a, uint32_t* b, uint32_t* c, size_t n) {
+  uint32_t* const p = blockIdx.y == 0 ? a : (blockIdx.y == 1 ? b : c);
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
+}
+
 // Bin means from the sums of w_i w_j x (x in bin units) and w_i w_j (z_i + z_j):
 // r = e0 + dr * sum(ww x) / W, z = sum(ww (z_i + z_j)) / (2 W); 0 where W = 0.
 __global__ void finalize_means_kernel(const double* wsum, const double* msum, int64_t n, GridDev g,
@@ -864,6 +869,14 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t st) {
   const size_t n = bytes / 4;
   const unsigned blocks = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
   hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, st, (uint32_t*)p, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_zero3(void* a, void* b, void* c, size_t bytes, hipStream_t st) {
+  if (bytes == 0) return hipSuccess;
+  const size_t n = bytes / 4;
+  const unsigned blocks = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
+  hipLaunchKernelGGL(zero3_kernel, dim3(blocks, c ? 3 : 2), dim3(256), 0, st, (uint32_t*)a, (uint32_t*)b, (uint32_t*)c, n);
   return hipGetLastError();
 }
 

@@ -44,6 +44,7 @@ struct Globals {
   int32_t flag;     // validation error bits
   int32_t pad;
   double span;      // sum of the forests' extents along the line of sight
+  unsigned long long cand;  // candidate pixel pairs of the work list
 };
 
 // Pixel records for the xi and backward kernels.
@@ -485,6 +486,8 @@ int xi_bwd_block();
 int xi_bwd_blocks_per_cu(int precision, int n_bins);
 
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
+// The same number of bytes of two or three arrays (c may be NULL), in one launch.
+hipError_t launch_zero3(void* a, void* b, void* c, size_t bytes, hipStream_t st);
 hipError_t launch_finalize_xi(const double* num, const double* wsum, double* xi, int64_t n,
                               hipStream_t st);
 

@@ -21,6 +21,8 @@ struct Buf {
   size_t bytes = 0;
 };
 
+constexpr size_t kPinnedWords = 4096;
+
 struct lya_context {
   int device = 0;
   int n_cu = 1;
@@ -29,7 +31,7 @@ struct lya_context {
   std::map<std::string, Buf> bufs;
   std::map<std::string, int> tuned;
   hipEvent_t ev[8]{};
-  void* pinned = nullptr;  // small pinned host staging area
+  void* pinned = nullptr;  // pinned host staging area: kPinnedWords bytes, then a grid's edges
   // candidate pairs after which an xi workgroup flushes its LDS histograms;
   // the environment variable LYA_XI_FLUSH_PAIRS lowers it (a test hook that
   // exercises the flush on small inputs)
@@ -226,6 +228,7 @@ __global__ void init_globals_kernel(Globals* g) {
   g->flag = 0;
   g->pad = 0;
   g->span = 0.0;
+  g->cand = 0ull;
 }
 
 struct Prepared {
@@ -253,10 +256,15 @@ lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
   LYA_TRY(wst(ctx, "finfo", (size_t)N, &P.finfo));
   EtaInfo* einfo;
   LYA_TRY(wst(ctx, "einfo", (size_t)N, &einfo));
-  LYA_TRY(wst(ctx, "edges_par", (size_t)gd.n_par + 1, &P.edges_par));
-  LYA_TRY(wst(ctx, "edges_perp", (size_t)gd.n_perp + 1, &P.edges_perp));
-  HIP_TRY(hipMemcpyAsync(P.edges_par, G->edges_par, sizeof(double) * (gd.n_par + 1), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(P.edges_perp, G->edges_perp, sizeof(double) * (gd.n_perp + 1), hipMemcpyHostToDevice, st));
+  // both edge arrays in one copy from pinned memory, which this call has to itself:
+  // the stream is synchronised before the call returns
+  const size_t ne = (size_t)gd.n_par + gd.n_perp + 2;
+  LYA_TRY(wst(ctx, "edges", ne, &P.edges_par));
+  P.edges_perp = P.edges_par + gd.n_par + 1;
+  double* const edges = (double*)((char*)ctx->pinned + kPinnedWords);
+  memcpy(edges, G->edges_par, sizeof(double) * (gd.n_par + 1));
+  memcpy(edges + gd.n_par + 1, G->edges_perp, sizeof(double) * (gd.n_perp + 1));
+  HIP_TRY(hipMemcpyAsync(P.edges_par, edges, sizeof(double) * ne, hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(init_globals_kernel, dim3(1), dim3(1), 0, st, P.glob);
   HIP_TRY(hipGetLastError());
   if (o->validate) {
@@ -336,6 +344,23 @@ lya_status read_i64(lya_context* ctx, const int64_t* dev, int64_t* host, int cou
   return LYA_OK;
 }
 
+__global__ void totals_kernel(const int64_t* a, const int64_t* b, const int64_t* c, int64_t* out) {
+  out[0] = *a;
+  out[1] = *b;
+  if (c) out[2] = *c;
+}
+
+// Two or three device integers, written to pinned memory by one kernel (a copy each
+// was 2 us of the stream and 5 of the host).
+lya_status read_totals(lya_context* ctx, const int64_t* a, const int64_t* b, const int64_t* c, int64_t* host,
+                       hipStream_t st) {
+  hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1), 0, st, a, b, c, (int64_t*)ctx->pinned);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipStreamSynchronize(st));
+  memcpy(host, ctx->pinned, sizeof(int64_t) * (c ? 3 : 2));
+  return LYA_OK;
+}
+
 int xi_chunk(const lya_forests* F, int target_stream) {
   const double mean = F->n_forests ? (double)F->n_pix / (double)F->n_forests : 1.0;
   int c = (int)llround(target_stream / (mean > 1.0 ? mean : 1.0));
@@ -393,17 +418,12 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
   a.cub_bytes = worklist_cub_bytes(N);
   LYA_TRY(ws(ctx, "wl_cub", a.cub_bytes, &a.cub_tmp));
 
-  LYA_TRY(wst(ctx, "wl_cand", 1, &a.cand));
-  HIP_TRY(launch_zero(a.cand, sizeof(unsigned long long), st));
+  a.cand = &P.glob->cand;  // cleared with the rest of it
   HIP_TRY(launch_sort_forests(a, st));
   HIP_TRY(launch_count_neighbours(a, st));
   HIP_TRY(launch_scan(a.cnt, a.nb_off, N, a.cub_tmp, a.cub_bytes, st));
   int64_t last[3];
-  HIP_TRY(hipMemcpyAsync((char*)ctx->pinned, a.cnt + (N - 1), 8, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync((char*)ctx->pinned + 8, a.nb_off + (N - 1), 8, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync((char*)ctx->pinned + 16, a.cand, 8, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  memcpy(last, ctx->pinned, 24);
+  LYA_TRY(read_totals(ctx, a.cnt + (N - 1), a.nb_off + (N - 1), (const int64_t*)a.cand, last, st));
   const int64_t total = last[0] + last[1];
   W.candidates = last[2];
   LYA_TRY(wst(ctx, (t + "_nbr").c_str(), (size_t)total, &a.nbr));
@@ -428,10 +448,7 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
     }
     HIP_TRY(launch_count_items(a, st));
     HIP_TRY(launch_scan(a.item_cnt, a.item_off, N, a.cub_tmp, a.cub_bytes, st));
-    HIP_TRY(hipMemcpyAsync((char*)ctx->pinned, a.item_cnt + (N - 1), 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync((char*)ctx->pinned + 8, a.item_off + (N - 1), 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    memcpy(last, ctx->pinned, 16);
+    LYA_TRY(read_totals(ctx, a.item_cnt + (N - 1), a.item_off + (N - 1), nullptr, last, st));
     W.n_items = last[0] + last[1];
     LYA_TRY(wst(ctx, (t + "_items").c_str(), (size_t)W.n_items, &a.items));
     HIP_TRY(launch_fill_items(a, st));
@@ -560,7 +577,7 @@ lya_status lya_create(lya_context** out, int device) {
       delete ctx;
       return create_failed(LYA_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
     }
-  if ((e = hipHostMalloc(&ctx->pinned, 4096)) != hipSuccess) {
+  if ((e = hipHostMalloc(&ctx->pinned, kPinnedWords + sizeof(double) * (kMaxBins + 4))) != hipSuccess) {
     delete ctx;
     return create_failed(LYA_E_NOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
   }
@@ -621,9 +638,7 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
   const int64_t nout = (int64_t)F->n_realisations * (sub ? n_sub : 1) * nb;
   Timer tm{ctx, st, o->timing != 0};
   tm.at(0);
-  HIP_TRY(launch_zero(num, nout * sizeof(double), st));
-  HIP_TRY(launch_zero(wsum, nout * sizeof(double), st));
-  HIP_TRY(launch_zero(npairs, nout * sizeof(int64_t), st));
+  HIP_TRY(launch_zero3(num, wsum, npairs, nout * sizeof(double), st));
   double* msum = nullptr;
   if (means) {
     LYA_TRY(wst(ctx, "xi_msum", (size_t)(3 * nout), &msum));
@@ -903,9 +918,7 @@ lya_status xi3_impl(lya_context* ctx, const lya_forests* F, const lya_grid3* G3,
   const int64_t nout = nslab * n_bins;
   Timer tm{ctx, st, o->timing != 0};
   tm.at(0);
-  HIP_TRY(launch_zero(num, nout * sizeof(double), st));
-  HIP_TRY(launch_zero(wsum, nout * sizeof(double), st));
-  HIP_TRY(launch_zero(ntrip, nout * sizeof(int64_t), st));
+  HIP_TRY(launch_zero3(num, wsum, ntrip, nout * sizeof(double), st));
   if (F->n_forests > 0 && F->n_pix > 0) {
     Prepared P;
     const bool project = o->project_deltas != 0;
@@ -1357,8 +1370,7 @@ lya_status lya_xi_backward(lya_context* ctx, const lya_forests* F, const lya_gri
   const int64_t R = F->n_realisations;
   Timer tm{ctx, st, o->timing != 0};
   tm.at(0);
-  HIP_TRY(launch_zero(grad_delta, (size_t)F->n_pix * sizeof(double), st));
-  HIP_TRY(launch_zero(grad_weight, (size_t)F->n_pix * sizeof(double), st));
+  HIP_TRY(launch_zero3(grad_delta, grad_weight, nullptr, (size_t)F->n_pix * sizeof(double), st));
   if (F->n_forests > 0 && F->n_pix > 0) {
     Prepared P;
     const bool project = o->project_deltas != 0;
