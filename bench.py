@@ -8,7 +8,7 @@ distortion matrix over the kept forest pairs and its finalisation.  Inputs are
 synthetic (seeded), resident in HBM before the timed region.
 
 value = in-grid pixel pairs of the step (xi pairs + pairs of the kept D forest
-pairs) / step time, for the FP32 form.  Kernel variants are the autotuner's
+pairs) / step time, for the FP32 form.  Kernel variants are the rule's (xi) and the autotuner's (D)
 choice, made during the first warm-up step.  The FP64 form is timed the same
 way (fewer steps) and reported beside it, with the FP32 form's error against
 FP64 at full size and both forms' errors against the FP64 CPU oracle on a
@@ -312,8 +312,8 @@ def issued_valu_frac(kernel, source, ms):
     return rec["insts_valu_per_launch"] * 64 / (ms / 1e3) / PEAK_VALU_LANE_OPS
 
 
-XI_KERNELS = {0: "xi_kernel<float, 512, true, false, false, false>", 1: "xi_kernel<float, 1024, true, false, false, false>",
-              2: "xi_kernel<float, 512, true, true, false, false>", 3: "xi_kernel<float, 1024, true, true, false, false>"}
+XI_KERNELS = {0: "xi_kernel<float, 512, true, false, false, false, 16>", 1: "xi_kernel<float, 1024, true, false, false, false, 16>",
+              2: "xi_kernel<float, 512, true, true, false, false, 16>", 3: "xi_kernel<float, 1024, true, true, false, false, 16>"}
 
 
 def xi_roofline(r, peaks):
@@ -363,9 +363,9 @@ def xi3_roofline(entries, ms, peaks):
 
 # FP32 distortion kernels by variant index: the 8-wave kernel, the two
 # single-wave tiles, and the hybrid launch of both single-wave kernels
-D_KERNELS = {0: ["dmat_kernel<float, 512, true>"], 1: ["dmat_wave_kernel<float, 10, 4, 2, true, 2>"],
-             2: ["dmat_wave_kernel<float, 8, 4, 2, true, 1>"],
-             3: ["dmat_wave_kernel<float, 10, 4, 2, true, 2>", "dmat_wave_kernel<float, 8, 4, 2, true, 1>"]}
+D_KERNELS = {0: ["dmat_kernel<float, 512, true>"], 1: ["dmat_wave_kernel<float, 10, 4, 2, true, 2, false>"],
+             2: ["dmat_wave_kernel<float, 8, 4, 2, true, 1, false>"],
+             3: ["dmat_wave_kernel<float, 10, 4, 2, true, 2, false>", "dmat_wave_kernel<float, 8, 4, 2, true, 1, false>"]}
 
 
 def d_roofline(r):
@@ -407,7 +407,7 @@ def main():
                     help="forests for the three-point timing on the paper's 80 Mpc/h grid")
     ap.add_argument("--cpu-xi-forests", type=int, default=600)
     ap.add_argument("--cpu-d-forests", type=int, default=200)
-    ap.add_argument("--xi-variant", type=int, default=-1, help="xi kernel variant (-1: the autotuner's choice)")
+    ap.add_argument("--xi-variant", type=int, default=-1, help="xi kernel variant (-1: by bin width and pixel spacing)")
     ap.add_argument("--d-variant", type=int, default=-1,
                     help="distortion kernel variant (-1: the autotuner's choice)")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
@@ -569,7 +569,7 @@ def main():
     line["roofline_xi"] = xi_roofline(r32, peaks)
     line["roofline_xi_lds"] = xi_lds_roofline(r32, peaks)
     line["roofline_d"] = d_roofline(r32)
-    line["variants"] = dict(xi=r32["xi_variant_name"], d=r32["d_variant_name"], chosen_by="autotuner"
+    line["variants"] = dict(xi=r32["xi_variant_name"], d=r32["d_variant_name"], chosen_by="rule (xi), autotuner (D)"
                             if args.xi_variant < 0 and args.d_variant < 0 else "command line")
     if peaks:
         line["measured_peaks_lane_ops_per_s"] = peaks

@@ -103,9 +103,10 @@ __device__ __forceinline__ int det_shift(unsigned long long mbits) {
   return sh > 1000 ? 1000 : (sh < -1000 ? -1000 : sh);
 }
 
-// LDS sums: arrays of nd = n_bins + 64 entries, the last 64 for the pairs
-// outside the grid, one per lane (one for all would be a conflict of all).  FP64 sums first: N, W and, with MEANS, w w x_par, w w x_perp, w w
-// (z_i + z_j); DET: the 64-bit low words of N and W, then their 32-bit high
+// LDS sums: arrays of nd = n_bins + spare entries, the last ones for the pairs
+// outside the grid: one per lane (one for all would be a conflict of all), or one
+// where the bin means' arrays fill the LDS.  FP64 sums first: N, W and, with MEANS,
+// w w x_par, w w x_perp, w w (z_i + z_j); DET: the 64-bit low words of N and W, then their 32-bit high
 // words; the u32 counts last.
 template <bool MEANS, bool DET>
 constexpr int n_f64() { return MEANS ? 5 : 2; }
@@ -131,7 +132,7 @@ __device__ __forceinline__ KArgs kargs() {
 template <int BLOCK, bool MEANS, bool DET>
 __device__ __forceinline__ void flush_hist(double* h, int slab) {
   const KArgs a = kargs();
-  const int NP = a->g.n_par, NT = a->g.n_perp, nb = NP * NT, nd = nb + 64;
+  const int NP = a->g.n_par, NT = a->g.n_perp, nb = NP * NT, nd = nb + a->spare;
   const int64_t base = (int64_t)slab * nb;
   int* hc = (int*)(h + n_f64<MEANS, DET>() * nd);  // DET high words
   unsigned* hn = (unsigned*)(hc + (DET ? 2 * nd : 0));
@@ -172,10 +173,11 @@ __device__ __forceinline__ void flush_hist(double* h, int slab) {
 }
 
 // A wave's item: first pixel, stream position, s and c of its neighbours.
+template <int CH>
 struct WaveTab {
-  int64_t pix[kChunkMax];
-  double s[kChunkMax], c[kChunkMax];
-  int32_t pos[kChunkMax];
+  int64_t pix[CH];
+  double s[CH], c[CH];
+  int32_t pos[CH];
 };
 
 // Lanes whose bin is not that of the run they sum (their low 16 bits differ).
@@ -236,14 +238,14 @@ __device__ __forceinline__ void change_sum(uint64_t m, double& p, double& a) {
 
 // Two workgroups of 16 waves fill a CU's wave slots at 2500 bins (50 KB of LDS
 // for the sums, 14 KB for the waves' items); MEANS needs 110 KB, one workgroup.
-template <typename T, int BLOCK, bool ZLO, bool RUNS, bool MEANS, bool DET>
+template <typename T, int BLOCK, bool ZLO, bool RUNS, bool MEANS, bool DET, int CH>
 __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
   static_assert(!(DET && MEANS), "the deterministic form has no bin means");
   static_assert(RUNS || !(DET || MEANS), "these forms sum runs");
-  static_assert((kChunkMax & (kChunkMax - 1)) == 0, "the search for a stream pixel's neighbour halves it");
+  static_assert((CH & (CH - 1)) == 0, "the search for a stream pixel's neighbour halves it");
   using Rec = typename RecOf<T>::type;
   extern __shared__ double smem[];
-  __shared__ WaveTab tabs[BLOCK / 64];
+  __shared__ WaveTab<CH> tabs[BLOCK / 64];
   __shared__ int s_next;
   __shared__ unsigned long long s_pairs;  // candidate pairs added since the last flush
   __shared__ unsigned s_lo, s_hi;         // several slabs: the workgroup's run of tickets,
@@ -251,8 +253,8 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
   __shared__ int s_gone;                  // one slab: counters found to have no ticket left
 
   const int lane = threadIdx.x & 63;
-  WaveTab& tab = tabs[uniform((int)threadIdx.x >> 6)];
-  const int NP = kargs()->g.n_par, nb = NP * kargs()->g.n_perp, nd = nb + 64;
+  WaveTab<CH>& tab = tabs[uniform((int)threadIdx.x >> 6)];
+  const int NP = kargs()->g.n_par, nb = NP * kargs()->g.n_perp, nd = nb + kargs()->spare;
   for (int e = threadIdx.x; e < nd * (int)(smem_per_bin<MEANS, DET>() / 4); e += BLOCK) ((unsigned*)smem)[e] = 0u;
   if (threadIdx.x == 0) {
     s_next = kWaitAll;
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
   // non-uniform edges: every pair in range is binned from the edge arrays
   const uint32_t thr = kargs()->g.exact_all ? 0xffffffffu : kGuard2;
   // bins are carried as L = k_perp NP + k_par + G, G what the two upper words add
-  const uint32_t G = (kMagicHi & 0xffffffu) * (uint32_t)NP + kMagicHi, Lout = G + (uint32_t)(nb + lane);
+  const uint32_t G = (kMagicHi & 0xffffffu) * (uint32_t)NP + kMagicHi, Lout = G + (uint32_t)(nb + (lane & (kargs()->spare - 1)));
   int shN = 0, shW = 0;  // DET: s of the current realisation
 
   int cur = -1;        // output slab of the LDS sums
@@ -347,12 +349,12 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
         n = lane < nbc ? tab.pos[lane] : 0;
         int incl = n;
 #pragma unroll
-        for (int o = 1; o < kChunkMax; o <<= 1) {
+        for (int o = 1; o < CH; o <<= 1) {
           const int v = __shfl_up(incl, o, 64);
           if (lane >= o) incl += v;
         }
         if (lane < nbc) tab.pos[lane] = incl - n;
-        total = __builtin_amdgcn_readlane(incl, kChunkMax - 1);
+        total = __builtin_amdgcn_readlane(incl, CH - 1);
         fext = (fpix0 >> 5) + uniform(f);
         // pixels of f per r_par bin, as the power of two below 1.4 times it
         const float per = 1.4f * (float)(nf - 1) / fmaxf((float)((fi.dmax - fi.dmin) * a->g.inv_par), 1e-6f);
@@ -439,7 +441,7 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
       // the neighbour of stream pixel q: the last that starts at or before it
       int k = 0;
 #pragma unroll
-      for (int step = kChunkMax / 2; step > 0; step >>= 1)
+      for (int step = CH / 2; step > 0; step >>= 1)
         if (k + step < nbc && tab.pos[k + step] <= q) k += step;
       // (past the stream's end: no pixel)
       double Dj = 0.0, cp, st = 0.0, bt;
@@ -662,10 +664,10 @@ constexpr Variant kVariants[] = {
     {"b512", 512, false}, {"b1024", 1024, false}, {"b512-runs", 512, true}, {"b1024-runs", 1024, true}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-template <typename T, int BLOCK, bool ZLO, bool RUNS, bool MEANS = false, bool DET = false>
+template <typename T, int BLOCK, bool ZLO, bool RUNS, bool MEANS = false, bool DET = false, int CH = kChunkMax>
 hipError_t launch_one(const XiArgs& a, int blocks, hipStream_t st) {
-  const size_t smem = ((size_t)a.g.n_par * a.g.n_perp + 64) * smem_per_bin<MEANS, DET>();
-  auto kern = xi_kernel<T, BLOCK, ZLO, RUNS, MEANS, DET>;
+  const size_t smem = ((size_t)a.g.n_par * a.g.n_perp + a.spare) * smem_per_bin<MEANS, DET>();
+  auto kern = xi_kernel<T, BLOCK, ZLO, RUNS, MEANS, DET, CH>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(BLOCK), smem, st, a);
@@ -692,7 +694,7 @@ hipError_t launch_t(int v, const XiArgs& a, int blocks, hipStream_t st) {
 template <typename T, int BLOCK, bool RUNS, bool MEANS = false, bool DET = false>
 int occupancy(int n_bins) {
   const size_t smem = ((size_t)n_bins + 64) * smem_per_bin<MEANS, DET>();
-  auto kern = xi_kernel<T, BLOCK, true, RUNS, MEANS, DET>;
+  auto kern = xi_kernel<T, BLOCK, true, RUNS, MEANS, DET, kChunkMax>;
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return 1;
   int nblk = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nblk, kern, BLOCK, smem) != hipSuccess) return 1;
@@ -841,9 +843,22 @@ hipError_t launch_finalize_det(const unsigned long long* det_acc, const unsigned
 // 2500 bins.
 constexpr int kMeansBlock = 1024;
 
+// Bin means over 3490 bins fill the LDS: one entry for the pairs outside the grid and
+// items of two neighbours then leave room up to 3698 bins.
+bool xi_means_tight(int n_bins) {
+  return ((size_t)n_bins + 64) * smem_per_bin<true, false>() + sizeof(WaveTab<kChunkMax>) * (kMeansBlock / 64) + 64 > kLdsBytes;
+}
+
 hipError_t launch_xi_means(int precision, const XiArgs& a, int blocks, hipStream_t st) {
   if (a.n_items == 0) return hipSuccess;
   const bool zlo = a.g.zero_lo_par && a.g.zero_lo_perp;
+  if (a.spare == 1) {
+    if (precision == LYA_FP64)
+      return zlo ? launch_one<double, kMeansBlock, true, true, true, false, kChunkTight>(a, blocks, st)
+                 : launch_one<double, kMeansBlock, false, true, true, false, kChunkTight>(a, blocks, st);
+    return zlo ? launch_one<float, kMeansBlock, true, true, true, false, kChunkTight>(a, blocks, st)
+               : launch_one<float, kMeansBlock, false, true, true, false, kChunkTight>(a, blocks, st);
+  }
   if (precision == LYA_FP64)
     return zlo ? launch_one<double, kMeansBlock, true, true, true>(a, blocks, st)
                : launch_one<double, kMeansBlock, false, true, true>(a, blocks, st);
@@ -852,6 +867,7 @@ hipError_t launch_xi_means(int precision, const XiArgs& a, int blocks, hipStream
 }
 
 int xi_means_blocks_per_cu(int precision, int n_bins) {
+  if (xi_means_tight(n_bins)) return 1;
   return precision == LYA_FP64 ? occupancy<double, kMeansBlock, true, true>(n_bins)
                                : occupancy<float, kMeansBlock, true, true>(n_bins);
 }

@@ -13,6 +13,8 @@ constexpr int kMaxBins = 4096;     // n_par * n_perp limit (LDS histograms)
 constexpr int kMaxStrips = 4096;   // declination strips of the sky index
 constexpr int kMaxRealisations = 1 << 20;
 constexpr int kXiCounters = 16, kXiCounterStride = 32;  // counters of an xi launch, a cache line each
+constexpr int kChunkTight = 2;     // the same where the bin means fill the LDS
+constexpr size_t kLdsBytes = 160 * 1024;  // of a CU
 constexpr int kChunkMax = 16;      // neighbour forests per xi work item
 
 // Per-forest geometry and layout, FP64 (64 bytes).
@@ -259,6 +261,7 @@ struct XiArgs {
   int32_t n_parts;         // every item in n_parts tickets: its f pixels in runs of 32 dealt out in turn
   int32_t share, grab;     // one output slab: tickets a wave starts with, and then takes at a time
   int32_t chunk;           // several output slabs: tickets a workgroup takes at a time (0 with one)
+  int32_t spare;           // entries after the bins' for the pairs outside the grid: 64, or 1
   unsigned int* counter;
   const int32_t* order;    // optional: the order the items are taken in (by output slab)
   const XRec32* xrec32;
@@ -478,6 +481,7 @@ int xi3_combine_capacity();
 int xi3_max_cos_bins();
 int xi3_partner_capacity();
 int xi_means_blocks_per_cu(int precision, int n_bins);
+bool xi_means_tight(int n_bins);  // a.spare = 1 and items of at most kChunkTight neighbours
 hipError_t launch_finalize_means(const double* wsum, const double* msum, int64_t n, const GridDev& g,
                                  double* rpar, double* rperp, double* z, hipStream_t st);
 hipError_t launch_project_adjoint(const lya_forests* F, const EtaInfo* einfo, const double* delta_proj,

@@ -658,7 +658,8 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
     // items of ~2048 partner pixels, shorter ones where a wave would get less
     // than 4 of them (16 with several output slabs, where a workgroup's waves
     // wait for each other between slabs)
-    const int chunk = xi_chunk(F, 2048);
+    const bool tight = means && xi_means_tight(nb);
+    const int most = xi_chunk(F, 2048), chunk = tight && most > kChunkTight ? kChunkTight : most;
     const int64_t n_slabs = (int64_t)F->n_realisations * (sub ? n_sub : 1);
     const int64_t min_items = 32 * (int64_t)ctx->n_cu * (n_slabs > 1 ? 16 : 4);
     // subsample sums and the deterministic form list each unordered pair under
@@ -681,6 +682,7 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
     a.items = W.items;
     a.n_items = W.n_items;
     a.n_parts = item_parts(ctx, F, W.n_items, n_slabs, 32);
+    a.spare = tight ? 1 : 64;
     a.order = W.order;
     a.counter = counter;
     a.xrec32 = P.xrec32;

@@ -92,3 +92,16 @@ def test_gradient_items_and_realisations(lib, prec, grid, n, npix, width):
             e = O.err_norm(g.cpu().numpy(), w)
             print(f"[{prec} {grid}] e_g={e:.2e}", flush=True)
             assert e <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_par,n_perp", [(58, 60), (60, 60), (263, 14)])
+def test_bin_means_that_fill_the_lds(lib, prec, n_par, n_perp):
+    """Bin means over 3480, 3600 and 3682 bins: below and above the line where the
+    sums leave room for items of two neighbours and one entry for the pairs outside."""
+    from paper_2507_00129_amd import DeviceForests
+    G = uniform_grid(n_par, 150.0, n_perp, 40.0)
+    F = make_patch(40, 0.6, 5, npix_range=(1, 140), z_range=(2.1, 2.6))
+    ref = O.xi_sums(F, G)
+    out = lib.xi_means(DeviceForests.from_host(F), G, precision=prec)
+    compare({k: out[k].cpu().numpy() for k in ("npairs", "num", "wsum")}, ref, prec, (1, G.n_bins))
