@@ -96,7 +96,7 @@ template <typename T, int BLOCK, bool ZLO>
 __global__ __launch_bounds__(BLOCK, 8) void xi_bwd_kernel(BwdArgs) {
   using Rec = typename RecOf<T>::type;
   using T2 = typename Pair2<T>::type;
-  extern __shared__ double smem[];
+  extern __shared__ __align__(16) double smem[];
   T2* const gam = (T2*)smem;  // [nb]: gamma, gamma xi  (local layout)
   __shared__ BwdTab tabs[BLOCK / 64];
   __shared__ int s_next, s_done, s_gone;
