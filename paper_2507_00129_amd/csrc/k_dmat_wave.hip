@@ -781,8 +781,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
                 }
               }
               const uint32_t unext = st + 1 < nturns ? bin_rows(ROWS * (st + 1), bnext, rdv) : 0u;
+              // Written only where rows were binned.  The first write of a sweep then
+              // comes after the barriers of its rows_at, which the other wave reaches
+              // once it has read the last mask of the sweep before; a sweep without rows
+              // has no barrier, and its write could clear a mask the other wave had yet
+              // to read (blocks of that turn would be left out).
               if constexpr (NW == 2) {
-                if (lane == 0) smask[bnext][wv] = unext;
+                if (lane == 0 && st + 1 < nturns) smask[bnext][wv] = unext;
               }
               if (st >= 0) {
                 if (COUNT && wv == 0) {
