@@ -257,14 +257,19 @@ lya_status prepare(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
   EtaInfo* einfo;
   LYA_TRY(wst(ctx, "einfo", (size_t)N, &einfo));
   // both edge arrays in one copy from pinned memory, which this call has to itself:
-  // the stream is synchronised before the call returns
-  const size_t ne = (size_t)gd.n_par + gd.n_perp + 2;
-  LYA_TRY(wst(ctx, "edges", ne, &P.edges_par));
-  P.edges_perp = P.edges_par + gd.n_par + 1;
+  // the stream is synchronised before the call returns.  Each has -1 before its first
+  // edge and infinity after its last.
+  const size_t np = (size_t)gd.n_par + 1, nt = (size_t)gd.n_perp + 1, ne = np + nt + 4;
+  double* edev;
+  LYA_TRY(wst(ctx, "edges", ne, &edev));
+  P.edges_par = edev + 1;
+  P.edges_perp = P.edges_par + np + 2;
   double* const edges = (double*)((char*)ctx->pinned + kPinnedWords);
-  memcpy(edges, G->edges_par, sizeof(double) * (gd.n_par + 1));
-  memcpy(edges + gd.n_par + 1, G->edges_perp, sizeof(double) * (gd.n_perp + 1));
-  HIP_TRY(hipMemcpyAsync(P.edges_par, edges, sizeof(double) * ne, hipMemcpyHostToDevice, st));
+  edges[0] = edges[np + 2] = -1.0;
+  edges[np + 1] = edges[np + nt + 3] = INFINITY;
+  memcpy(edges + 1, G->edges_par, sizeof(double) * np);
+  memcpy(edges + np + 3, G->edges_perp, sizeof(double) * nt);
+  HIP_TRY(hipMemcpyAsync(edev, edges, sizeof(double) * ne, hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(init_globals_kernel, dim3(1), dim3(1), 0, st, P.glob);
   HIP_TRY(hipGetLastError());
   if (o->validate) {
@@ -577,7 +582,7 @@ lya_status lya_create(lya_context** out, int device) {
       delete ctx;
       return create_failed(LYA_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
     }
-  if ((e = hipHostMalloc(&ctx->pinned, kPinnedWords + sizeof(double) * (kMaxBins + 4))) != hipSuccess) {
+  if ((e = hipHostMalloc(&ctx->pinned, kPinnedWords + sizeof(double) * (kMaxBins + 8))) != hipSuccess) {
     delete ctx;
     return create_failed(LYA_E_NOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
   }

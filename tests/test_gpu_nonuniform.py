@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from synth import Grid, make_config, subset_forests
+from synth import Grid, make_config, make_patch, subset_forests
 from synth.survey import nearest_to_centre
 
 from test_gpu_xi import check as check_xi
@@ -142,3 +142,46 @@ def test_dmat_vs_oracle(lib, grid, prec, variant):
         e_d = float(np.max(np.abs(out["dmat"] - ref.D)))
     print(f"[{grid} {prec} v{variant}] e_D={e_d:.3e} e_W={e_w:.3e}", flush=True)
     assert e_d <= TOL[prec] and e_w <= TOL[prec]
+
+
+WALKS = {
+    # widths from 0.05 to 30 Mpc/h: steps of one pixel over many bins
+    "steep": Grid(np.array([0.0, 0.05, 0.1, 0.2, 0.4, 0.8, 1.6, 3.2, 6.4, 12.8, 25.6, 55.6]),
+                  60.0 * (np.arange(13) / 12.0) ** 2),
+    # pixels pass below the first edge (r_par through 0) and beyond the last
+    "gap": Grid(np.array([7.0, 8.0, 11.0, 23.0]), np.array([3.0, 4.0, 30.0, 31.0, 33.0])),
+    # one bin on an axis, non-uniform on the other
+    "one": Grid(np.array([0.0, 40.0]), np.array([0.0, 1.0, 10.0, 45.0])),
+}
+
+
+@pytest.mark.parametrize("grid", sorted(WALKS))
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,npix,model", [(3, (64, 65), "log"), (40, (1, 33), "log"), (14, (300, 700), "lin")])
+def test_lanes_walk_along_the_edges(lib, grid, prec, n, npix, model):
+    """Lanes follow a pixel's bin from one pixel of the other forest to the next: by
+    steps, by jumps (narrow bins, runs of 32 pixels out of reach passed over), out of
+    the grid on either side and back in, with idle lanes and items in parts.  Every form:
+    run sums and single pairs, reproducible, subsamples, bin means."""
+    G = WALKS[grid]
+    F = make_patch(n, 0.3, 60 + n, model=model, npix_range=npix, z_range=(2.1, 2.6))
+    ref = O.xi_sums(F, G, means=True)
+    assert ref.n_near_edge == 0, "input has pairs within 1e-12 of an edge; choose another seed"
+    dF = dev(F)
+    rp, rt, z = O.bin_means(ref)
+    outs = [host(lib.xi(dF, G, precision=prec, variant=v)) for v in range(4)]
+    outs += [host(lib.xi(dF, G, precision=prec, deterministic=True)), host(lib.xi_means(dF, G, precision=prec))]
+    sub = torch.arange(n, dtype=torch.int32, device="cuda:0") % 3
+    parts = host(lib.xi_subsamples(dF, G, sub, 3, precision=prec))
+    outs.append({k: parts[k].sum(1) for k in ("npairs", "num", "wsum")})
+    scale = np.where(ref.absnum > 0, ref.absnum, 1.0)
+    for out in outs:
+        np.testing.assert_array_equal(out["npairs"].reshape(ref.npairs.shape), ref.npairs)
+        assert np.max(np.abs(out["num"].reshape(ref.num.shape) - ref.num) / scale) <= TOL[prec]
+        assert O.err_rel(out["wsum"].reshape(ref.wsum.shape), ref.wsum) <= TOL[prec]
+    out = outs[5]
+    wp, wt = (np.ptp(e) / (len(e) - 1) for e in (G.edges_par, G.edges_perp))
+    tol_r, tol_z = {"fp64": (1e-12, 1e-12), "fp32": (1e-4, 1e-6)}[prec]
+    assert float(np.max(np.abs(out["rpar"] - rp))) / wp <= tol_r
+    assert float(np.max(np.abs(out["rperp"] - rt))) / wt <= tol_r
+    assert O.err_rel(out["z"], z) <= tol_z
