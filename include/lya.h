@@ -122,7 +122,11 @@ typedef struct {
   int32_t eta;                /* lya_eta: projection used by lya_dmat and project_deltas */
   int32_t project_deltas;     /* lya_xi: replace delta by eta delta per forest first */
   int32_t autotune;           /* lya_dmat: pick the kernel variant by timing them on
-                                 this input (lya_xi chooses by a rule) */
+                                 this input.  The context keeps the choice for the
+                                 precision, n_par, n_perp and a class of pairs per CU;
+                                 calls with few pairs take variant 0 untimed.  The
+                                 variant decides the last bits of an FP32 D.  (lya_xi
+                                 chooses by a rule.) */
   int32_t validate;           /* check array contents on the device (one extra sync) */
   int32_t timing;             /* record per-stage device times (see lya_stats) */
   int32_t variant;            /* >= 0 forces that kernel variant; -1 lets the

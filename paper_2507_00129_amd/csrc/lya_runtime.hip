@@ -1274,21 +1274,20 @@ lya_status lya_dmat(lya_context* ctx, const lya_forests* F, const lya_grid* G, c
         return fail(ctx, LYA_E_INVALID, "variant %d out of range (dmat has %d)", o->variant, kHybrid + 1);
       variant = o->variant;
     } else {
+      // Few pairs take the 8-wave kernel, whatever was tuned before: it shares a pair
+      // among 8 waves, where the wave kernels end in a tail of single pairs.  Below the
+      // line it is within a quarter of the best variant and up to 2.5 (FP32) or 4.9 times
+      // (FP64) as fast as the large tile; above it falls behind (FP32, 14 k and 23 k
+      // pairs, 55 and 91 per CU: 5.4 ms, not 2.0, and 4.2, not 1.6; FP64, 8.8 k pairs, 34
+      // per CU: 4.6, not 2.0; as many of other shapes still within a third).
+      const bool few = W.n_pairs < (o->precision == LYA_FP64 ? 8 : 16) * (int64_t)ctx->n_cu;
+      // Other calls share a choice if their windows (the grid's shape) and their sizes
+      // are alike: tails, and in FP64 the items' size, depend on the pairs per CU.
+      int size = 0;
+      for (int64_t x = W.n_pairs / (128 * (int64_t)ctx->n_cu); x > 0 && size < 2; x /= 8) ++size;
       char key[96];
-      snprintf(key, sizeof key, "dmat/%d/%d", o->precision, nb);
+      snprintf(key, sizeof key, "dmat/%d/%dx%d/%d", o->precision, gd.n_par, gd.n_perp, size);
       auto found = ctx->tuned.find(key);
-      // FP32 calls with fewer than 32 pairs per CU, where nothing was tuned before the
-      // first of them, take the 8-wave kernel untimed: it shares a pair among 8 waves,
-      // where the wave kernels end in a tail (1057 pairs: 2.3 ms, not 4.3; 735: 1.8, not
-      // 2.9), and is within a fifth of them elsewhere (8118 pairs: 6.4 ms, not 5.7).
-      // What such calls took first they keep, so that their rounding does not change
-      // when a larger call is tuned.  FP64 wave kernels take smaller items and are timed.
-      char few_key[104];
-      snprintf(few_key, sizeof few_key, "%s/few", key);
-      bool few = o->precision != LYA_FP64 && W.n_pairs < 32 * (int64_t)ctx->n_cu;
-      if (few && ctx->tuned.count(few_key) == 0) {
-        if (found == ctx->tuned.end()) ctx->tuned[few_key] = 0; else few = false;
-      }
       if (few) {
         variant = 0;
       } else if (found != ctx->tuned.end()) {

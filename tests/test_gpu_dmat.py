@@ -253,3 +253,26 @@ def test_full_config1_fp32_vs_fp64(lib):
     e_w = O.err_rel(out["fp32"]["wsum_d"], out["fp64"]["wsum_d"])
     print(f"[dmat full] fp32 vs fp64: e_D={e_d:.2e} e_W={e_w:.2e}", flush=True)
     assert e_d <= 1e-5 and e_w <= 1e-5
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_few_pairs_do_not_follow_an_earlier_choice(prec):
+    """A call with few forest pairs takes the 8-wave kernel, alone on its context and
+    after a large call of the same grid that the autotuner gave another variant to (230
+    pairs per CU, where the 8-wave kernel takes several times as long)."""
+    from paper_2507_00129_amd import Library
+    F = make_patch(420, 2.0, 31, npix_range=(18, 128), z_range=(2.1, 2.9))
+    G = uniform_grid(15, 100.0)
+    p, seed = 0.004, 5
+    ref = O.dmat(F, G, O.dmat_pairs(F, G, p, seed))
+    taken = []
+    for first in (False, True):
+        lib = Library(0)
+        if first:
+            run_dmat(lib, F, G, precision=prec)
+            assert lib.last_stats()["forest_pairs"] > 40000 and lib.last_stats()["variant"] != 0
+        out = run_dmat(lib, F, G, precision=prec, keep_fraction=p, seed=seed)
+        taken.append(lib.last_stats()["variant"])
+        check(out, ref, prec, f"few pairs, large call first: {first}")
+        lib.close()
+    assert taken == [0, 0]
