@@ -190,18 +190,31 @@ __global__ __launch_bounds__(256) void neighbours_kernel(WorklistArgs a) {
   }
 }
 
-__global__ void count_items_kernel(WorklistArgs a) {
+// Output slab of each sorted position, and the positions.
+__global__ void slab_keys_kernel(WorklistArgs a) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= a.n_forests) return;
-  a.item_cnt[p] = (a.cnt[p] + a.chunk - 1) / a.chunk;
+  const int f = a.sorted[p];
+  a.keys[p] = (uint64_t)a.finfo[f].real * (uint64_t)a.n_sub + (uint64_t)a.sub[f];
+  a.ids[p] = (int32_t)p;
+}
+
+// item_cnt and item_off go by the order of the items: that of the sorted positions, or
+// with a subsample split by output slab first.
+__global__ void count_items_kernel(WorklistArgs a) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= a.n_forests) return;
+  const int64_t p = a.by_slab ? a.by_slab[k] : k;
+  a.item_cnt[k] = (a.cnt[p] + a.chunk - 1) / a.chunk;
 }
 
 // One wave per sorted position, lanes over its items.
 __global__ __launch_bounds__(256) void fill_items_kernel(WorklistArgs a) {
   const int lane = threadIdx.x & 63;
-  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (p >= a.n_forests) return;
-  const int64_t n = a.cnt[p], base = a.nb_off[p], o = a.item_off[p], m = a.item_cnt[p];
+  const int64_t at = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (at >= a.n_forests) return;
+  const int64_t p = a.by_slab ? a.by_slab[at] : at;
+  const int64_t n = a.cnt[p], base = a.nb_off[p], o = a.item_off[at], m = a.item_cnt[at];
   for (int64_t k = lane; k < m; k += 64) {
     Item it;
     it.nb_begin = base + k * a.chunk;
@@ -210,15 +223,6 @@ __global__ __launch_bounds__(256) void fill_items_kernel(WorklistArgs a) {
     it.nb_count = (int32_t)(left < a.chunk ? left : a.chunk);
     a.items[o + k] = it;
   }
-}
-
-__global__ void item_slabs_kernel(WorklistArgs a, int64_t n_items, const int32_t* sub, int32_t n_sub, uint64_t* keys,
-                                  int32_t* idx) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_items) return;
-  const int f = a.sorted[a.items[t].p];
-  keys[t] = (uint64_t)a.finfo[f].real * (uint64_t)n_sub + (uint64_t)sub[f];
-  idx[t] = (int32_t)t;
 }
 
 inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -296,11 +300,14 @@ hipError_t launch_fill_items(const WorklistArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_item_slabs(const WorklistArgs& a, int64_t n_items, const int32_t* sub, int32_t n_sub, uint64_t* keys,
-                             int32_t* idx, hipStream_t st) {
-  if (n_items == 0) return hipSuccess;
-  hipLaunchKernelGGL(item_slabs_kernel, dim3(nblk(n_items, 256)), dim3(256), 0, st, a, n_items, sub, n_sub, keys, idx);
-  return hipGetLastError();
+hipError_t launch_slab_order(const WorklistArgs& a, hipStream_t st) {
+  if (a.n_forests == 0) return hipSuccess;
+  hipLaunchKernelGGL(slab_keys_kernel, dim3(nblk(a.n_forests, 256)), dim3(256), 0, st, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  unsigned bits = 1;
+  while (bits < 63 && ((int64_t)a.n_real * a.n_sub) >> bits) ++bits;
+  return launch_sort_keys(a.keys, a.slab_keys, a.ids, a.by_slab, a.n_forests, a.cub_tmp, a.cub_bytes, st, bits);
 }
 
 }  // namespace lya

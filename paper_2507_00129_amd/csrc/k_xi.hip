@@ -319,7 +319,7 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
       if ((int64_t)t < a->n_items * a->n_parts) {
         part0 = t % (unsigned)a->n_parts * kRunMax;
         t /= (unsigned)a->n_parts;
-        const Item item = a->items[a->order ? a->order[t] : (int)t];
+        const Item item = a->items[t];
         const int f = a->sorted[item.p];
         const ForestInfo fi = a->finfo[f];
         key = uniform(a->sub ? fi.real * a->n_sub + a->sub[f] : fi.real);

@@ -233,8 +233,12 @@ struct WorklistArgs {
   int32_t* nbr;           // neighbour sorted positions
   int32_t* pair_p;        // optional: sorted position of the first forest per entry
   unsigned long long* cand;  // total candidate pixel pairs (sum n_f n_g), accumulated by the count pass
-  int64_t* item_cnt;      // [n_forests]
+  int64_t* item_cnt;      // [n_forests], in the order of the items
   int64_t* item_off;
+  const int32_t* sub;     // subsample split: subsample of each forest
+  int32_t n_sub;
+  uint64_t* slab_keys;    // [n_forests]
+  int32_t* by_slab;       // [n_forests], or NULL: items in order of the sorted positions
   Item* items;
   int chunk;
   void* cub_tmp;
@@ -248,9 +252,8 @@ hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t n, void* tmp, si
 hipError_t launch_fill_neighbours(const WorklistArgs& a, hipStream_t st);
 hipError_t launch_count_items(const WorklistArgs& a, hipStream_t st);
 hipError_t launch_fill_items(const WorklistArgs& a, hipStream_t st);
-// sort keys (output slab realisation * n_sub + sub) and indices of the items
-hipError_t launch_item_slabs(const WorklistArgs& a, int64_t n_items, const int32_t* sub, int32_t n_sub, uint64_t* keys,
-                             int32_t* idx, hipStream_t st);
+// by_slab: the sorted positions by output slab realisation * n_sub + sub (keys, ids reused)
+hipError_t launch_slab_order(const WorklistArgs& a, hipStream_t st);
 
 struct XiArgs {
   const ForestInfo* finfo;
@@ -263,7 +266,6 @@ struct XiArgs {
   int32_t chunk;           // several output slabs: tickets a workgroup takes at a time (0 with one)
   int32_t spare;           // entries after the bins' for the pairs outside the grid: 64, or 1
   unsigned int* counter;
-  const int32_t* order;    // optional: the order the items are taken in (by output slab)
   const XRec32* xrec32;
   const XAux32* xaux32;
   const Rec64* rec64;

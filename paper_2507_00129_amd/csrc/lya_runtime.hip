@@ -336,7 +336,6 @@ struct Worklist {
   int64_t* cnt = nullptr;     // neighbours of each sorted position, and their scan
   int64_t* nb_off = nullptr;
   Item* items = nullptr;
-  int32_t* order = nullptr;   // items by output slab (with a subsample split)
   int64_t n_pairs = 0;
   int64_t n_items = 0;
   int64_t candidates = 0;
@@ -451,6 +450,15 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
       if (c < 1) c = 1;
       if (c < a.chunk) a.chunk = (int)c;
     }
+    if (sub) {
+      // items in order of their output slab: the forests sorted by it (a sort of the
+      // items themselves took 25 us longer)
+      a.sub = sub;
+      a.n_sub = n_sub;
+      LYA_TRY(wst(ctx, "wl_slab_keys", (size_t)N, &a.slab_keys));
+      LYA_TRY(wst(ctx, "wl_by_slab", (size_t)N, &a.by_slab));
+      HIP_TRY(launch_slab_order(a, st));
+    }
     HIP_TRY(launch_count_items(a, st));
     HIP_TRY(launch_scan(a.item_cnt, a.item_off, N, a.cub_tmp, a.cub_bytes, st));
     LYA_TRY(read_totals(ctx, a.item_cnt + (N - 1), a.item_off + (N - 1), nullptr, last, st));
@@ -458,23 +466,6 @@ lya_status build_worklist(lya_context* ctx, const lya_forests* F, const GridDev&
     LYA_TRY(wst(ctx, (t + "_items").c_str(), (size_t)W.n_items, &a.items));
     HIP_TRY(launch_fill_items(a, st));
     W.items = a.items;
-    if (sub && W.n_items > 0) {
-      // items in order of their output slab
-      if (W.n_items > INT32_MAX) return fail(ctx, LYA_E_UNSUPPORTED, "too many work items");
-      uint64_t *k_in, *k_out;
-      int32_t* idx;
-      LYA_TRY(wst(ctx, "wl_slab_keys_in", (size_t)W.n_items, &k_in));
-      LYA_TRY(wst(ctx, "wl_slab_keys", (size_t)W.n_items, &k_out));
-      LYA_TRY(wst(ctx, "wl_slab_idx", (size_t)W.n_items, &idx));
-      LYA_TRY(wst(ctx, "wl_order", (size_t)W.n_items, &W.order));
-      const size_t bytes = sort_keys_bytes(W.n_items);
-      void* tmp;
-      LYA_TRY(ws(ctx, "wl_slab_tmp", bytes, &tmp));
-      HIP_TRY(launch_item_slabs(a, W.n_items, sub, n_sub, k_in, idx, st));
-      unsigned bits = 1;
-      while (bits < 63 && ((int64_t)R * n_sub) >> bits) ++bits;
-      HIP_TRY(launch_sort_keys(k_in, k_out, idx, W.order, W.n_items, tmp, bytes, st, bits));
-    }
   }
   return LYA_OK;
 }
@@ -688,7 +679,6 @@ lya_status xi_impl(lya_context* ctx, const lya_forests* F, const lya_grid* G, co
     a.n_items = W.n_items;
     a.n_parts = item_parts(ctx, F, W.n_items, n_slabs, 32);
     a.spare = tight ? 1 : 64;
-    a.order = W.order;
     a.counter = counter;
     a.xrec32 = P.xrec32;
     a.xaux32 = P.xaux32;

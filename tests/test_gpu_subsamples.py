@@ -115,3 +115,19 @@ def test_invalid_subsample_ids(lib):
     sub[5] = -1
     with pytest.raises(LyaError):
         lib.xi_subsamples(DeviceForests.from_host(F), G60, torch.from_numpy(sub).cuda(), 3)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_sub", [1, 7, 3000])
+def test_ids_in_no_order(lib, prec, n_sub):
+    """Subsamples dealt out at random over three realisations, slabs without a forest
+    and forests without a neighbour: the items are put in the order of their slab from
+    sky positions that change slab at every step."""
+    parts = [make_patch(n, w, 20 + n, npix_range=(1, 90), z_range=(2.1, 2.8)) for n, w in ((70, 1.2), (1, 0.1), (45, 6.0))]
+    F = concat_realisations(parts)
+    sub = np.random.default_rng(n_sub).integers(0, n_sub, F.n_forests).astype(np.int32)
+    ref = O.xi_sums(F, G60, sub=sub, n_sub=n_sub)
+    out = run_sub(lib, F, G60, sub, n_sub, precision=prec)
+    same, e_n, e_w = errors(out, ref, 3, n_sub, G60.n_bins)
+    print(f"[ids {prec} {n_sub}] pairs={int(ref.npairs.sum())} e_N={e_n:.2e} e_W={e_w:.2e}", flush=True)
+    assert same and e_n <= TOL[prec] and e_w <= TOL[prec]
