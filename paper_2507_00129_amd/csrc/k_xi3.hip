@@ -417,7 +417,9 @@ struct Lane3 {
 //
 // 2^20 + x, x the coordinate of cos alpha in bins, has the bin in its upper
 // word and the fraction in its lower one: three FMAs give both.  The bin is
-// settled by the definition where the fraction is within 1e-8 of an edge.
+// settled by the definition where the fraction is within 1e-8 of an edge; on axes
+// with bins so narrow that the coordinate's rounding reaches that (Xi3Args::near),
+// for every pair.
 //
 // Runs of consecutive j in one bin are summed in registers.  A finished run
 // waits in the lane (one slot) and goes to LDS only when some lane needs its
@@ -428,7 +430,6 @@ template <bool DIAG>
 __device__ __forceinline__ void sum_pairs(const Xi3Args& a, Xi3SmemP& sm, const CosAxis& cx, const Partner3* list,
                                           int j0, int j1, const Lane3& L, uint64_t on, int kpos, double c0) {
   constexpr uint32_t kMagicHi = 0x41300000u;  // upper word of 2^20
-  constexpr uint32_t kNear = 86u;             // 2e-8 in units of 2^-32
   const int nc = a.n_c;
   uint32_t key = 0, pkey = 0;  // bin minus (first j << 16); bin plus (count << 16)
   double rn = 0.0, rw = 0.0, pn = 0.0, pw = 0.0;
@@ -458,7 +459,7 @@ __device__ __forceinline__ void sum_pairs(const Xi3Args& a, Xi3SmemP& sm, const 
     if constexpr (DIAG) ok &= __ballot(j < kpos);
     const double u = fma(J.ux, L.kx, fma(J.uy, L.ky, fma(J.uz, L.kz, c0)));
     uint32_t kc = (uint32_t)__double2hiint(u) - kMagicHi;
-    const uint64_t near = ok & __ballot((uint32_t)__double2loint(u) <= kNear);
+    const uint64_t near = ok & __ballot((uint32_t)__double2loint(u) <= a.near);
     if (near) {
       if (lane_in(near)) {
         const Partner3 k = list[kpos];
@@ -741,6 +742,14 @@ int xi3_passes(int n_r, int n_t, int n_c, Pass3* out) {
     ++ca;
   }
   return n;
+}
+
+// The coordinate's rounding: three sides scaled by 1 / d (half an ulp each, at most
+// 1 / d in size), three FMAs and the axis origin, in all below 10 x 2^-53 / d bins,
+// and 2^-33 of the sum's last bit.
+uint32_t xi3_near(double c_inv) {
+  constexpr uint32_t kNear = 86u;  // 2e-8 bins in units of 2^-32: 1e-8 to either side
+  return c_inv <= 1e6 ? kNear : 0xffffffffu;
 }
 
 int xi3_partner_capacity() { return kCap3; }

@@ -438,6 +438,7 @@ struct Xi3Args {
   const double* cos_theta_edges;  // [n_t + 1] cosines of the theta edges (decreasing)
   const double* cos_edges;        // [n_c + 1]
   double r_e0, r_inv, c_e0, c_inv;
+  uint32_t near;          // pair kernel: largest fraction of a bin, in 2^-32, that is looked at again
   double* num;            // n_copies copies of the (half) sums, copy c at c * copy_stride
   double* wsum;
   unsigned long long* ntrip;
@@ -477,6 +478,7 @@ hipError_t launch_xi3_count(const Xi3Args& a, int64_t n_forests, hipStream_t st)
 hipError_t launch_xi3_pairs(const Xi3Args& a, int64_t n_forests, int blocks, hipStream_t st);
 hipError_t launch_xi3_expand(const Xi3Args& a, int64_t n, double* num, double* wsum, int64_t* ntrip, hipStream_t st);
 int xi3_passes(int n_r, int n_t, int n_c, Pass3* out);  // number of passes; fills out unless NULL
+uint32_t xi3_near(double c_inv);  // Xi3Args::near of a cos alpha axis
 int xi3_blocks_per_cu(bool pairs);
 bool xi3_can_combine(int n_r, int n_t, int n_c);
 int xi3_combine_capacity();

@@ -967,6 +967,7 @@ lya_status xi3_impl(lya_context* ctx, const lya_forests* F, const lya_grid3* G3,
     a.r_inv = r_inv;
     a.c_e0 = ce[0];
     a.c_inv = 1.0 / cd;
+    a.near = xi3_near(a.c_inv);
     a.sub = sub;
     a.n_sub = sub ? n_sub : 1;
     // variant 1: the direct kernel; 0 and 2: the pair kernel with partner limits

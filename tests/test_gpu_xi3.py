@@ -368,3 +368,24 @@ def test_xi3_pair_kernel_passes_vs_oracle(lib, n_r, n_t, n_c, cos_lo):
     F = concat_realisations(parts)
     G3 = O.Grid3(np.linspace(0.0, 35.0, n_r + 1), np.linspace(0.0, np.pi, n_t + 1), np.linspace(cos_lo, 1.0, n_c + 1))
     check3(run3(lib, F, G3, expect_variant=0), O.xi3_sums(F, G3), f"passes {n_r} {n_t} {n_c}")
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("width", [2.0 ** -36, 2.0 ** -20])
+def test_xi3_narrow_cos_bins(lib, variant, width):
+    """cos alpha bins of 1.5e-11 (and 9.5e-7) below 1: the coordinate in units of the
+    bin is then rounded by thousands of times the 1e-8 within which a bin is looked at
+    again (above by less).  Forests on one line of sight, whose sides lie along it:
+    every partner pair on the same side of the vertex has cos alpha = 1 to rounding, at
+    the closed upper edge and far from every other."""
+    F = truncate(make_patch(9, 0.4, 12, z_range=(2.1, 2.4)), 12)
+    F.ra[:5], F.dec[:5] = F.ra[0], F.dec[0]
+    F.dist += 0.37 * np.repeat(np.arange(9), np.diff(F.offsets))  # no two pixels in one place
+    G3 = O.Grid3(np.linspace(0.013, 29.2, 5), np.linspace(0.0, np.pi, 4), 1.0 - width * np.arange(16, -1, -1))
+    ref = O.xi3_sums(F, G3)
+    out = run3(lib, F, G3, variant=variant)
+    assert ref.ntrip.sum() > 10000
+    np.testing.assert_array_equal(out["ntrip"], ref.ntrip)
+    m = ref.absnum > 0
+    assert np.max(np.abs(out["num"] - ref.num)[m] / ref.absnum[m]) <= TOL
+    assert O.err_rel(out["wsum"], ref.wsum) <= TOL
