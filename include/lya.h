@@ -107,9 +107,10 @@ typedef struct {
 
 /* Bin edges (HOST pointers), strictly increasing, finite, edges[0] >= 0;
    bins are half-open, [e_k, e_k+1) (Sec. 2.1).  Edges uniformly spaced on both
-   axes (to 1e-9 of a bin) are binned from floor((r - e_0) / dr) with an FP64
-   edge guard; any other edges are binned by searching the FP64 edge arrays
-   for every pair in range (same results, slower).  n_par * n_perp <= 4096. */
+   axes (to 1e-9 of a bin, the last at most 1e6 bins from 0) are binned from
+   floor((r - e_0) / dr) with an FP64 edge guard; any other edges are binned by
+   the FP64 edge arrays for every pair in range (same results, slower).
+   n_par * n_perp <= 4096. */
 typedef struct {
   int32_t n_par;
   int32_t n_perp;

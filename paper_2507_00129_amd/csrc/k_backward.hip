@@ -105,8 +105,9 @@ __global__ __launch_bounds__(BLOCK, 8) void xi_bwd_kernel(BwdArgs) {
   const int lane = threadIdx.x & 63;
   BwdTab& tab = tabs[uniform((int)threadIdx.x >> 6)];
   const int NP = bargs()->g.n_par;
-  const double mp = uniform(kMagic + kGuard - bargs()->g.e0_par * bargs()->g.inv_par);
-  const double uphi = uniform(kMagic + NP + 2.0 * kGuard), uthi = uniform(kMagic + bargs()->g.n_perp + 2.0 * kGuard);
+  const double guard = bargs()->g.exact_all ? kWideGuard : kGuard;
+  const double mp = uniform(kMagic + guard - bargs()->g.e0_par * bargs()->g.inv_par);
+  const double uphi = uniform(kMagic + NP + 2.0 * guard), uthi = uniform(kMagic + bargs()->g.n_perp + 2.0 * guard);
   const uint32_t thr = bargs()->g.exact_all ? 0xffffffffu : kGuard2;
   // bins are carried as L = k_perp NP + k_par + G, G what the two upper words add
   const uint32_t G = (kMagicHi & 0xffffffu) * (uint32_t)NP + kMagicHi;
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(BLOCK, 8) void xi_bwd_kernel(BwdArgs) {
             const double s64 = tab.s[k], invt = a->g.inv_perp;
             cp = tab.c[k] * a->g.inv_par;
             st = s64 * invt;
-            bt = (Di * s64 - a->g.e0_perp) * invt + (kMagic + kGuard);
+            bt = (Di * s64 - a->g.e0_perp) * invt + (kMagic + (a->g.exact_all ? kWideGuard : kGuard));
           }
           if constexpr (sizeof(T) == 4) rg = a->xrec32 + gpix0; else rg = a->rec64 + gpix0;
           ext = a->ext + (gpix0 >> 5) + uniform(tab.f[k]);

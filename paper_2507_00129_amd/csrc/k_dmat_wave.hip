@@ -295,9 +295,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
 
   // bin coordinates 2^20 + x + guard (upper word: the bin, lower: the fraction)
   const int NP = dargs()->g.n_par;
-  const double mp = uniform(kMagic + kGuard - dargs()->g.e0_par * dargs()->g.inv_par);
-  const double mt = uniform(kMagic + kGuard - dargs()->g.e0_perp * dargs()->g.inv_perp);
-  const double uphi = uniform(kMagic + NP + 2.0 * kGuard), uthi = uniform(kMagic + dargs()->g.n_perp + 2.0 * kGuard);
+  const double guard = dargs()->g.exact_all ? kWideGuard : kGuard;
+  const double mp = uniform(kMagic + guard - dargs()->g.e0_par * dargs()->g.inv_par);
+  const double mt = uniform(kMagic + guard - dargs()->g.e0_perp * dargs()->g.inv_perp);
+  const double uphi = uniform(kMagic + NP + 2.0 * guard), uthi = uniform(kMagic + dargs()->g.n_perp + 2.0 * guard);
   const uint32_t thr = dargs()->g.exact_all ? 0xffffffffu : kGuard2;
   const uint32_t G = (kMagicHi & 0xffffffu) * (uint32_t)NP + kMagicHi;  // what the upper words add to k_perp NP + k_par
   auto records = []() __attribute__((always_inline)) {

@@ -46,10 +46,11 @@ struct BinK {
       taut = 1e-8;
     }
     if (g.exact_all) {
-      // non-uniform edges: a guard half width of a whole (mean) bin sends every
-      // pair in range to the FP64 search of the edge arrays
-      taup = (T)1;
-      taut = (T)1;
+      // binned by the edges: a guard half width of a whole (mean) bin, or the
+      // rounding's where that is larger, sends every pair in range to the FP64 search
+      // of the edge arrays
+      taup = fmax((T)1, taup);
+      taut = fmax((T)1, taut);
     }
     np_hi = (T)NP + taup;
     nt_hi = (T)NT + taut;

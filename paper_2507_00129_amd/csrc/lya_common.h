@@ -10,6 +10,10 @@
 namespace lya {
 
 constexpr int kMaxBins = 4096;     // n_par * n_perp limit (LDS histograms)
+// A uniform grid is binned by the coordinates x = r / dr of its pairs where the last edge
+// is at most this many bins from 0 (x is then good to 2^-33 + 4 x 2^-53 x 1e6 < 1e-9 bins,
+// a tenth of the edge guard), by its edge arrays beyond.
+constexpr double kUniformRange = 1e6;
 constexpr int kMaxStrips = 4096;   // declination strips of the sky index
 constexpr int kMaxRealisations = 1 << 20;
 constexpr int kXiCounters = 16, kXiCounterStride = 32;  // counters of an xi launch, a cache line each

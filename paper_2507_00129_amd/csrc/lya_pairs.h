@@ -15,7 +15,8 @@ constexpr int kWaitAll = 0x7fffffff;
 // word and the fraction in its lower word, in units of 2^-32.
 constexpr double kMagic = 1048576.0;
 constexpr uint32_t kMagicHi = 0x41300000u;
-constexpr double kGuard = 1e-8;        // edge guard, bins
+constexpr double kGuard = 1e-8;        // edge guard, bins (see kUniformRange)
+constexpr double kWideGuard = 0.25;    // where every pair in range goes by the edges
 constexpr uint32_t kGuard2 = 86u;      // 2 kGuard in units of 2^-32
 
 // How a kernel bins: uniform edges whose first ones are both 0 (the lower-edge tests

@@ -166,10 +166,11 @@ lya_status check_axis(lya_context* ctx, const double* e, int n, const char* axis
   for (int k = 0; k < n; ++k)
     if (!(e[k + 1] > e[k]))
       return fail(ctx, LYA_E_INVALID, "edges_%s not strictly increasing at %d", axis, k);
-  // uniform to 1e-9 of a bin: binned from floor(x) with the edge guard;
-  // otherwise every pair searches the edge array (GridDev::exact_all)
+  // uniform to 1e-9 of a bin and within the coordinates' range: binned from floor(x)
+  // with the edge guard; otherwise every pair searches the edge array
+  // (GridDev::exact_all)
   const double d = (e[n] - e[0]) / n;
-  uniform = true;
+  uniform = e[n] <= kUniformRange * d;
   for (int k = 0; k <= n; ++k)
     if (fabs(e[k] - (e[0] + k * d)) > 1e-9 * d) uniform = false;
   e0 = e[0];

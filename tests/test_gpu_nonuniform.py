@@ -185,3 +185,35 @@ def test_lanes_walk_along_the_edges(lib, grid, prec, n, npix, model):
     assert float(np.max(np.abs(out["rpar"] - rp))) / wp <= tol_r
     assert float(np.max(np.abs(out["rperp"] - rt))) / wt <= tol_r
     assert O.err_rel(out["z"], z) <= tol_z
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_uniform_edges_far_from_zero_in_bins(lib, prec):
+    """A uniform grid of 1.4e-12 Mpc/h bins from 96 Mpc/h on: the rounding of r / dr is
+    4e-3 bins, 400000 times the guard within which the edges are looked at.  Forests
+    on one line of sight and distances in units of a sixth of a bin, so that separations
+    are exact and every sixth pair lies on an edge: every kernel has to bin it above."""
+    n_bins, dr = 60, 3.0 * 2.0 ** -41
+    G = Grid(96.0 + dr * np.arange(n_bins + 1), np.array([0.0, 1.0]))
+    rng = np.random.default_rng(4)
+    F = make_patch(6, 0.3, 5, npix_range=(30, 60), z_range=(2.3, 2.4))
+    F.ra[:], F.dec[:] = F.ra[0], F.dec[0]
+    near = np.repeat(np.arange(6) < 3, np.diff(F.offsets))
+    unit = 2.0 ** -42
+    F.dist = np.where(near, 1000.0 + unit * rng.integers(0, 120, F.n_pix), 1096.0 + unit * rng.integers(0, 360, F.n_pix))
+    ref = O.xi_sums(F, G)
+    assert ref.npairs.sum() > 10000
+    dF = dev(F)
+    for out in [host(lib.xi(dF, G, precision=prec, variant=v)) for v in range(4)] + [host(lib.xi_means(dF, G, precision=prec))]:
+        np.testing.assert_array_equal(out["npairs"], ref.npairs)
+        assert O.err_rel(out["wsum"], ref.wsum) <= TOL[prec]
+    gxi = rng.normal(size=ref.xi.shape)
+    put = lambda x: torch.as_tensor(x, device="cuda:0")
+    got = lib.xi_backward(dF, G, put(gxi), put(ref.xi), put(ref.wsum), precision=prec)
+    for g, w in zip(got, O.xi_grad(F, G, gxi, ref.xi, ref.wsum)):
+        assert O.err_norm(g.cpu().numpy(), w) <= TOL[prec]
+    rd = O.dmat(F, G, O.dmat_pairs(F, G), O.IDENTITY)
+    for v in range(4):
+        out = host(lib.dmat(dF, G, precision=prec, eta="identity", variant=v, autotune=False))
+        assert O.err_rel(out["wsum_d"], rd.wd) <= TOL[prec]
+        assert O.err_rows(out["dmat"], rd.D) <= TOL[prec]
