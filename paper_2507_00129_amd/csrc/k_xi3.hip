@@ -309,9 +309,9 @@ __device__ __forceinline__ void each_candidate(const Xi3Args& a, int64_t nb0, in
 
 // Partners of every vertex pixel (cnt[pixel]) and the largest count.  A wave
 // per vertex pixel, lanes over the neighbours' pixels.
-__global__ __launch_bounds__(64 * kListWaves) void xi3_count_kernel(Xi3Args a) {
+__global__ __launch_bounds__(64 * kListWaves) void xi3_count_kernel(Xi3Args a, int p0) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t p = blockIdx.x / kListSplit;
+  const int64_t p = p0 + blockIdx.x / kListSplit;
   const int f = a.sorted[p];
   const ForestInfo fi = a.finfo[f];
   const int64_t nb0 = a.nb_off[p], nbc = a.nb_cnt[p];
@@ -335,11 +335,11 @@ __global__ __launch_bounds__(64 * kListWaves) void xi3_count_kernel(Xi3Args a) {
 // The partner lists of vertex pixels [v0, v0 + n_v), ordered by cell k_r n_t +
 // k_t: counts per cell in LDS, a scan (written as the cells' first positions),
 // then the partners go to their places.  A wave per vertex pixel.
-__global__ __launch_bounds__(64 * kListWaves) void xi3_fill_kernel(Xi3Args a) {
+__global__ __launch_bounds__(64 * kListWaves) void xi3_fill_kernel(Xi3Args a, int p0) {
   __shared__ int32_t cell_pos[kListWaves][kCellC];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int32_t* pos = cell_pos[wave];
-  const int64_t p = blockIdx.x / kListSplit;
+  const int64_t p = p0 + blockIdx.x / kListSplit;
   const int f = a.sorted[p];
   const ForestInfo fi = a.finfo[f];
   const int64_t nb0 = a.nb_off[p], nbc = a.nb_cnt[p];
@@ -688,14 +688,26 @@ hipError_t launch_xi3_direct(const Xi3Args& a, int blocks, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The list kernels over sorted positions, 2^20 of them a launch (2^31 threads; a launch
+// takes less than 2^32).
+template <typename Kernel>
+static hipError_t launch_lists(Kernel kernel, const Xi3Args& a, int64_t n_forests, hipStream_t st) {
+  constexpr int64_t kMost = 1 << 20;
+  for (int64_t p0 = 0; p0 < n_forests; p0 += kMost) {
+    const int64_t n = n_forests - p0 < kMost ? n_forests - p0 : kMost;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n * kListSplit)), dim3(64 * kListWaves), 0, st, a, (int)p0);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_xi3_count(const Xi3Args& a, int64_t n_forests, hipStream_t st) {
-  hipLaunchKernelGGL(xi3_count_kernel, dim3((unsigned)(n_forests * kListSplit)), dim3(64 * kListWaves), 0, st, a);
-  return hipGetLastError();
+  return launch_lists(xi3_count_kernel, a, n_forests, st);
 }
 
 hipError_t launch_xi3_pairs(const Xi3Args& a, int64_t n_forests, int blocks, hipStream_t st) {
-  hipLaunchKernelGGL(xi3_fill_kernel, dim3((unsigned)(n_forests * kListSplit)), dim3(64 * kListWaves), 0, st, a);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = launch_lists(xi3_fill_kernel, a, n_forests, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(xi3_pair_kernel, dim3(blocks), dim3(kBlock3), 0, st, a);
   return hipGetLastError();

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from synth import concat_realisations, make_config, make_patch, subset_forests
+from synth import Forests, concat_realisations, make_config, make_patch, subset_forests
 from synth.survey import nearest_to_centre
 
 from helpers import forests_from_dict, load_json, tiny, truncate
@@ -389,3 +389,24 @@ def test_xi3_narrow_cos_bins(lib, variant, width):
     m = ref.absnum > 0
     assert np.max(np.abs(out["num"] - ref.num)[m] / ref.absnum[m]) <= TOL
     assert O.err_rel(out["wsum"], ref.wsum) <= TOL
+
+
+def test_xi3_more_forests_than_one_launch_takes(lib):
+    """2.1e6 forests of one pixel, out of each other's reach, and twelve close together at
+    the end of the sky order: the partner lists' kernels take 8 workgroups of 256 threads
+    a forest, more threads than one launch can have."""
+    far = 2 ** 21 + 500
+    side = int(np.ceil(far ** 0.5))
+    k = np.arange(far)
+    near = tiny(5, n_forests=12, k=6, width_deg=0.1)
+    ra = np.concatenate([0.004 * (k % side), near.ra])
+    dec = np.concatenate([-0.7 + 1.4 * (k // side) / side, near.dec + 1.0])
+    cat = lambda name, fill: np.concatenate([np.full(far, fill), getattr(near, name)])
+    F = Forests(np.concatenate([k, far + near.offsets]).astype(np.int64), ra, dec, cat("dist", near.dist[0]),
+                cat("delta", 0.1), cat("weight", 1.0), cat("loglam", 8.2))
+    G3 = grid3(r_max=3.0, n_r=3, n_t=3, n_c=4)
+    only = near.copy()
+    only.dec = near.dec + 1.0
+    ref = O.xi3_sums(only, G3)
+    assert ref.ntrip.sum() > 1000
+    check3(run3(lib, F, G3, expect_variant=0), ref, "2.1e6 forests")
