@@ -22,6 +22,7 @@ struct Buf {
 };
 
 constexpr size_t kPinnedWords = 4096;
+constexpr int64_t kXi3ListBytes = (int64_t)4 << 30;
 
 struct lya_context {
   int device = 0;
@@ -36,6 +37,9 @@ struct lya_context {
   // the environment variable LYA_XI_FLUSH_PAIRS lowers it (a test hook that
   // exercises the flush on small inputs)
   double xi_flush_pairs = kXiFlushPairs;
+  // bytes of the 3PCF's partner lists of one batch of vertex pixels; the environment
+  // variable LYA_XI3_LIST_BYTES lowers it (a test hook: batches on small inputs)
+  int64_t xi3_list_bytes = kXi3ListBytes;
   // the no-allocation entry point carves its workspace from `scratch_base`
   // (this device's copy of the library's fixed scratch array) while `noalloc`
   // is set, bumping `scratch_off`
@@ -586,6 +590,10 @@ lya_status lya_create(lya_context** out, int device) {
     const double v = atof(fp);
     if (v >= 1.0 && v < kXiFlushPairs) ctx->xi_flush_pairs = v;
   }
+  if (const char* lb = getenv("LYA_XI3_LIST_BYTES")) {
+    const long long v = atoll(lb);
+    if (v >= 1 && v < kXi3ListBytes) ctx->xi3_list_bytes = v;
+  }
   *out = ctx;
   return LYA_OK;
 }
@@ -861,9 +869,8 @@ lya_status lya_xi_covariance(lya_context* ctx, const double* num, const double* 
   return LYA_OK;
 }
 
-// partner limit of one vertex pixel, and of the bytes of a batch's lists
+// partner limit of one vertex pixel
 constexpr int kXi3WideCap = 32768;
-constexpr int64_t kXi3ListBytes = (int64_t)4 << 30;
 
 namespace {
 
@@ -1045,10 +1052,10 @@ lya_status xi3_impl(lya_context* ctx, const lya_forests* F, const lya_grid3* G3,
         return fail(ctx, LYA_E_UNSUPPORTED, "more than %d partner pixels within r_max of one pixel%s", cap,
                     o->variant == 0 ? " (variant 0)" : "");
       ctx->stats.variant = o->variant >= 0 ? o->variant : (n_most > xi3_combine_capacity() ? 2 : 0);
-      // batches of vertex pixels whose lists fit kXi3ListBytes (at least one pixel)
+      // batches of vertex pixels whose lists fit xi3_list_bytes (at least one pixel)
       std::vector<int64_t> off;  // list offsets, only read where one batch does not hold them all
       const int64_t per_vertex = (ncell + 1) * 4 + (int64_t)sizeof(Vertex3);
-      const bool split = total * (int64_t)sizeof(Partner3) + npix * per_vertex > kXi3ListBytes;
+      const bool split = total * (int64_t)sizeof(Partner3) + npix * per_vertex > ctx->xi3_list_bytes;
       if (split) {
         off.resize((size_t)npix + 1);
         HIP_TRY(hipMemcpyAsync(off.data(), p_off, (size_t)npix * 8, hipMemcpyDeviceToHost, st));
@@ -1067,7 +1074,7 @@ lya_status xi3_impl(lya_context* ctx, const lya_forests* F, const lya_grid3* G3,
         if (split) {
           v1 = v0 + 1;
           while (v1 < npix && (off[v1 + 1] - off[v0]) * (int64_t)sizeof(Partner3) + (v1 + 1 - v0) * per_vertex <=
-                                  kXi3ListBytes)
+                                  ctx->xi3_list_bytes)
             ++v1;
         }
         const int64_t n_list = split ? off[v1] - off[v0] : total;

@@ -5,6 +5,8 @@ every entry to the global sums, variant 2 is variant 0 with the partner
 lists in global scratch for vertex pixels with many partners).  Entry counts must match exactly; N and W to
 1e-12 of the bin's absolute sum (FP64 throughout, only the summation order
 differs)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -410,3 +412,50 @@ def test_xi3_more_forests_than_one_launch_takes(lib):
     ref = O.xi3_sums(only, G3)
     assert ref.ntrip.sum() > 1000
     check3(run3(lib, F, G3, expect_variant=0), ref, "2.1e6 forests")
+
+
+@pytest.mark.parametrize("list_bytes", [1, 60000, 500000])
+@pytest.mark.parametrize("n_sub", [1, 3])
+def test_xi3_batches_of_vertex_pixels_vs_oracle(monkeypatch, list_bytes, n_sub):
+    """Partner lists beyond a limit (4 GiB) are made and summed for one batch of vertex
+    pixels after the other.  LYA_XI3_LIST_BYTES (read by lya_create) lowers it: to one
+    pixel a batch, some nine (a list is ~95 partners of 64 bytes and 1 KB of cells) and
+    four batches, which begin and end inside forests, on two realisations."""
+    from paper_2507_00129_amd import Library
+    parts = [truncate(make_patch(n, 0.5, 90 + n, z_range=(2.1, 2.3)), 15) for n in (9, 7)]
+    F = concat_realisations(parts)
+    G3 = grid3(r_max=30.0, n_r=15, n_t=15, n_c=6)
+    sub = (np.arange(F.n_forests) % n_sub).astype(np.int32)
+    monkeypatch.setenv("LYA_XI3_LIST_BYTES", str(list_bytes))
+    L = Library(0)
+    try:
+        if n_sub == 1:
+            check3(run3(L, F, G3, expect_variant=0), O.xi3_sums(F, G3), f"batches {list_bytes}")
+            return
+        out = run3_sub(L, F, G3, sub, n_sub, expect_variant=0)
+    finally:
+        L.close()
+    for s in range(n_sub):
+        ref = O.xi3_sums(F, G3, vertices=np.nonzero(sub == s)[0])
+        check3({k: v[:, s] for k, v in out.items()}, ref, f"batches {list_bytes} slab {s}")
+
+
+@pytest.mark.parametrize("n_r,n_t,n_c,cos_lo", [(10, 10, 20, -1.0), (7, 3, 9, -0.4)])
+def test_xi3_pair_kernel_against_the_direct_kernel(lib, n_r, n_t, n_c, cos_lo):
+    """The pair kernel writes both orders of an entry from one half bin; the direct
+    kernel adds each order by itself.  40 forests at eBOSS density to 40 Mpc/h: equal
+    counts, N and W to rounding, and the direct kernel's own symmetry."""
+    F, _, _ = make_config(1, seed=3, scale=0.05)
+    S = subset_forests(F, nearest_to_centre(F, 40))
+    G3 = grid3(r_max=40.0, n_r=n_r, n_t=n_t, n_c=n_c, c=(cos_lo, 1.0))
+    pair = run3(lib, S, G3, expect_variant=0)
+    direct = run3(lib, S, G3, variant=1, expect_variant=1)
+    assert direct["ntrip"].sum() > 1e6
+    np.testing.assert_array_equal(pair["ntrip"], direct["ntrip"])
+    c = direct["ntrip"][0].reshape(n_r, n_r, n_c, n_t, n_t)
+    np.testing.assert_array_equal(c, c.transpose(1, 0, 2, 4, 3))
+    A = dataclasses.replace(S, delta=np.abs(S.delta))
+    scale = run3(lib, A, G3, variant=1)["num"]
+    m = scale > 0
+    assert np.max(np.abs(pair["num"] - direct["num"])[m] / scale[m]) <= TOL
+    assert O.err_rel(pair["wsum"], direct["wsum"]) <= TOL
