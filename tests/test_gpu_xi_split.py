@@ -105,3 +105,32 @@ def test_bin_means_that_fill_the_lds(lib, prec, n_par, n_perp):
     ref = O.xi_sums(F, G)
     out = lib.xi_means(DeviceForests.from_host(F), G, precision=prec)
     compare({k: out[k].cpu().numpy() for k in ("npairs", "num", "wsum")}, ref, prec, (1, G.n_bins))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_par,n_perp", [(58, 60), (60, 60), (263, 14), (14, 263)])
+def test_bin_mean_coordinates_that_fill_the_lds(lib, prec, n_par, n_perp):
+    """The coordinates of the same bin means, the sums that only this form has.  A mean
+    is off by the coordinates' rounding in the working precision u (as bounded for the
+    FP32 edge guard, in bins: (2 M / dr + 3 (N + 2)) u and ((3 M + 2 D) s / dr + N + 2) u)
+    and by that of the runs of 32 terms of up to N in both sums (64 N u); the FP64
+    additions of the runs of a bin of n pairs add some sqrt(n) 2^-53 N."""
+    from paper_2507_00129_amd import DeviceForests
+    G = uniform_grid(n_par, 150.0, n_perp, 40.0)
+    F = make_patch(40, 0.6, 5, npix_range=(1, 140), z_range=(2.1, 2.6))
+    ref = O.xi_sums(F, G, means=True)
+    out = {k: v.cpu().numpy() for k, v in lib.xi_means(DeviceForests.from_host(F), G, precision=prec).items()}
+    np.testing.assert_array_equal(out["npairs"], ref.npairs)
+    u = {"fp64": 2.0 ** -53, "fp32": 2.0 ** -24}[prec]
+    acc = 8.0 * 2.0 ** -53 * float(ref.npairs.max()) ** 0.5
+    lo, hi = F.dist.min(), F.dist.max()
+    M, D, s = 0.5 * (hi - lo), 0.5 * (hi + lo), 40.0 / (2.0 * lo)
+    dp, dt = 150.0 / n_par, 40.0 / n_perp
+    tol_p = u * (2.0 * M / dp + 67.0 * (n_par + 2)) + acc * n_par
+    tol_t = u * ((3.0 * M + 2.0 * D) * s / dt + 65.0 * (n_perp + 2)) + acc * n_perp
+    tol_z = 70.0 * u + acc
+    for got, want, scale, tol in zip((out["rpar"], out["rperp"], out["z"]), O.bin_means(ref),
+                                     (dp, dt, 1.0), (tol_p, tol_t, tol_z)):
+        e = float(np.max(np.abs(got - want))) / scale
+        print(f"[{prec} {n_par}x{n_perp}] e={e:.2e} of {tol:.2e}", flush=True)
+        assert e <= tol and np.abs(want).max() > 0.0
