@@ -9,6 +9,7 @@
 
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -1057,7 +1058,11 @@ lya_status xi3_impl(lya_context* ctx, const lya_forests* F, const lya_grid3* G3,
       const int64_t per_vertex = (ncell + 1) * 4 + (int64_t)sizeof(Vertex3);
       const bool split = total * (int64_t)sizeof(Partner3) + npix * per_vertex > ctx->xi3_list_bytes;
       if (split) {
-        off.resize((size_t)npix + 1);
+        try {
+          off.resize((size_t)npix + 1);
+        } catch (const std::bad_alloc&) {
+          return fail(ctx, LYA_E_NOMEM, "host allocation of %lld list offsets failed", (long long)npix + 1);
+        }
         HIP_TRY(hipMemcpyAsync(off.data(), p_off, (size_t)npix * 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         off[npix] = total;
