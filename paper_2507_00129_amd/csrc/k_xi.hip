@@ -699,9 +699,10 @@ __global__ __launch_bounds__(BLOCK, MEANS ? 4 : 8) void xi_kernel(XiArgs) {
 }
 
 // Two forms, each with two workgroup sizes.  The larger size is the default:
-// most waves per CU, fewest copies of the histograms.  Runs where an r_par bin
-// holds at least 1.2 pixels of a forest; below, where a run would rarely hold two
-// pixels, every pair's products are added by themselves (xi_default_variant).
+// most waves per CU, fewest copies of the histograms; the smaller one is there for
+// options.variant.  Runs where an r_par bin holds at least 1.05 pixels of a forest;
+// below, where a run would rarely hold two pixels, every pair's products are added by
+// themselves (xi_default_variant).
 struct Variant {
   const char* name;
   int block;
@@ -844,7 +845,12 @@ __global__ void finalize_xi_kernel(const double* num, const double* wsum, double
 }  // namespace
 
 int xi_num_variants() { return kNumVariants; }
-int xi_default_variant(double bin_par, double spacing) { return bin_par < 1.2 * spacing ? 1 : 3; }
+// Direct and runs in ms at 1.25 / 1.1 / 1.0 / 0.8 pixels per bin, 2500 log forests to 200
+// Mpc/h in 10 r_perp bins: FP32 9.5, 5.8 / 8.9, 5.9 / 6.3, 6.0 / 6.9, 7.1; FP64 9.6, 6.3 /
+// 8.9, 6.3 / 6.3, 6.4 / 7.0, 7.2.  500 linear forests to 60: FP32 1.82, 1.56 / 1.67, 1.54 /
+// 1.63, 1.63 / 1.52, 1.68.  40 r_perp bins, FP32, at 1.1 and 1.0: 8.7, 6.1 and 6.4, 7.8.
+// (While bins and pixels are nearly as wide, lanes a bin apart meet on an address.)
+int xi_default_variant(double bin_par, double spacing) { return bin_par < 1.05 * spacing ? 1 : 3; }
 int xi_variant_block(int v) { return kVariants[v].block; }
 const char* xi_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVariants[v].name : "?"; }
 

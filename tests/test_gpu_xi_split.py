@@ -134,3 +134,17 @@ def test_bin_mean_coordinates_that_fill_the_lds(lib, prec, n_par, n_perp):
         e = float(np.max(np.abs(got - want))) / scale
         print(f"[{prec} {n_par}x{n_perp}] e={e:.2e} of {tol:.2e}", flush=True)
         assert e <= tol and np.abs(want).max() > 0.0
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("per_bin,variant", [(0.97, 1), (1.12, 3), (1.5, 3)])
+def test_form_by_pixels_per_bin(lib, prec, per_bin, variant):
+    """Runs from 1.05 pixels to an r_par bin on, single pairs below."""
+    from paper_2507_00129_amd import DeviceForests
+    F = make_patch(30, 0.5, 77, npix_range=(20, 120), z_range=(2.1, 2.6))
+    first, last = F.offsets[:-1], F.offsets[1:] - 1
+    spacing = float(np.sum(F.dist[last] - F.dist[first]) / (F.n_pix - F.n_forests))
+    G = uniform_grid(25, 25 * per_bin * spacing, 12, 40.0)
+    out = lib.xi(DeviceForests.from_host(F), G, precision=prec)
+    assert lib.last_stats()["variant"] == variant
+    compare({k: out[k].cpu().numpy() for k in ("npairs", "num", "wsum")}, O.xi_sums(F, G), prec, (1, G.n_bins))
