@@ -120,9 +120,12 @@ __device__ __forceinline__ void past_end(double& cp, double& bt) {
 
 // A wave's next `grab` tickets of n, the first of which is returned (~0u: none left),
 // from kXiCounters counters beyond the first `base` tickets, the workgroup's own
-// counter first.  gone (LDS): counters the workgroup has found empty.
+// counter first.  gone (LDS): counters the workgroup has found empty.  Nobody asks where
+// all tickets were dealt out beforehand: a round of 16 atomics that tell 8192 waves so
+// was two thirds of a small call's kernel (290 forests of 35 pixels: 83 us, 27 without).
 __device__ __forceinline__ unsigned grab_ticket(unsigned* counter, unsigned base, unsigned grab, unsigned n, int* gone) {
   unsigned t = ~0u;
+  if (base >= n) return t;
   if ((threadIdx.x & 63) == 0) {
     for (int k = *(volatile int*)gone; k < kXiCounters;) {
       const unsigned w = ((blockIdx.x >> 3) + k) % kXiCounters;
