@@ -312,8 +312,8 @@ def issued_valu_frac(kernel, source, ms):
     return rec["insts_valu_per_launch"] * 64 / (ms / 1e3) / PEAK_VALU_LANE_OPS
 
 
-XI_KERNELS = {0: "xi_kernel<float, 512, true, false, false, false, 16>", 1: "xi_kernel<float, 1024, true, false, false, false, 16>",
-              2: "xi_kernel<float, 512, true, true, false, false, 16>", 3: "xi_kernel<float, 1024, true, true, false, false, 16>"}
+XI_KERNELS = {0: "xi_kernel<float, 512, 0, false, false, false, 16>", 1: "xi_kernel<float, 1024, 0, false, false, false, 16>",
+              2: "xi_kernel<float, 512, 0, true, false, false, 16>", 3: "xi_kernel<float, 1024, 0, true, false, false, 16>"}
 
 
 def xi_roofline(r, peaks):

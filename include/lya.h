@@ -68,17 +68,22 @@ typedef enum {
 } lya_status;
 
 typedef enum {
-  /* Pair geometry and products in FP32 (distances re-centred so that
-     FP32 keeps ~1e-4 Mpc/h); pairs within rounding of a bin edge are re-binned
-     in FP64, so binning equals the FP64 decision.  xi: runs of at most 32
-     same-bin FP32 products are summed in FP32 registers and the run sums are
-     accumulated in FP64 (LDS, then global) -- FP64 accumulation, not a
-     compensated FP32 sum.  D: the row histograms and the row contraction are
-     FP32, accumulated in FP32 over a run of forest pairs and then added to
-     FP64 totals.  Per-forest projection sums and the final normalisation
-     are FP64. */
+  /* Products in FP32; bins from FP64 distances and separations, so binning
+     equals the FP64 decision (the 8-wave kernel of lya_dmat, variant 0, takes
+     them from re-centred FP32 distances and goes to FP64 within rounding of an
+     edge).  xi: runs of at most 32 same-bin FP32 products are summed in FP32
+     registers and the run sums are accumulated in FP64 (LDS, then global) --
+     FP64 accumulation, not a compensated FP32 sum.  The bin means' coordinates
+     are FP32 (distances re-centred so that FP32 keeps ~1e-4 Mpc/h).  Gradients:
+     FP32 sums over one pixel and neighbour forest, FP64 across forests.  D: the
+     row histograms are FP64 sums of FP32 values; the row contraction is FP32,
+     accumulated in FP32 over a run of forest pairs and then added to FP64
+     totals.  Per-forest projection sums and the final normalisation are
+     FP64. */
   LYA_FP32_COMP = 0,
-  /* Everything in FP64. */
+  /* Everything in FP64.  (In both forms sums meet in FP64 atomics, whose order is
+     not fixed: repeated calls differ in the last bits, the gradients' too.  See
+     lya_options.deterministic.) */
   LYA_FP64 = 1
 } lya_precision;
 

@@ -1019,13 +1019,13 @@ int wave_occupancy() {
 
 // The two variants per form.  FP32: the larger tile (160-bin windows, three
 // k_perp rows of 50 bins, in one pass) is split between the two waves of a
-// workgroup, each holding half of its accumulator blocks and binning one of
-// the two rows of a step, so that two waves fit on a SIMD (one wave holding
+// workgroup, each holding half of its accumulator blocks and binning two of
+// the four rows of a turn, so that two waves fit on a SIMD (one wave holding
 // the whole tile in AGPRs, one wave per SIMD, took 6 % longer); the smaller
 // tile runs one wave per workgroup, two per SIMD.  FP64: the larger tile runs
-// one wave per SIMD (split between two waves it spills registers and took 5 %
-// longer), the smaller two.  All are the largest that compile without (or
-// with a few bytes of) register spills.
+// one wave per SIMD (split between two waves it spilled more and took 5 %
+// longer), the smaller two.  Spilled vector / scalar registers: FP32 12 / 219
+// and 7 / 56, FP64 23 / 129 and 4 / 60.
 constexpr int kNB32[2] = {10, 8};
 constexpr int kNB64[2] = {7, 5};
 constexpr int kPMax = 4;    // FP32: 256 pixels of the other forest in registers at a time

@@ -1,7 +1,9 @@
-// Pair binning shared by the xi, distortion and backward kernels.
+// Pair separations (all pair kernels) and the binning of the 8-wave distortion kernel;
+// the others bin from FP64 coordinates (lya_pairs.h).
 //
-// On a grid with non-uniform edges the coordinates below use the mean bin width
-// and every pair in range takes the FP64 edge-array path (GridDev::exact_all).
+// On a grid with non-uniform edges, or far from zero in bins, the coordinates below use
+// the mean bin width and every pair in range takes the FP64 edge-array path
+// (GridDev::exact_all).
 //
 // A pair's bin coordinates are x = (r - e0) / dr on each axis.  In FP32 the
 // separations carry a bounded rounding error (tau bins, computed per call from

@@ -17,9 +17,9 @@ constexpr double kUniformRange = 1e6;
 constexpr int kMaxStrips = 4096;   // declination strips of the sky index
 constexpr int kMaxRealisations = 1 << 20;
 constexpr int kXiCounters = 16, kXiCounterStride = 32;  // counters of an xi launch, a cache line each
-constexpr int kChunkTight = 2;     // the same where the bin means fill the LDS
 constexpr size_t kLdsBytes = 160 * 1024;  // of a CU
-constexpr int kChunkMax = 16;      // neighbour forests per xi work item
+constexpr int kChunkMax = 16;      // neighbour forests per xi or backward work item
+constexpr int kChunkTight = 2;     // the same where the bin means fill the LDS
 
 // Per-forest geometry and layout, FP64 (64 bytes).
 struct ForestInfo {
@@ -81,9 +81,9 @@ struct GridDev {
   double inv_par, inv_perp;     // 1 / bin width
   double emax_par, emax_perp;   // last edges
   int32_t zero_lo_par, zero_lo_perp;  // first edge is exactly 0
-  // 0: uniformly spaced edges on both axes (bin = floor of the coordinate,
-  // edge guard only near integers); 1: other edges -- the coordinates use the
-  // mean bin width and every pair is binned by searching the FP64 edge arrays
+  // 0: uniformly spaced edges on both axes, within kUniformRange bins of 0 (bin =
+  // floor of the coordinate, edge guard only near integers); 1: other edges -- the
+  // coordinates use the mean bin width and every pair is binned by the FP64 edge arrays
   int32_t exact_all;
 };
 
@@ -403,7 +403,6 @@ struct BwdArgs {
   const double* delta;
   const double* edges_par;
   const double* edges_perp;
-  const Globals* glob;
   GridDev g;
   const double2* gtab;     // [R][nb] (gamma, gamma * xi) in local bin order
   int64_t n_pix;

@@ -1413,7 +1413,6 @@ lya_status lya_xi_backward(lya_context* ctx, const lya_forests* F, const lya_gri
     a.delta = project ? P.delta_proj : F->delta;
     a.edges_par = P.edges_par;
     a.edges_perp = P.edges_perp;
-    a.glob = P.glob;
     a.g = gd;
     a.gtab = gtab;
     a.grad_delta = grad_delta;
